@@ -14,7 +14,7 @@
 //                       largest 32-bit key with LDS histograms; index-ordered ties.
 //   tis_coef_kernel     many workgroups: per-token ratio, TIS weight, clip gate and
 //                       loss coefficient; partial sums of the loss in fp64
-//                       (tis_coef_step_kernel: one workgroup, step-level ratios).
+//                       (tis_coef_step_kernel: step-level ratios, one wave per step).
 //   tis_loss_finalize_kernel  adds the partial sums in a fixed order.
 //   select_coef_kernel  one workgroup: step_select_kernel's and tis_coef_kernel's
 //                       device code back to back (up to 4096 tokens), the
@@ -719,6 +719,7 @@ step_select_kernel(const float* __restrict__ H, int64_t T, const int32_t* __rest
 // ------------------------------------------------------------------------
 
 constexpr int kAdvThreads = 256;
+constexpr int64_t kAdvTokens = 2048, kAdvMaxPer = 16;
 
 // One workgroup per group. Over the group's steps (each step counts its
 // trajectory's reward once): mean and population standard deviation, summed
@@ -772,17 +773,18 @@ grpo_advantage_kernel(const float* __restrict__ reward, const int32_t* __restric
     }
     block_sum2(sq, unused);
     const double sd = cnt > 0.0 ? sqrt(sq / cnt) : 0.0;
-    if (tid == 0) {
+    if (tid == 0 && blockIdx.y == 0) {
         if (group_mean) group_mean[blockIdx.x] = (float)mean;
         if (group_std) group_std[blockIdx.x] = (float)sd;
     }
-    for (int64_t i = i0; i < i1; ++i) {
+    for (int64_t i = i0 + wave; i < i1; i += kAdvThreads / 64) {
         int64_t a, b;
         steps_of(i, a, b);
         const float A = sd > 0.0 ? (float)(((double)reward[i] - mean) / sd) : 0.f;
         const int64_t t0 = min(max((int64_t)off[a], (int64_t)0), T);
         const int64_t t1 = min(max((int64_t)off[b], t0), T);
-        for (int64_t t = t0 + tid; t < t1; t += kAdvThreads) adv[t] = A;
+        for (int64_t t = t0 + blockIdx.y * 64 + lane; t < t1; t += (int64_t)gridDim.y * 64)
+            adv[t] = A;
     }
 }
 
@@ -808,7 +810,7 @@ struct LossConfig {
 // Token ratios run on many workgroups (one CU cannot keep enough loads in
 // flight to read T tokens quickly); each writes the partial sums of its
 // tokens to a small workspace, and tis_loss_finalize_kernel adds them in
-// workgroup order. Step ratios run on one workgroup, one wave per step.
+// workgroup order. Step ratios run one wave per step, on many workgroups too.
 // Every sum is in fp64 and in a fixed order: per lane in token order, then a
 // fixed butterfly, then waves, then workgroups.
 
@@ -834,6 +836,9 @@ constexpr int64_t kSelCoefMaxT = 4096;
 constexpr int kCoefLdsSteps = 8192;  // offsets and mask of up to this many steps go to LDS
 constexpr int kStepCoefThreads = 1024;
 constexpr int kStepCoefWaves = kStepCoefThreads / 64;
+// up to this many steps (two a wave) the step ratios run on one workgroup also
+// with a workspace: beyond, the finalize kernel costs less than a third step
+constexpr int64_t kStepCoefOneBlockMaxS = 2 * kStepCoefWaves;
 
 // workgroups of the many-workgroup launch for T tokens
 __host__ __device__ constexpr int64_t coef_blocks(int64_t T) {
@@ -1192,13 +1197,23 @@ select_coef_kernel(const float* __restrict__ H, int64_t T, const int32_t* __rest
                                               off_l, mask_l, red, x);
 }
 
-// Step ratios: one workgroup, one wave per step, the step's sums first.
+// Step ratios: one wave per step, the step's sums first. Workgroup b takes
+// steps b * kStepCoefWaves + wave, then every gridDim.x * kStepCoefWaves-th;
+// with part != null it writes its partial sums there (workgroup 0 also N and
+// K) for tis_loss_finalize_kernel, with part == null the grid is one workgroup,
+// which writes the loss and stats itself.
+// A step costs a wave ~2 us of dependent loads and fp64 arithmetic, whatever
+// its length up to a few hundred tokens, so the steps have to run beside each
+// other: 1600 steps of 95 tokens took 200 us on one workgroup (100 steps a
+// wave). A lane's next kStepBatch tokens are loaded together.
+constexpr int kStepBatch = 4;
 __global__ void __launch_bounds__(kStepCoefThreads)
 tis_coef_step_kernel(int64_t T, const float* __restrict__ logp, const float* __restrict__ lp_old,
                      const float* __restrict__ lp_roll, const float* __restrict__ lp_ref,
                      const float* __restrict__ adv, const int32_t* __restrict__ off, int64_t S,
                      const uint8_t* __restrict__ mask, LossConfig cfg, float* __restrict__ coef,
-                     double* __restrict__ loss, float* __restrict__ stats, int nstats) {
+                     double* __restrict__ part, double* __restrict__ loss,
+                     float* __restrict__ stats, int nstats) {
     __shared__ int64_t red_i[2][kStepCoefWaves];
     __shared__ double red_d[kParts][kStepCoefWaves];
 
@@ -1207,13 +1222,18 @@ tis_coef_step_kernel(int64_t T, const float* __restrict__ logp, const float* __r
     const int wave = tid >> 6;
     int64_t N, K;
     count_kept<kStepCoefThreads>(off, mask, S, T, nullptr, nullptr, red_i, N, K);
+    if (part && blockIdx.x == 0 && tid == 0) {
+        part[(int64_t)gridDim.x * kParts] = (double)N;
+        part[(int64_t)gridDim.x * kParts + 1] = (double)K;
+    }
 
     const double inv_n = N > 0 ? 1.0 / (double)N : 0.0;
     const float lo = 1.f - cfg.eps_low, hi = 1.f + cfg.eps_high;
     const bool with_kl = cfg.kl != DART_KL_NONE;
     const double beta = (double)cfg.beta;
     double acc[kParts] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int64_t s = wave; s < S; s += kStepCoefWaves) {
+    for (int64_t s = (int64_t)blockIdx.x * kStepCoefWaves + wave; s < S;
+         s += (int64_t)gridDim.x * kStepCoefWaves) {
         int64_t b, e;
         step_bounds(off, s, T, b, e);
         const int64_t len = e - b;
@@ -1226,10 +1246,26 @@ tis_coef_step_kernel(int64_t T, const float* __restrict__ logp, const float* __r
         if (cfg.agg == DART_AGG_TOKEN_MEAN_ALL) om = 1.0 / (double)T;
         if (cfg.agg == DART_AGG_STEP_MEAN) om = 1.0 / ((double)K * (double)len);
         double slr = 0.0, slw = 0.0, sa = 0.0, dlog = 1.0;
-        for (int64_t t = b + lane; t < e; t += 64) {
-            slr += (double)logp[t] - (double)lp_old[t];
-            slw += (double)lp_old[t] - (double)lp_roll[t];
-            sa += (double)adv[t];
+        for (int64_t t0 = b + lane; t0 < e; t0 += 64 * kStepBatch) {
+            float lp[kStepBatch], lpo[kStepBatch], lpr[kStepBatch], A[kStepBatch];
+#pragma unroll
+            for (int j = 0; j < kStepBatch; ++j) {
+                const int64_t t = t0 + 64 * j;
+                // tokens past the step's end add exact zeros
+                lp[j] = lpo[j] = lpr[j] = A[j] = 0.f;
+                if (t < e) {
+                    lp[j] = logp[t];
+                    lpo[j] = lp_old[t];
+                    lpr[j] = lp_roll[t];
+                    A[j] = adv[t];
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < kStepBatch; ++j) {
+                slr += (double)lp[j] - (double)lpo[j];
+                slw += (double)lpo[j] - (double)lpr[j];
+                sa += (double)A[j];
+            }
         }
         slr = wave_sum(slr);
         slw = wave_sum(slw);
@@ -1262,7 +1298,12 @@ tis_coef_step_kernel(int64_t T, const float* __restrict__ logp, const float* __r
         }
     }
     block_sum_parts<kStepCoefThreads>(acc, red_d);
-    if (tid == 0) write_loss(acc, (double)N, (double)K, loss, stats, nstats);
+    if (tid != 0) return;
+    if (part)
+#pragma unroll
+        for (int i = 0; i < kParts; ++i) part[(int64_t)blockIdx.x * kParts + i] = acc[i];
+    else
+        write_loss(acc, (double)N, (double)K, loss, stats, nstats);
 }
 
 // Adds the nblocks partial sums in workgroup order and writes the loss and
@@ -1394,19 +1435,26 @@ dart_status_t launch_status() {
     return hipGetLastError() == hipSuccess ? DART_OK : DART_ERR_HIP;
 }
 
-// K3 and the loss reduction for one configuration: step ratios on one
-// workgroup; token ratios on up to kCoefMaxBlocks workgroups plus the
-// finalize kernel when a workspace is given and T > kCoefOneBlockMaxT, else
-// on one workgroup.
+// K3 and the loss reduction for one configuration: up to kCoefMaxBlocks
+// workgroups plus the finalize kernel when a workspace is given and T >
+// kCoefOneBlockMaxT (token ratios) or S > kStepCoefOneBlockMaxS (step ratios),
+// else one workgroup.
 dart_status_t launch_tis_coef(bool general, int64_t T, const float* logp, const float* lp_old,
                               const float* lp_roll, const float* lp_ref, const float* adv,
                               const int32_t* off, int64_t S, const uint8_t* mask,
                               const LossConfig& cfg, float* coef, double* loss, float* stats,
                               int nstats, void* workspace, hipStream_t stream) {
     if (general && cfg.ratio != DART_RATIO_TOKEN) {
-        hipLaunchKernelGGL(tis_coef_step_kernel, dim3(1), dim3(kStepCoefThreads), 0, stream, T,
-                           logp, lp_old, lp_roll, lp_ref, adv, off, S, mask, cfg, coef, loss,
-                           stats, nstats);
+        // never more workgroups than the workspace has room for
+        const int64_t want = (S + kStepCoefWaves - 1) / kStepCoefWaves, room = coef_blocks(T);
+        const int64_t nb = !workspace || S <= kStepCoefOneBlockMaxS ? 1 : want < room ? want : room;
+        double* part = nb > 1 ? static_cast<double*>(workspace) : nullptr;
+        hipLaunchKernelGGL(tis_coef_step_kernel, dim3((unsigned)nb), dim3(kStepCoefThreads), 0,
+                           stream, T, logp, lp_old, lp_roll, lp_ref, adv, off, S, mask, cfg, coef,
+                           part, loss, stats, nstats);
+        if (part)
+            hipLaunchKernelGGL(tis_loss_finalize_kernel, dim3(1), dim3(kCoefThreads), 0, stream,
+                               part, nb, loss, stats, nstats);
         return launch_status();
     }
     if (!workspace || T <= kCoefOneBlockMaxT) {
@@ -1637,7 +1685,12 @@ dart_status_t dart_grpo_advantage(const float* reward, int64_t n_traj,
                      {dart_check::Item::Offsets, group_traj_offsets, G, n_traj},
                      {dart_check::Item::Offsets, step_offsets, S, T}}); ck != DART_OK)
         return ck;
-    hipLaunchKernelGGL(grpo_advantage_kernel, dim3((unsigned)G), dim3(kAdvThreads), 0, stream,
+    // workgroups per group: one per kAdvTokens tokens of an average group, while
+    // the dispatch holds them
+    int64_t per = T / (G * kAdvTokens);
+    per = per < 1 ? 1 : per > kAdvMaxPer ? kAdvMaxPer : per;
+    if (!grid_fits(G * per, kAdvThreads)) per = 1;
+    hipLaunchKernelGGL(grpo_advantage_kernel, dim3((unsigned)G, (unsigned)per), dim3(kAdvThreads), 0, stream,
                        reward, traj_step_offsets, n_traj, group_traj_offsets, step_offsets, S, T,
                        adv, group_mean, group_std);
     return launch_status();

@@ -1,0 +1,93 @@
+"""The kernels on both sides of the sizes and alignments at which their launch
+shape changes: against the oracle, or bit for bit against the same call in the
+shape that the oracle tests cover."""
+
+import numpy as np
+import pytest
+
+import oracle
+from tests import _harness as H
+
+pytestmark = pytest.mark.gpu
+
+
+def _cuda(a):
+    import torch
+
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def _loss_inputs(rng, lens):
+    T = int(np.sum(lens))
+    off = np.r_[0, np.cumsum(lens)].astype(np.int32)
+    logp = (-rng.random(T) * 5.0).astype(np.float32)
+    lp_old = (logp + rng.uniform(-0.4, 0.4, T)).astype(np.float32)
+    lp_roll = (lp_old + rng.uniform(-3.0, 3.0, T)).astype(np.float32)
+    lp_ref = (logp + rng.uniform(-0.5, 0.5, T)).astype(np.float32)
+    adv = rng.choice([-1.0, 1.0, 0.5], T).astype(np.float32)
+    mask = (rng.random(len(lens)) < 0.6).astype(np.uint8)
+    mask[0] = 1
+    return logp, lp_old, lp_roll, lp_ref, adv, off, mask
+
+
+@pytest.mark.parametrize("kl,ratio", [("none", "step_geomean"), ("k3", "step_product")])
+@pytest.mark.parametrize("S,length", [
+    (1, 3),        # one wave with a step
+    (32, 40),      # the last size on one workgroup
+    (33, 40),      # the first on several, the second workgroup's waves mostly idle
+    (48, 257),     # a lane's second batch of tokens holds one token
+    (3000, 1),     # fewer workgroups than the steps ask for (the workspace's room)
+    (700, 256),
+])
+def test_step_ratio_launch_shapes(S, length, kl, ratio):
+    """Coefficients bit for bit those of the one-workgroup launch, the loss the
+    same fp64 sum in another order, and both the oracle's."""
+    import paper_2509_23866_amd as dart
+
+    rng = np.random.default_rng(S * 1000 + length)
+    lens = np.full(S, length) if length == 1 else rng.integers(max(1, length - 2), length + 1, S)
+    lens[-1] = length
+    logp, lp_old, lp_roll, lp_ref, adv, off, mask = _loss_inputs(rng, lens)
+    eps_low, eps_high, C = H.f32(0.2), H.f32(0.28), H.f32(2.0)
+    ref = oracle.tis_loss_ex(logp.astype(np.float64), lp_old, lp_roll, adv, off, mask, eps_low,
+                             eps_high, C, lp_ref=lp_ref, kl=kl, beta=0.05, agg="step_mean",
+                             ratio=ratio)
+    args = [_cuda(a) for a in (logp, lp_old, lp_roll, adv, off, mask)]
+    got = {}
+    for ws in ("auto", None):
+        got[ws] = dart.dart_tis_loss_fwd_ex(*args, eps_low, eps_high, C, logp_ref=_cuda(lp_ref),
+                                            kl=kl, beta=0.05, aggregation="step_mean",
+                                            ratio=ratio, workspace=ws)
+    (la, ca, sa), (lb, cb, sb) = got["auto"], got[None]
+    assert np.array_equal(ca.cpu().numpy().view(np.uint32), cb.cpu().numpy().view(np.uint32))
+    assert abs(la.item() - lb.item()) <= 1e-12 * max(abs(lb.item()), 1e-300)
+    assert np.allclose(sa.cpu().numpy(), sb.cpu().numpy(), rtol=1e-6, atol=0)
+    ok = ~ref["boundary"]
+    g = ca.cpu().numpy().astype(np.float64)
+    floor = 1e-6 * np.abs(ref["g"]).max()
+    assert np.all((np.abs(g - ref["g"]) <= 1e-4 * np.abs(ref["g"]) + floor)[ok])
+    if ok.all():
+        assert abs(la.item() - ref["L"]) <= H.LOSS_RTOL * max(abs(ref["L"]), 1e-30)
+
+
+@pytest.mark.parametrize("G,T", [(1, 2048), (2, 9000), (3, 40000), (1, 70000)])
+def test_grpo_advantage_several_workgroups_a_group(G, T):
+    """1, 2, 6 and 16 workgroups a group; trajectories shorter than a run of 64
+    tokens among them."""
+    import paper_2509_23866_amd as dart
+
+    rng = np.random.default_rng(T)
+    n_traj = 7 * G
+    cut = lambda n, k: np.r_[0, np.sort(rng.choice(np.arange(1, n), k - 1, False)), n].astype(np.int32)  # noqa: E731
+    S = 5 * n_traj
+    off, traj = cut(T, S), cut(S, n_traj)
+    grp = (np.arange(G + 1) * 7).astype(np.int32)
+    reward = rng.random(n_traj).astype(np.float32)
+    A, mean, std = oracle.grpo_advantage(reward, traj, grp, off)[:3]
+    adv = _cuda(np.full(T, np.nan, np.float32))
+    adv, gm, gs = dart.dart_grpo_advantage(_cuda(reward), _cuda(traj), _cuda(grp), _cuda(off), T=T,
+                                           adv=adv)
+    # one rounding to fp32 of a value formed in fp64 on both sides
+    assert np.all(np.abs(adv.cpu().numpy() - A) <= 2.0 ** -23 * np.abs(A))
+    assert np.allclose(gm.cpu().numpy(), mean, rtol=2.0 ** -23, atol=0)
+    assert np.allclose(gs.cpu().numpy(), std, rtol=2.0 ** -23, atol=0)
