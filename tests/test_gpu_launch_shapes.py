@@ -91,3 +91,44 @@ def test_grpo_advantage_several_workgroups_a_group(G, T):
     assert np.all(np.abs(adv.cpu().numpy() - A) <= 2.0 ** -23 * np.abs(A))
     assert np.allclose(gm.cpu().numpy(), mean, rtol=2.0 ** -23, atol=0)
     assert np.allclose(gs.cpu().numpy(), std, rtol=2.0 ** -23, atol=0)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V,pad", [(1, 2), (7, 1), (50, 3), (2049, 0), (4099, 9)])
+def test_gradient_rows_aligned_unlike_the_logits(dtype, V, pad):
+    """Every alignment of the logits against every alignment of the gradient
+    gives the bits of the call on 16-byte aligned rows, reads nothing outside
+    the rows (NaN there) and writes nothing outside them."""
+    import torch
+
+    import paper_2509_23866_amd as dart
+
+    T = 9
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    per = 8 if dtype == "bf16" else 4
+    g = torch.Generator(device="cuda").manual_seed(V)
+    z = (torch.randn(T, V, generator=g, device="cuda") * 3).to(dt)
+    y = torch.randint(V, (T,), generator=g, device="cuda", dtype=torch.int32)
+    wide = -(-V // per) * per
+
+    def rows(offset, ld, fill):
+        buf = torch.full((offset + T * ld + per,), fill, dtype=dt, device="cuda")
+        return buf, buf[offset:offset + T * ld].view(T, ld)[:, :V]
+
+    _, za = rows(0, wide, float("nan"))
+    za.copy_(z)
+    logp, ent, lse = dart.dart_tok_stats(za, y)
+    coef = torch.randn(T, generator=g, device="cuda") * 0.1
+    coef[3] = 0.0
+    _, want = rows(0, wide, 7.0)
+    for skip in (False, True):
+        dart.dart_tis_grad(za, y, logp, lse, coef, dlogits=want, skip_zero_rows=skip)
+        for a in range(per):
+            for b in range(per):
+                _, zi = rows(a, V + pad, float("nan"))
+                zi.copy_(z)
+                buf, out = rows(b, V + (pad + a) % 3, 7.0)
+                dart.dart_tis_grad(zi, y, logp, lse, coef, dlogits=out, skip_zero_rows=skip)
+                assert torch.equal(out, want), (a, b, skip)
+                out.fill_(7.0)
+                assert bool((buf == 7.0).all()), (a, b, skip)
