@@ -533,6 +533,17 @@ size_t dart_lmhead_backward_ex_workspace_bytes(int64_t T, int64_t d, int64_t V,
                                                int64_t chunk_rows, int64_t chunk_cols,
                                                uint32_t flags);
 
+/* Bytes of workspace with which dart_lmhead_backward_ex is fastest (host only;
+ * 0 for bad arguments or flags): the value above and, where a block has few
+ * rows, room for dhidden's sum over the vocabulary in several fp32 parts of
+ * min(chunk_rows, T) * d that run beside each other (together at most 64 MiB
+ * where T and d are multiples of 256). A workspace of at least this size takes
+ * the parts (one more rounding to fp32 per part in dhidden's sum), a smaller
+ * one sums each element in one run. */
+size_t dart_lmhead_backward_split_workspace_bytes(int64_t T, int64_t d, int64_t V,
+                                                  int64_t chunk_rows, int64_t chunk_cols,
+                                                  uint32_t flags);
+
 /* Host helper (no device work): k = clamp(ceil(rho * S - 1e-6), 0, S), the
  * number of steps dart_step_select keeps (the guard absorbs the representation
  * error of rho: 0.8 * 240 gives 192). Returns -1 for S < 0 or rho outside

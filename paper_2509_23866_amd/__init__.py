@@ -42,7 +42,8 @@ EXPORTED = ("dart_tok_stats", "dart_step_select", "dart_tis_loss_fwd_bwd", "dart
             "dart_lmhead_tok_stats", "dart_lmhead_tok_stats_ex", "dart_lmhead_stats_workspace_bytes",
             "dart_lmhead_dlogits", "dart_lmhead_dlogits_ex",
             "dart_lmhead_backward", "dart_lmhead_backward_workspace_bytes",
-            "dart_lmhead_backward_ex", "dart_lmhead_backward_ex_workspace_bytes", "dart_kept_steps",
+            "dart_lmhead_backward_ex", "dart_lmhead_backward_ex_workspace_bytes",
+            "dart_lmhead_backward_split_workspace_bytes", "dart_kept_steps",
             "dart_status_string")
 
 
@@ -140,6 +141,9 @@ def load_library():
         lib.dart_lmhead_backward_ex_workspace_bytes.restype = ctypes.c_size_t
         lib.dart_lmhead_backward_ex_workspace_bytes.argtypes = [_I64, _I64, _I64, _I64, _I64,
                                                                 ctypes.c_uint32]
+        lib.dart_lmhead_backward_split_workspace_bytes.restype = ctypes.c_size_t
+        lib.dart_lmhead_backward_split_workspace_bytes.argtypes = [_I64, _I64, _I64, _I64, _I64,
+                                                                   ctypes.c_uint32]
         lib.dart_kept_steps.restype = _I64
         lib.dart_kept_steps.argtypes = [_I64, ctypes.c_double]
         lib.dart_status_string.restype = ctypes.c_char_p
@@ -639,6 +643,12 @@ def dart_lmhead_backward_ex_workspace_bytes(T: int, d: int, V: int, chunk_rows: 
         int(T), int(d), int(V), int(chunk_rows), int(chunk_cols), int(flags)))
 
 
+def dart_lmhead_backward_split_workspace_bytes(T: int, d: int, V: int, chunk_rows: int,
+                                               chunk_cols: int, flags: int) -> int:
+    return int(load_library().dart_lmhead_backward_split_workspace_bytes(
+        int(T), int(d), int(V), int(chunk_rows), int(chunk_cols), int(flags)))
+
+
 def _lmhead_common(hidden, weight, target, lse, logp, tok_coef):
     torch = _torch()
     _matrix_bf16("hidden", hidden)
@@ -696,8 +706,7 @@ def _lmhead_backward(name, flags, hidden, weight, target, lse, logp, tok_coef, c
     if isinstance(workspace, str):
         if workspace != "auto":
             raise ValueError('workspace must be "auto" or a uint8 device tensor')
-        nbytes = (dart_lmhead_backward_workspace_bytes(chunk_rows, V) if flags is None else
-                  dart_lmhead_backward_ex_workspace_bytes(T, d, V, chunk_rows, chunk_cols, f))
+        nbytes = dart_lmhead_backward_split_workspace_bytes(T, d, V, chunk_rows, chunk_cols, f)
         if nbytes == 0:
             raise ValueError(f"{name}: bad sizes or flags")
         workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev)
@@ -744,7 +753,8 @@ def dart_lmhead_backward_ex(hidden, weight, target, lse, logp, tok_coef, chunk_r
     (the call synchronises the stream once).
     ``workspace`` is "auto" or a uint8 device tensor of
     dart_lmhead_backward_ex_workspace_bytes(T, d, V, chunk_rows, chunk_cols, flags)
-    bytes."""
+    bytes; one of dart_lmhead_backward_split_workspace_bytes(...), as "auto" allocates, is
+    faster where a block has few rows."""
     if chunk_rows is None and chunk_cols is None:
         chunk_rows, chunk_cols = lmhead_backward_plan(hidden.shape[0], weight.shape[0])
     elif chunk_rows is None or chunk_cols is None:

@@ -711,7 +711,8 @@ static_assert(LmCfg::BM == kTw && LmCfg::BN == kTw, "transposed rows are one til
 // Slot of chunk c of row k of a transposed operand tile.
 __device__ __forceinline__ int tr_slot(int c, int k) { return c ^ (4 * (k & 3)); }
 
-// acc = this wave's part of C[m0:m0+BM, n0:n0+BN] = A B over k in [0, K).
+// acc = this wave's part of C[m0:m0+BM, n0:n0+BN] = A B over k in [kbeg, K), kbeg
+// a multiple of BK.
 // A_KMAJ: A(m, k) = A[m lda + k], else A(m, k) = A[k lda + m]. B(k, n) =
 // B[k ldb + n]. Rows and columns past M, N read zero or whatever lies there
 // in the matrices (their results are not stored); k past K is zero in LDS
@@ -722,8 +723,8 @@ __device__ __forceinline__ int tr_slot(int c, int k) { return c ^ (4 * (k & 3));
 template <class C, bool A_KMAJ>
 __device__ __forceinline__ void gemm_tile_bwd(const uint16_t* __restrict__ A, int64_t lda,
                                               const uint16_t* __restrict__ B, int64_t ldb,
-                                              int64_t M, int64_t N, int64_t K, int64_t m0,
-                                              int64_t n0, typename C::Smem& sm,
+                                              int64_t M, int64_t N, int64_t kbeg, int64_t K,
+                                              int64_t m0, int64_t n0, typename C::Smem& sm,
                                               f32x16 (&acc)[C::TM][C::TN]) {
 #if defined(__HIP_DEVICE_COMPILE__)
     static_assert(C::BK == 64 && C::BM == kTw && C::BN == kTw, "backward tile");
@@ -934,8 +935,8 @@ __device__ __forceinline__ void gemm_tile_bwd(const uint16_t* __restrict__ A, in
         }
         __builtin_amdgcn_s_setprio(0);
     };
-    if (nk > 0) issue(0, 0);
-    int64_t kt = 0;
+    int64_t kt = kbeg / BK;
+    if (kt < nk) issue(kt, 0);
     for (; kt + 1 < nk; kt += 2) {
         slice(std::integral_constant<int, 0>{}, kt);
         slice(std::integral_constant<int, 1>{}, kt + 1);
@@ -943,8 +944,8 @@ __device__ __forceinline__ void gemm_tile_bwd(const uint16_t* __restrict__ A, in
     if (kt < nk) slice(std::integral_constant<int, 0>{}, kt);
     __syncthreads();
 #else
-    (void)A, (void)lda, (void)B, (void)ldb, (void)M, (void)N, (void)K, (void)m0, (void)n0;
-    (void)sm, (void)acc;
+    (void)A, (void)lda, (void)B, (void)ldb, (void)M, (void)N, (void)kbeg, (void)K, (void)m0;
+    (void)n0, (void)sm, (void)acc;
 #endif
 }
 
@@ -966,6 +967,9 @@ struct BwdGemm {
     const int32_t* dyn;
     int64_t dyn_base;
     bool dyn_m, dyn_k;
+    // the sum over k in ksplit parts of kper (a multiple of BK), part i written
+    // to out + i * part_stride elements
+    int64_t ksplit, kper, part_stride;
 };
 
 // Output modes of a backward GEMM: fp32 written, fp32 added to, bf16 written.
@@ -992,7 +996,7 @@ template <class C, bool A_KMAJ, int OUT>
 __device__ __forceinline__ void bwd_gemm_tile(const BwdGemm& g, int64_t b, typename C::Smem& sm) {
     using OutT = typename std::conditional<OUT == kOutBf16, uint16_t, float>::type;
     constexpr bool ACC = OUT == kOutF32Acc;
-    int64_t M = g.M, K = g.K, nmt = g.nmt;
+    int64_t M = g.M, K = g.K, nmt = g.nmt, kbeg = 0;
     const int64_t N = g.N;
     if (g.dyn) {
         const int64_t live = (int64_t)*g.dyn - g.dyn_base;
@@ -1004,21 +1008,29 @@ __device__ __forceinline__ void bwd_gemm_tile(const BwdGemm& g, int64_t b, typen
             // the tiles laid over the live rows' tiles (spread over every XCD)
             M = lim;
             nmt = (M + C::BM - 1) / C::BM;
-            if (b >= nmt * g.nnt) return;
+            if (b >= nmt * g.nnt * g.ksplit) return;
         }
     }
     int64_t mt, nt;
-    tile_of_block_nfast(b, nmt, g.nnt, mt, nt);
+    tile_of_block_nfast(b, nmt * g.ksplit, g.nnt, mt, nt);
+    OutT* out = static_cast<OutT*>(g.out);
+    if (g.ksplit > 1) {  // row tiles of part 0, then of part 1, ...
+        const int64_t part = mt / nmt;
+        mt -= part * nmt;
+        out += part * g.part_stride;
+        kbeg = part * g.kper;
+        K = kbeg + g.kper < K ? kbeg + g.kper : K;
+        if (kbeg >= K && ACC) return;
+    }
     const int64_t m0 = mt * C::BM, n0 = nt * C::BN;
     f32x16 acc[C::TM][C::TN];
-    gemm_tile_bwd<C, A_KMAJ>(g.A, g.lda, g.B, g.ldb, M, N, K, m0, n0, sm, acc);
+    gemm_tile_bwd<C, A_KMAJ>(g.A, g.lda, g.B, g.ldb, M, N, kbeg, K, m0, n0, sm, acc);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wr = (wave / C::WN) * 32, wc = (wave % C::WN) * (C::BN / C::WN);
     constexpr bool F32 = OUT != kOutBf16;
     constexpr int EPV = F32 ? 4 : 8;  // elements per 16-byte vector
     constexpr int VPR = C::BN / EPV;  // vectors per tile row
-    OutT* out = static_cast<OutT*>(g.out);
     static_assert(C::EPI == C::RS, "one row block of every wave per pass");
 #pragma unroll
     for (int ip = 0; ip < C::TM; ++ip) {
@@ -1081,7 +1093,7 @@ lmhead_bwd_gemms_kernel(BwdGemm dh, BwdGemm dw, int64_t n_dh) {
     __shared__ typename C::Smem sm;
     const int64_t b = blockIdx.x;
     if (b < n_dh) {
-        if (b < dh.nmt * dh.nnt) bwd_gemm_tile<C, true, DH_OUT>(dh, b, sm);
+        if (b < dh.nmt * dh.nnt * dh.ksplit) bwd_gemm_tile<C, true, DH_OUT>(dh, b, sm);
     } else {
         bwd_gemm_tile<C, false, DW_OUT>(dw, b - n_dh, sm);
     }
@@ -1173,6 +1185,30 @@ to_bf16_kernel(const float* __restrict__ src, int64_t ld_src, int64_t rows, int6
     for (int64_t r = blockIdx.x; r < rows; r += gridDim.x)
         for (int64_t c = threadIdx.x; c < cols; c += 256)
             dst[r * ld_dst + c] = bf16_bits(src[r * ld_src + c]);
+}
+
+// The sum of the ksplit parts of dh (each [rows, d] fp32, part_stride elements
+// apart) in part order, for rows [0, rows), with dyn_rows those below
+// *dyn_rows - dyn_base: four columns a work-item.
+template <class O>
+__global__ void __launch_bounds__(256)
+sum_parts_kernel(const float* __restrict__ part, int64_t ksplit, int64_t part_stride, int64_t rows,
+                 int64_t d, O* __restrict__ out, int64_t ld_out,
+                 const int32_t* __restrict__ dyn_rows, int64_t dyn_base) {
+    if (dyn_rows) {
+        const int64_t live = (int64_t)*dyn_rows - dyn_base;
+        rows = live < rows ? live : rows;
+    }
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;  // d % 8 == 0
+    if (i * 4 >= rows * d) return;
+    const f32x4* p = reinterpret_cast<const f32x4*>(part) + i;
+    f32x4 x = p[0];
+#pragma unroll 8
+    for (int64_t k = 1; k < ksplit; ++k) x += p[k * (part_stride / 4)];
+    const int64_t r = i * 4 / d;
+    O* o = out + r * ld_out + (i * 4 - r * d);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) put(o + q, x[q]);
 }
 
 // Workgroups of the row kernels above: one per row up to this many.
@@ -1309,7 +1345,27 @@ struct BackwardPlan {
     bool acc_w;          // dW summed over row blocks into bf16: through fp32
     bool acc_h;          // dh summed over vocabulary blocks into bf16: through fp32
     size_t dz, accw, acch, h_c, dh_c, target_c, lse_c, logp_c, coef_c, map, count, total;
+    // beyond total, used where the caller's workspace reaches split_total: dh's
+    // sum over the vocabulary in ksplit parts (1: no parts, split_total = total)
+    int64_t ksplit;
+    size_t parts, split_total;
 };
+
+// Parts of a block's dh sum. dh has rows / 256 x d / 256 tiles, each a sum over
+// the block's whole vocabulary, and one launch holds them and dW's tiles, the
+// same work in many short sums: while dh's tiles fill less than half of the
+// compute units the launch waits for them (at 1000 rows, d = 3584, V = 152064:
+// 56 tiles of 2376 slices, 3.62 ms; in 2, 4 or 9 parts 2.10, 1.95 or 2.02 ms, adding
+// them up 7, 17 or 37 us more). So that at least half
+// and at most all of the units have a part, none shorter than kMinPartSlices.
+constexpr int64_t kUnits = 256, kMinPartSlices = 32;
+int64_t dh_parts(int64_t rows, int64_t d, int64_t cols) {
+    const int64_t tiles =
+        ((rows + LmCfg::BM - 1) / LmCfg::BM) * ((d + LmCfg::BN - 1) / LmCfg::BN);
+    const int64_t by_units = kUnits / tiles, by_k = cols / (LmCfg::BK * kMinPartSlices);
+    const int64_t n = by_units < by_k ? by_units : by_k;
+    return n > 1 ? n : 1;
+}
 
 // total = 0 when the sizes do not fit the address arithmetic.
 BackwardPlan plan_backward(int64_t T, int64_t d, int64_t V, int64_t chunk_rows,
@@ -1346,6 +1402,9 @@ BackwardPlan plan_backward(int64_t T, int64_t d, int64_t V, int64_t chunk_rows,
         P.count = take(4);
     }
     P.total = end;
+    P.ksplit = dh_parts(P.rows, d, P.cols);
+    if (P.ksplit > 1) P.parts = take((size_t)P.ksplit * (size_t)P.rows * (size_t)d * 4);
+    P.split_total = end;
     return P;
 }
 
@@ -1371,6 +1430,7 @@ BwdGemm make_bwd_gemm(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t
     g.nmt = (M + LmCfg::BM - 1) / LmCfg::BM;
     g.nnt = (N + LmCfg::BN - 1) / LmCfg::BN;
     g.dyn = nullptr, g.dyn_base = 0, g.dyn_m = g.dyn_k = false;
+    g.ksplit = 1, g.kper = K, g.part_stride = 0;
     return g;
 }
 
@@ -1395,13 +1455,15 @@ void launch_bwd_gemms_dw(int dw_mode, const BwdGemm& dh, const BwdGemm& dw, int6
 
 // One block's dh[rows, d] (+)= dz[rows, cols] W[cols, d] and
 // dW[cols, d] (+)= dz[rows, cols]^T h[rows, d], in one launch. A bf16 output
-// is never added to (sums over blocks go through fp32). With dyn_rows, the
-// block's rows are at most *dyn_rows - dyn_base (read on the device).
+// is never added to (sums over blocks go through fp32). With ksplit > 1 dh_out is
+// ksplit fp32 matrices part_stride elements apart, which each get their part of
+// the sum. With dyn_rows, the block's rows are at most *dyn_rows - dyn_base
+// (read on the device).
 dart_status_t launch_bwd_gemms(const uint16_t* dz, int64_t ld_dz, int64_t rows, int64_t cols,
                                const uint16_t* w, int64_t ld_w, const uint16_t* h, int64_t ld_h,
-                               int64_t d, const Grad& dh_out, bool dh_acc, const Grad& dw_out,
-                               bool dw_acc, hipStream_t stream, const int32_t* dyn_rows,
-                               int64_t dyn_base) {
+                               int64_t d, const Grad& dh_out, bool dh_acc, int64_t ksplit,
+                               int64_t part_stride, const Grad& dw_out, bool dw_acc,
+                               hipStream_t stream, const int32_t* dyn_rows, int64_t dyn_base) {
     if ((dh_out.bf16 && dh_acc) || (dw_out.bf16 && dw_acc)) return DART_ERR_INVALID_ARG;
     if (ld_dz > kMaxLd || ld_w > kMaxLd || ld_h > kMaxLd || dh_out.ld > kMaxLd ||
         dw_out.ld > kMaxLd)
@@ -1412,7 +1474,12 @@ dart_status_t launch_bwd_gemms(const uint16_t* dz, int64_t ld_dz, int64_t rows, 
     dh.dyn = dw.dyn = dyn_rows;
     dh.dyn_base = dw.dyn_base = dyn_base;
     dh.dyn_m = dw.dyn_k = dyn_rows != nullptr;
-    const int64_t n_dh = (dh.nmt * dh.nnt + 7) / 8 * 8;
+    if (ksplit > 1) {
+        const int64_t nk = (cols + LmCfg::BK - 1) / LmCfg::BK;
+        dh.ksplit = ksplit, dh.kper = (nk + ksplit - 1) / ksplit * LmCfg::BK;
+        dh.part_stride = part_stride;
+    }
+    const int64_t n_dh = (dh.nmt * dh.nnt * ksplit + 7) / 8 * 8;
     const int64_t blocks = n_dh + dw.nmt * dw.nnt;
     if (!grid_fits(blocks, LmCfg::THREADS)) return DART_ERR_UNSUPPORTED;
     const int dhm = out_mode(dh_out, dh_acc), dwm = out_mode(dw_out, dw_acc);
@@ -1438,18 +1505,21 @@ void launch_to_bf16(const float* src, int64_t rows, int64_t cols, const Grad& ds
 // one block writes is that GEMM's fp32 result rounded once. With dyn_rows, T
 // is the most rows there can be and only the first *dyn_rows are formed (the
 // count is read on the device: blocks past it have nothing to do, and the
-// first row block writes dW even when it holds no rows).
+// first row block writes dW even when it holds no rows). With parts (ksplit > 1),
+// a row block's dh is summed there, [ksplit][R, d], and added up once its last
+// vocabulary block is in.
 dart_status_t backward_core(const uint16_t* h, int64_t T, int64_t d,
                             int64_t ld_h, const uint16_t* w, int64_t V, int64_t ld_w,
                             const int32_t* target, const float* lse, const float* logp,
                             const float* coef, float scale, const Grad& dh, const Grad& dw,
                             int64_t R,
-                            int64_t C, uint16_t* dz, float* acc_h, float* acc_w,
-                            hipStream_t stream, const int32_t* dyn_rows = nullptr) {
+                            int64_t C, uint16_t* dz, float* acc_h, float* acc_w, float* parts,
+                            int64_t ksplit, hipStream_t stream,
+                            const int32_t* dyn_rows = nullptr) {
     if (R > T) R = T;
     if (C > V) C = V;
     const int64_t ld_dz = ceil8(C);
-    const bool via_h = dh.bf16 && C < V, via_w = dw.bf16 && R < T;
+    const bool via_h = dh.bf16 && C < V && !parts, via_w = dw.bf16 && R < T;
     const Grad sum_h = via_h ? Grad{acc_h, d, false} : dh;
     const Grad sum_w = via_w ? Grad{acc_w, d, false} : dw;
     for (int64_t r0 = 0; r0 < T; r0 += R) {
@@ -1464,9 +1534,20 @@ dart_status_t backward_core(const uint16_t* h, int64_t T, int64_t d,
             if (st != DART_OK) return st;
             const dart_status_t sg = launch_bwd_gemms(
                 dz, ld_dz, rows, cols, wc, ld_w, hr, ld_h, d,
-                Grad{sum_h.row(r0), sum_h.ld, sum_h.bf16}, c0 > 0,
-                Grad{sum_w.row(c0), sum_w.ld, sum_w.bf16}, r0 > 0, stream, dyn_rows, r0);
+                parts ? Grad{parts, d, false} : Grad{sum_h.row(r0), sum_h.ld, sum_h.bf16}, c0 > 0,
+                parts ? ksplit : 1, R * d, Grad{sum_w.row(c0), sum_w.ld, sum_w.bf16}, r0 > 0, stream, dyn_rows, r0);
             if (sg != DART_OK) return sg;
+        }
+        if (parts) {
+            const dim3 grid((unsigned)((rows * d / 4 + 255) / 256));
+            if (dh.bf16)
+                hipLaunchKernelGGL(sum_parts_kernel<uint16_t>, grid, dim3(256), 0, stream, parts,
+                                   ksplit, R * d, rows, d, static_cast<uint16_t*>(dh.row(r0)),
+                                   dh.ld, dyn_rows, r0);
+            else
+                hipLaunchKernelGGL(sum_parts_kernel<float>, grid, dim3(256), 0, stream, parts,
+                                   ksplit, R * d, rows, d, static_cast<float*>(dh.row(r0)), dh.ld,
+                                   dyn_rows, r0);
         }
     }
     if (via_h) launch_to_bf16(acc_h, T, d, dh, stream);
@@ -1492,6 +1573,14 @@ size_t dart_lmhead_backward_ex_workspace_bytes(int64_t T, int64_t d, int64_t V,
         d > 0x7FFFFFFFll || V > 0x7FFFFFFFll || (flags & ~kBackwardFlags))
         return 0;
     return plan_backward(T, d, V, chunk_rows, chunk_cols, flags).total;
+}
+
+size_t dart_lmhead_backward_split_workspace_bytes(int64_t T, int64_t d, int64_t V,
+                                                  int64_t chunk_rows, int64_t chunk_cols,
+                                                  uint32_t flags) {
+    if (dart_lmhead_backward_ex_workspace_bytes(T, d, V, chunk_rows, chunk_cols, flags) == 0)
+        return 0;
+    return plan_backward(T, d, V, chunk_rows, chunk_cols, flags).split_total;
 }
 
 dart_status_t dart_lmhead_backward_ex(const void* hidden, int64_t T, int64_t d, int64_t ld_h,
@@ -1525,10 +1614,12 @@ dart_status_t dart_lmhead_backward_ex(const void* hidden, int64_t T, int64_t d, 
     uint16_t* dz = reinterpret_cast<uint16_t*>(ws + P.dz);
     float* acc_w = P.acc_w ? reinterpret_cast<float*>(ws + P.accw) : nullptr;
     float* acc_h = P.acc_h ? reinterpret_cast<float*>(ws + P.acch) : nullptr;
+    const bool split = P.ksplit > 1 && workspace_bytes >= P.split_total;
+    float* parts = split ? reinterpret_cast<float*>(ws + P.parts) : nullptr;
     const Grad dh{dhidden, ld_dh, P.bf16}, dw{dweight, ld_dw, P.bf16};
     if (!P.skip)
-        return backward_core(h, T, d, ld_h, w, V, ld_w, target, lse, logp, tok_coef,
-                             inv_temp, dh, dw, P.rows, P.cols, dz, acc_h, acc_w, stream);
+        return backward_core(h, T, d, ld_h, w, V, ld_w, target, lse, logp, tok_coef, inv_temp, dh,
+                             dw, P.rows, P.cols, dz, acc_h, acc_w, parts, P.ksplit, stream);
 
     // rows with a zero coefficient have dz = 0: they add nothing to dW and
     // their rows of dh are 0, so the GEMMs run over the other rows only
@@ -1553,7 +1644,8 @@ dart_status_t dart_lmhead_backward_ex(const void* hidden, int64_t T, int64_t d, 
     // the kernels read the kept-row count on the device: T rows at most
     const dart_status_t st =
         backward_core(h_c, T, d, d, w, V, ld_w, target_c, lse_c, logp_c, coef_c, inv_temp,
-                      Grad{dh_c, d, false}, dw, P.rows, P.cols, dz, nullptr, acc_w, stream, count);
+                      Grad{dh_c, d, false}, dw, P.rows, P.cols, dz, nullptr, acc_w, parts,
+                      P.ksplit, stream, count);
     if (st != DART_OK) return st;
     const unsigned nb = (unsigned)(T < kRowBlocks ? T : kRowBlocks);
     if (P.bf16)

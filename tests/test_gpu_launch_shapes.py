@@ -132,3 +132,57 @@ def test_gradient_rows_aligned_unlike_the_logits(dtype, V, pad):
                 assert torch.equal(out, want), (a, b, skip)
                 out.fill_(7.0)
                 assert bool((buf == 7.0).all()), (a, b, skip)
+
+
+SKIP, BF16 = 1, 4
+
+
+@pytest.mark.parametrize("flags", [0, BF16, SKIP, SKIP | BF16])
+@pytest.mark.parametrize("T,d,V,rows,cols,parts", [
+    (40, 72, 4095, 40, 4095, 1),     # one column short of two parts
+    (40, 72, 4096, 40, 4096, 2),
+    (300, 136, 9001, 300, 9001, 4),  # the last part ends inside a slice
+    (300, 136, 9001, 300, 8300, 4),  # the second block has fewer slices than parts
+    (300, 136, 9001, 100, 9001, 4),  # several row blocks on one set of parts
+])
+def test_lmhead_backward_dh_in_parts(T, d, V, rows, cols, parts, flags):
+    """dhidden summed in parts: against the oracle and the exact product of the
+    GPU's own bf16 dlogits, within the bounds of the one-run sum (which a smaller
+    workspace takes); bf16 gradients are the fp32 ones rounded; garbage in the
+    workspace does not matter."""
+    import torch
+
+    import paper_2509_23866_amd as dart
+    from tests import test_gpu_lmhead_grad as G
+
+    h, w, y, g = G._problem(T, d, V)
+    rlogp, _, rlse = oracle.lmhead_token_stats(h, w, y)
+    dz64, dh64, dw64 = oracle.lmhead_grads(h, w, y, rlse, rlogp, g)
+    h64, w64 = oracle.bf16_bits_to_f64(h), oracle.bf16_bits_to_f64(w)
+    hd, wd, yd, gd = G._dev_bf16(h), G._dev_bf16(w), _cuda(y), _cuda(g)
+    logp, _, lse = dart.dart_lmhead_tok_stats(hd, wd, yd)
+    dzo = G._own_dz(hd, wd, yd, lse, logp, gd)
+    need = dart.dart_lmhead_backward_ex_workspace_bytes(T, d, V, rows, cols, flags)
+    full = dart.dart_lmhead_backward_split_workspace_bytes(T, d, V, rows, cols, flags)
+    up = -(-need // 256) * 256
+    assert full == (need if parts == 1 else up + parts * min(rows, T) * d * 4)
+
+    def run(nbytes, f):
+        ws = torch.full((nbytes,), 0x7F, dtype=torch.uint8, device="cuda")
+        return dart.dart_lmhead_backward_ex(hd, wd, yd, lse, logp, gd, chunk_rows=rows,
+                                            chunk_cols=cols, flags=f, workspace=ws)
+
+    bf = bool(flags & BF16)
+    for nbytes in (full, full - 1) if parts > 1 else (full,):
+        dh, dw = run(nbytes, flags)
+        G._check_grad(dh, dh64, dzo @ w64, np.abs(dz64) @ np.abs(w64), "dhidden", bf16=bf)
+        G._check_grad(dw, dw64, dzo.T @ h64, np.abs(dz64).T @ np.abs(h64), "dweight", bf16=bf)
+        if flags & SKIP:
+            assert bool((dh[torch.from_numpy(g == 0.0).cuda()] == 0).all())
+    auto = dart.dart_lmhead_backward_ex(hd, wd, yd, lse, logp, gd, chunk_rows=rows,
+                                        chunk_cols=cols, flags=flags)
+    a, b = run(full, flags)
+    assert torch.equal(auto[0], a) and torch.equal(auto[1], b)
+    if bf:
+        wide = dart.dart_lmhead_backward_split_workspace_bytes(T, d, V, rows, cols, flags & SKIP)
+        assert torch.equal(a, run(wide, flags & SKIP)[0].to(torch.bfloat16))
