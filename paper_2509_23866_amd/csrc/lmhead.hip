@@ -44,6 +44,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 // Waits until at most N loads of this wave are outstanding (vmcnt), leaving
 // the LDS and export counters alone.
@@ -103,12 +104,11 @@ struct Cfg {
     // epilogue pass over EPI = RS rows takes one block from every wave
     static constexpr int RS = BM / TM;
     static constexpr int IA = BM / LROWS / WAVES, IB = BN / LROWS / WAVES;  // loads per slice
-    // LDS row of the fp32 result tile: BN + 16 floats, so that consecutive
-    // rows start one bank quad apart: the 16 lanes of one 16-byte read cycle
-    // (4 rows x 4 adjacent 16-byte pieces) fall in 16 distinct quads
-    static constexpr int CROW = BN + 16;
-    // the epilogue stages EPI rows of the fp32 tile at a time through LDS:
-    // one 32-row block of every wave
+    // LDS rows of a result tile: 16 bytes beyond BN elements, so that
+    // consecutive rows start one bank quad apart and the rows that the lanes of
+    // one write cycle hold fall in distinct banks. A bf16 tile goes through LDS
+    // whole, an fp32 one EPI rows at a time: one 32-row block of every wave
+    static constexpr int CROW = BN + 4, CROW16 = BN + 8;
     static constexpr int EPI = RS;
     static_assert(BK == 32 || BK == 64, "slice depth");
     static_assert(BM % (32 * WM) == 0 && BN % (32 * WN) == 0, "tile shape");
@@ -121,10 +121,9 @@ struct Cfg {
                 uint16_t a[NS][BM][BK];
                 uint16_t b[NS][BN][BK];
             } in;
-            struct {
-                float c[EPI][CROW];
-                float4 rowp[EPI];  // per-row constants of the gradient epilogue
-            };
+            float c[EPI][CROW];
+            uint16_t c16[BM][CROW16];
+            float4 red[WN][BM];  // per-row partial triples of the statistics
         };
     };
 };
@@ -172,8 +171,15 @@ __device__ __forceinline__ Triple merge(const Triple& a, const Triple& b) {
 // and B [N, K] row-major bf16, rows 16-byte aligned, K % 8 == 0). Rows past M
 // or N read as zero (their results are not used); K past the end is zeroed in
 // LDS. Layout of acc[i][j]: value v of lane l is
-// tile row (wave / WN) * 32 + i * RS + (v/4)*8 + (l/32)*4 + v%4, column
-// (wave % WN) * BN/WN + j*32 + l%32. Ends on a barrier with no loads in
+// tile row (wave / WN) * 32 + i * RS + l%32, column
+// (wave % WN) * BN/WN + j*32 + (v/4)*8 + (l/32)*4 + v%4: the MFMA takes B's rows
+// as its first operand, so that a lane holds 16 TN columns of one row, four
+// adjacent ones in consecutive registers. (With A's rows first a lane holds
+// one column of 16 rows, and every epilogue had to turn the fp32 tile round in
+// LDS, one value at a time. Measured at d = 3584, V = 152064, the same box:
+// statistics 3450 -> 3378 us at T = 4096 and 950 -> 925 at 1000, the backward
+// with bf16 gradients 10702 -> 10565 and 2953 -> 2856, dlogits 928 -> 917 at
+// 1000, the fp32 gradients within 0.3%.) Ends on a barrier with no loads in
 // flight, so the caller may reuse the LDS.
 template <class C>
 __device__ __forceinline__ void gemm_tile(const uint16_t* __restrict__ A, int64_t M, int64_t lda,
@@ -305,7 +311,7 @@ __device__ __forceinline__ void gemm_tile(const uint16_t* __restrict__ A, int64_
 #pragma unroll
             for (int j = 0; j < C::TN; ++j)
                 if (i >= i0 && i < i1)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[set][i], bfr[set][j],
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[set][j], af[set][i],
                                                                         acc[i][j], 0, 0, 0);
     };
     // Every wave holds back the last k-step's MFMAs of its last row block
@@ -363,6 +369,27 @@ __device__ __forceinline__ void gemm_tile(const uint16_t* __restrict__ A, int64_
 #endif
 }
 
+// The workgroup's result tile in LDS, rounded to bf16: four adjacent columns
+// of a row leave a lane as one 8-byte write.
+template <class C>
+__device__ __forceinline__ void tile_to_lds_bf16(const f32x16 (&acc)[C::TM][C::TN],
+                                                 typename C::Smem& sm) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wr = (wave / C::WN) * 32 + (lane & 31), wc = (wave % C::WN) * (C::BN / C::WN);
+#pragma unroll
+    for (int i = 0; i < C::TM; ++i)
+#pragma unroll
+        for (int j = 0; j < C::TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; v += 4) {
+                u32x2 pk;
+                pk.x = pack_bf16x2(acc[i][j][v], acc[i][j][v + 1]);
+                pk.y = pack_bf16x2(acc[i][j][v + 2], acc[i][j][v + 3]);
+                *reinterpret_cast<u32x2*>(
+                    &sm.c16[wr + i * C::RS][wc + j * 32 + (v >> 2) * 8 + (lane >> 5) * 4]) = pk;
+            }
+}
+
 // Logical tile of workgroup b: the hardware places workgroup b on XCD b % 8,
 // so each XCD gets a contiguous run of logical tiles. Logical tiles come in
 // groups of G token tiles x every vocabulary tile, token tile fastest within
@@ -397,115 +424,98 @@ lmhead_stats_kernel(const uint16_t* __restrict__ h, int64_t T, int64_t ldh,
     f32x16 acc[C::TM][C::TN];
     gemm_tile<C>(h, T, ldh, w, V, ldw, d, m0, n0, sm, acc);
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = (wave / C::WN) * 32, wc = (wave % C::WN) * (C::BN / C::WN);
-    static_assert(C::EPI == C::RS, "one row block of every wave per pass");
+    // A lane's columns of one row: their maximum, then the sums in base-2 units
+    // against it, one partial sum per 32-column block; merged with the lane
+    // that holds the row's other columns of the wave, then across the WN waves
+    // of the row through LDS. The whole epilogue stays in registers until there.
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5;
+    const int wr = (wave / C::WN) * 32 + (lane & 31), wc = (wave % C::WN) * (C::BN / C::WN);
+    // columns below vlim (counted from the wave's first) exist
+    const int vlim = (int)min(V - n0 - wc, (int64_t)C::BN);
+    // the inverse temperature enters the base-2 exponent's factor (1 at scale
+    // 1: the same bits)
+    const float c2 = scale * 1.4426950408889634f;
 #pragma unroll
-    for (int ip = 0; ip < C::TM; ++ip) {
-        const int e0 = ip * C::EPI;
-        // LDS-only barriers: the workgroup exchanges nothing but LDS here, and a
-        // __syncthreads fence would also wait for the previous pass's stores
-        if (ip) lds_ring_barrier();
-        // rows [e0, e0 + EPI) of the tile to LDS: row block ip of every wave
+    for (int i = 0; i < C::TM; ++i) {
+        const int64_t t = m0 + wr + i * C::RS;
+        const int64_t yrel = (t < T ? (int64_t)target[t] : -1) - n0 - wc;
+        // the target's column within the wave's (-1: not here)
+        const int y32 = yrel >= 0 && yrel < min(vlim, C::BN / C::WN) ? (int)yrel : -1;
+        // only the tile's last columns past V and a row's target column drop
+        // out: the selects run only in lanes that hold such a column
+        const bool masked = vlim < C::BN / C::WN || (y32 >= 0 && ((y32 >> 2) & 1) == half);
+        if (masked) {
+            float zy = 0.f;
+            // opaque, so that the compiler does not take the comparisons of
+            // every row block's columns together, and spill their masks
+            int vl = vlim - half * 4, yl = y32 - half * 4;
+            asm volatile("" : "+v"(vl), "+v"(yl));
+#pragma unroll
+            for (int j = 0; j < C::TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int col = j * 32 + (v >> 2) * 8 + (v & 3);
+                    const bool at_y = col == yl;
+                    zy = at_y ? acc[i][j][v] : zy;
+                    acc[i][j][v] = col >= vl || at_y ? -INFINITY : acc[i][j][v];
+                }
+            if (y32 >= 0 && ((y32 >> 2) & 1) == half) z_y[t] = zy * scale;
+        }
+        float mx = -INFINITY;
 #pragma unroll
         for (int j = 0; j < C::TN; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
-                sm.c[wr + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3)][wc + j * 32 + (lane & 31)] =
-                    acc[ip][j][v];
-        lds_ring_barrier();
-        // P threads per row; thread p takes the 16-byte pieces p, p + P, ...
-        // of the row (columns 16 c + 4 p + u) into registers: maximum over the
-        // row's columns other than the target, then the sums in base-2 units
-        // against it; the P partial triples merged in lane order
-        constexpr int P = C::THREADS / C::EPI, NX = C::BN / P;
-        static_assert(C::THREADS == C::EPI * P && P == 4, "four threads per epilogue row");
-        const int r = tid / P, p = tid % P;
-        const int64_t t = m0 + e0 + r;
-        const int64_t yrel = (t < T ? (int64_t)target[t] : -1) - n0;
-        // columns below vlim exist; the target sits at column y32 (-1: not here)
-        const int vlim = (int)min(V - n0, (int64_t)C::BN);
-        const int y32 = yrel >= 0 && yrel < vlim ? (int)yrel : -1;
-        // the thread's 64 columns in two halves of 32 registers, each folded
-        // into a triple (maximum, then the sums in base-2 units against it)
-        // and merged; columns past V and the target's column drop out as -inf
-        constexpr int NH = NX / 2;
-        // only the tile's last columns past V and a row's target column drop
-        // out: the selects run only in threads that hold such a column
-        const bool masked = vlim < C::BN || (y32 >= 0 && ((y32 >> 2) & (P - 1)) == p);
-        // the tile stays unscaled in LDS: the inverse temperature enters the
-        // base-2 exponent's factor (1 at scale 1: the same bits)
-        const float c2 = scale * 1.4426950408889634f;
-        Triple mine = {-INFINITY, 0.f, 0.f};
+            for (int v = 0; v < 16; ++v) mx = fmaxf(mx, acc[i][j][v]);
+        // scale > 0: the maximum of the scaled row is the scaled maximum
+        Triple mine = {mx * scale, 0.f, 0.f};
+        if (mx > -INFINITY) {
+            // e = 2^xl with xl = (x - mx) scale log2(e); where a column was
+            // dropped (-inf) xl is floored at -200, where 2^xl is already 0 in
+            // fp32, so that it adds 0 (other columns are finite)
+            const float ml = mx * c2;
+            float s2[C::TN], w2[C::TN];
+            auto sums = [&](auto floored) {
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-            // the half's eight 16-byte reads, issued together; the empty asm
-            // keeps the compiler from turning the selects below into
-            // per-element predicated reads
-            static_assert(NH / 4 == 8, "eight vectors per half row");
-            f32x4 q[8];
+                for (int j = 0; j < C::TN; ++j) {
+                    s2[j] = w2[j] = 0.f;
 #pragma unroll
-            for (int c4 = 0; c4 < 8; ++c4)
-                q[c4] = *reinterpret_cast<const f32x4*>(&sm.c[r][16 * (hh * 8 + c4) + 4 * p]);
-            asm volatile("" : "+v"(q[0]), "+v"(q[1]), "+v"(q[2]), "+v"(q[3]), "+v"(q[4]),
-                         "+v"(q[5]), "+v"(q[6]), "+v"(q[7]));
-            float x[NH];
-#pragma unroll
-            for (int c4 = 0; c4 < 8; ++c4)
-#pragma unroll
-                for (int u = 0; u < 4; ++u) x[4 * c4 + u] = q[c4][u];
-            if (masked) {
-#pragma unroll
-                for (int c4 = 0; c4 < 8; ++c4)
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int col = 16 * (hh * 8 + c4) + 4 * p + u;
-                        x[4 * c4 + u] = col < vlim && col != y32 ? x[4 * c4 + u] : -INFINITY;
-                    }
-            }
-            float mx = -INFINITY;
-#pragma unroll
-            for (int i = 0; i < NH; ++i) mx = fmaxf(mx, x[i]);
-            // scale > 0: the maximum of the scaled row is the scaled maximum
-            Triple part_h = {mx * scale, 0.f, 0.f};
-            if (mx > -INFINITY) {
-                // e = 2^xl with xl = (x - mx) scale log2(e); where a column was
-                // dropped (-inf) xl is floored at -200, where 2^xl is already 0
-                // in fp32, so that it adds 0 (other columns are finite)
-                const float ml = mx * c2;
-                float s2 = 0.f, w2 = 0.f;
-                if (masked) {
-#pragma unroll
-                    for (int i = 0; i < NH; ++i) {
-                        const float xl = fmaxf(fmaf(x[i], c2, -ml), -200.f);
+                    for (int v = 0; v < 16; ++v) {
+                        float xl = fmaf(acc[i][j][v], c2, -ml);
+                        if constexpr (decltype(floored)::value) xl = fmaxf(xl, -200.f);
                         const float e = __builtin_amdgcn_exp2f(xl);
-                        s2 += e;
-                        w2 = fmaf(e, xl, w2);
-                    }
-                } else {
-#pragma unroll
-                    for (int i = 0; i < NH; ++i) {
-                        const float xl = fmaf(x[i], c2, -ml);
-                        const float e = __builtin_amdgcn_exp2f(xl);
-                        s2 += e;
-                        w2 = fmaf(e, xl, w2);
+                        s2[j] += e;
+                        w2[j] = fmaf(e, xl, w2[j]);
                     }
                 }
-                part_h.s = s2;
-                part_h.w = w2 * 0.6931471805599453f;
-            }
-            mine = merge(mine, part_h);
-        }
+            };
+            if (masked)
+                sums(std::true_type{});
+            else
+                sums(std::false_type{});
 #pragma unroll
-        for (int off = 1; off < P; off <<= 1) {
-            Triple o;
-            o.m = __shfl_xor(mine.m, off);
-            o.s = __shfl_xor(mine.s, off);
-            o.w = __shfl_xor(mine.w, off);
-            mine = (p & off) ? merge(o, mine) : merge(mine, o);
+            for (int j = 0; j < C::TN; ++j) {
+                mine.s += s2[j];
+                mine.w += w2[j];
+            }
+            mine.w *= 0.6931471805599453f;
         }
-        if (t < T && p == 0) part[t * nvt + vt] = make_float4(mine.m, mine.s, mine.w, 0.f);
-        if (t < T && y32 >= 0 && ((y32 >> 2) & (P - 1)) == p) z_y[t] = sm.c[r][y32] * scale;
+        Triple o;
+        o.m = __shfl_xor(mine.m, 32);
+        o.s = __shfl_xor(mine.s, 32);
+        o.w = __shfl_xor(mine.w, 32);
+        mine = half ? merge(o, mine) : merge(mine, o);
+        if (half == 0) sm.red[wave % C::WN][wr + i * C::RS] = make_float4(mine.m, mine.s, mine.w, 0.f);
+    }
+    lds_ring_barrier();
+    for (int r = tid; r < C::BM && m0 + r < T; r += C::THREADS) {
+        Triple x = {-INFINITY, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < C::WN; ++k) {
+            const float4 q = sm.red[k][r];
+            x = merge(x, Triple{q.x, q.y, q.z});
+        }
+        part[(m0 + r) * nvt + vt] = make_float4(x.m, x.s, x.w, 0.f);
     }
 }
 
@@ -515,8 +525,7 @@ lmhead_stats_kernel(const uint16_t* __restrict__ h, int64_t T, int64_t ldh,
 // entries vbase .. vbase + V - 1 (w already offset to entry vbase), written in
 // bf16 (nearest even) to out [M, ld_out]: the gradient pass of the logits
 // path with the logits formed on the fly. The target element is
-// s g_t * -expm1(logp_t), accurate when p_y -> 1. The fp32 tile is staged
-// through LDS so that each row leaves as 16-byte vectors.
+// s g_t * -expm1(logp_t), accurate when p_y -> 1.
 template <class C>
 __global__ void __launch_bounds__(C::THREADS)
 lmhead_dlogits_kernel(const uint16_t* __restrict__ h, int64_t M, int64_t ldh,
@@ -543,94 +552,54 @@ lmhead_dlogits_kernel(const uint16_t* __restrict__ h, int64_t M, int64_t ldh,
     f32x16 acc[C::TM][C::TN];
     gemm_tile<C>(h, M, ldh, w, V, ldw, d, m0, n0, sm, acc);
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = (wave / C::WN) * 32, wc = (wave % C::WN) * (C::BN / C::WN);
-    constexpr int CHUNKS = C::BN / 8;  // 16-byte output chunks per tile row
-    static_assert(C::EPI == C::RS, "one row block of every wave per pass");
-    // the tile stays unscaled in LDS: the inverse temperature enters the
-    // base-2 exponent's factor (1 at scale 1: the same bits)
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5;
+    const int wr = (wave / C::WN) * 32 + (lane & 31), wc = (wave % C::WN) * (C::BN / C::WN);
+    // the inverse temperature enters the base-2 exponent's factor (1 at scale
+    // 1: the same bits)
     const float c2 = scale * 1.4426950408889634f;
+    // the lane's rows turned into bf16 in registers, then the bf16 tile through
+    // LDS so that each row leaves as 16-byte vectors
 #pragma unroll
-    for (int ip = 0; ip < C::TM; ++ip) {
-        const int e0 = ip * C::EPI;
-        // LDS-only barriers: a __syncthreads fence here would also wait for
-        // the previous pass's gradient stores
-        if (ip) lds_ring_barrier();
+    for (int i = 0; i < C::TM; ++i) {
+        // the row's constants: -g, -lse log2(e), the target's gradient
+        // g (-expm1(logp)) (accurate when p_y -> 1), the target's column here;
+        // g carries the inverse temperature (the chain rule through scale z)
+        const int64_t t = m0 + wr + i * C::RS;
+        const int64_t tc = t < M ? t : M - 1;  // rows past M are not stored
+        const float g = coef[tc] * scale;
+        const float neg_g = -g, neg_lse = -lse[tc] * 1.4426950408889634f;
+        const int64_t yrel = (int64_t)target[tc] - vbase - n0 - wc;
+        const int y32 = yrel >= 0 && yrel < C::BN / C::WN ? (int)yrel : -1;
 #pragma unroll
         for (int j = 0; j < C::TN; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v)
-                sm.c[wr + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3)][wc + j * 32 + (lane & 31)] =
-                    acc[ip][j][v];
-        // per-row constants: -g, -lse log2(e), the target's gradient
-        // g (-expm1(logp)) (accurate when p_y -> 1), the target's column here;
-        // g carries the inverse temperature (the chain rule through scale z)
-        if (tid < C::EPI) {
-            const int64_t t = m0 + e0 + tid;
-            float4 rp = make_float4(0.f, 0.f, 0.f, __int_as_float(-1));
-            if (t < M) {
-                const float g = coef[t] * scale;
-                const int64_t yrel = (int64_t)target[t] - vbase - n0;
-                rp = make_float4(-g, -lse[t] * 1.4426950408889634f, g * -expm1f(logp[t]),
-                                 __int_as_float(yrel >= 0 && yrel < C::BN ? (int)yrel : -1));
-            }
-            sm.rowp[tid] = rp;
-        }
-        lds_ring_barrier();
-        for (int e = tid; e < C::EPI * CHUNKS; e += C::THREADS) {
-            const int r = e / CHUNKS, ch = e % CHUNKS;
-            const int64_t t = m0 + e0 + r;
-            const int64_t col0 = n0 + ch * 8;
-            if (t >= M || col0 >= V) continue;
-            const float4 rp = sm.rowp[r];
-            const int yc = __float_as_int(rp.w) - ch * 8;  // the target's index in this chunk
-            // the chunk's two 16-byte halves, read in an order that alternates
-            // every 8 chunks so that the 16 lanes of one LDS read cycle hit 16
-            // distinct bank quads
-            const int sw = (ch >> 3) & 1;
-            const float4 a = *reinterpret_cast<const float4*>(&sm.c[r][ch * 8 + 4 * sw]);
-            const float4 b = *reinterpret_cast<const float4*>(&sm.c[r][ch * 8 + 4 - 4 * sw]);
-            uint16_t* dst = out + t * ld_out + col0;
-            if ((unsigned)yc >= 8u && col0 + 8 <= V) {
-                // no target here (all but one chunk of a row): every element
-                // takes the same formula, each half is rounded in the order
-                // it was read, and only the four packed words follow the swap
-                const float xa[4] = {a.x, a.y, a.z, a.w}, xb[4] = {b.x, b.y, b.z, b.w};
-                float da[4], db[4];
+                acc[i][j][v] = neg_g * __builtin_amdgcn_exp2f(fmaf(acc[i][j][v], c2, neg_lse));
+        if (y32 >= 0 && ((y32 >> 2) & 1) == half) {
+            const float dy = g * -expm1f(logp[tc]);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    da[q] = rp.x * __builtin_amdgcn_exp2f(fmaf(xa[q], c2, rp.y));
-                    db[q] = rp.x * __builtin_amdgcn_exp2f(fmaf(xb[q], c2, rp.y));
+            for (int j = 0; j < C::TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int col = j * 32 + (v >> 2) * 8 + (v & 3);
+                    acc[i][j][v] = col == y32 - half * 4 ? dy : acc[i][j][v];
                 }
-                const uint32_t a01 = pack_bf16x2(da[0], da[1]), a23 = pack_bf16x2(da[2], da[3]);
-                const uint32_t b01 = pack_bf16x2(db[0], db[1]), b23 = pack_bf16x2(db[2], db[3]);
-                u32x4 pk;
-                pk.x = sw ? b01 : a01;
-                pk.y = sw ? b23 : a23;
-                pk.z = sw ? a01 : b01;
-                pk.w = sw ? a23 : b23;
-                __builtin_nontemporal_store(pk, reinterpret_cast<u32x4*>(dst));
-                continue;
-            }
-            const float4 lo = sw ? b : a, hi = sw ? a : b;
-            const float xs[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-            float dz[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const float e2 = __builtin_amdgcn_exp2f(fmaf(xs[q], c2, rp.y));
-                dz[q] = q == yc ? rp.z : rp.x * e2;
-            }
-            if (col0 + 8 <= V) {
-                u32x4 pk;
-                pk.x = pack_bf16x2(dz[0], dz[1]);
-                pk.y = pack_bf16x2(dz[2], dz[3]);
-                pk.z = pack_bf16x2(dz[4], dz[5]);
-                pk.w = pack_bf16x2(dz[6], dz[7]);
-                __builtin_nontemporal_store(pk, reinterpret_cast<u32x4*>(dst));
-            } else {
-                for (int q = 0; q < 8 && col0 + q < V; ++q) dst[q] = bf16_bits(dz[q]);
-            }
         }
+    }
+    tile_to_lds_bf16<C>(acc, sm);
+    lds_ring_barrier();
+    constexpr int CHUNKS = C::BN / 8;  // 16-byte output chunks per tile row
+    for (int e = tid; e < C::BM * CHUNKS; e += C::THREADS) {
+        const int r = e / CHUNKS, ch = e % CHUNKS;
+        const int64_t t = m0 + r, col0 = n0 + ch * 8;
+        if (t >= M || col0 >= V) continue;
+        const u32x4 pk = *reinterpret_cast<const u32x4*>(&sm.c16[r][ch * 8]);
+        uint16_t* dst = out + t * ld_out + col0;
+        if (col0 + 8 <= V)
+            __builtin_nontemporal_store(pk, reinterpret_cast<u32x4*>(dst));
+        else
+            for (int q = 0; q < 8 && col0 + q < V; ++q) dst[q] = sm.c16[r][ch * 8 + q];
     }
 }
 
@@ -904,7 +873,7 @@ __device__ __forceinline__ void gemm_tile_bwd(const uint16_t* __restrict__ A, in
         for (int i = 0; i < C::TM; ++i)
 #pragma unroll
             for (int j = 0; j < C::TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[set][i], bfr[set][j],
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[set][j], af[set][i],
                                                                     acc[i][j], 0, 0, 0);
     };
     auto slice = [&](auto bufc, int64_t kt) {
@@ -989,9 +958,9 @@ __device__ __forceinline__ void tile_of_block_nfast(int64_t b, int64_t nmt, int6
     mt = lg / nnt;
 }
 
-// Tile b of GEMM g: the MFMA tile, then the fp32 result through LDS, 128 rows
-// at a time, so that each row leaves as 16-byte vectors (vec), else one
-// element at a time.
+// Tile b of GEMM g: the MFMA tile, then the result through LDS (bf16 whole,
+// fp32 128 rows at a time), so that each row leaves as 16-byte vectors (vec),
+// else one element at a time.
 template <class C, bool A_KMAJ, int OUT>
 __device__ __forceinline__ void bwd_gemm_tile(const BwdGemm& g, int64_t b, typename C::Smem& sm) {
     using OutT = typename std::conditional<OUT == kOutBf16, uint16_t, float>::type;
@@ -1027,54 +996,53 @@ __device__ __forceinline__ void bwd_gemm_tile(const BwdGemm& g, int64_t b, typen
     gemm_tile_bwd<C, A_KMAJ>(g.A, g.lda, g.B, g.ldb, M, N, kbeg, K, m0, n0, sm, acc);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = (wave / C::WN) * 32, wc = (wave % C::WN) * (C::BN / C::WN);
-    constexpr bool F32 = OUT != kOutBf16;
-    constexpr int EPV = F32 ? 4 : 8;  // elements per 16-byte vector
-    constexpr int VPR = C::BN / EPV;  // vectors per tile row
-    static_assert(C::EPI == C::RS, "one row block of every wave per pass");
-#pragma unroll
-    for (int ip = 0; ip < C::TM; ++ip) {
-        const int e0 = ip * C::EPI;
-        // LDS-only barriers: a __syncthreads fence here would also wait for
-        // the previous pass's stores
-        if (ip) lds_ring_barrier();
-#pragma unroll
-        for (int j = 0; j < C::TN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v)
-                sm.c[wr + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3)][wc + j * 32 + (lane & 31)] =
-                    acc[ip][j][v];
+    const int wr = (wave / C::WN) * 32 + (lane & 31), wc = (wave % C::WN) * (C::BN / C::WN);
+    if constexpr (OUT == kOutBf16) {
+        constexpr int VPR = C::BN / 8;  // 16-byte vectors per tile row
+        tile_to_lds_bf16<C>(acc, sm);
         lds_ring_barrier();
-        for (int e = tid; e < C::EPI * VPR; e += C::THREADS) {
+        for (int e = tid; e < C::BM * VPR; e += C::THREADS) {
             const int r = e / VPR, cv = e % VPR;
-            const int64_t m = m0 + e0 + r, n = n0 + (int64_t)cv * EPV;
+            const int64_t m = m0 + r, n = n0 + (int64_t)cv * 8;
             if (m >= M || n >= N) continue;
-            const float* src = &sm.c[r][cv * EPV];
-            OutT* dst = out + m * g.ldc + n;
-            if (g.vec && n + EPV <= N) {
-                if constexpr (F32) {
-                    float4 x = *reinterpret_cast<const float4*>(src);
-                    if constexpr (ACC) {
-                        const float4 o = *reinterpret_cast<const float4*>(dst);
-                        x.x += o.x, x.y += o.y, x.z += o.z, x.w += o.w;
-                    }
-                    *reinterpret_cast<float4*>(dst) = x;
-                } else {
-                    const float4 lo = *reinterpret_cast<const float4*>(src);
-                    const float4 hi = *reinterpret_cast<const float4*>(src + 4);
-                    u32x4 pk;
-                    pk.x = pack_bf16x2(lo.x, lo.y);
-                    pk.y = pack_bf16x2(lo.z, lo.w);
-                    pk.z = pack_bf16x2(hi.x, hi.y);
-                    pk.w = pack_bf16x2(hi.z, hi.w);
-                    *reinterpret_cast<u32x4*>(dst) = pk;
+            uint16_t* dst = out + m * g.ldc + n;
+            if (g.vec && n + 8 <= N)
+                *reinterpret_cast<u32x4*>(dst) = *reinterpret_cast<const u32x4*>(&sm.c16[r][cv * 8]);
+            else
+                for (int q = 0; q < 8 && n + q < N; ++q) dst[q] = sm.c16[r][cv * 8 + q];
+        }
+        return;
+    } else {
+        constexpr int VPR = C::BN / 4;
+        static_assert(C::EPI == C::RS, "one row block of every wave per pass");
+#pragma unroll
+        for (int i = 0; i < C::TM; ++i) {
+            const int e0 = i * C::EPI;
+            // LDS-only barriers: a __syncthreads fence here would also wait for
+            // the previous pass's stores
+            if (i) lds_ring_barrier();
+#pragma unroll
+            for (int j = 0; j < C::TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; v += 4) {
+                    const f32x4 x = {acc[i][j][v], acc[i][j][v + 1], acc[i][j][v + 2],
+                                     acc[i][j][v + 3]};
+                    *reinterpret_cast<f32x4*>(
+                        &sm.c[wr][wc + j * 32 + (v >> 2) * 8 + (lane >> 5) * 4]) = x;
                 }
-            } else {
-                for (int q = 0; q < EPV && n + q < N; ++q) {
-                    if constexpr (F32)
-                        dst[q] = ACC ? dst[q] + src[q] : src[q];
-                    else
-                        dst[q] = bf16_bits(src[q]);
+            lds_ring_barrier();
+            for (int e = tid; e < C::EPI * VPR; e += C::THREADS) {
+                const int r = e / VPR, cv = e % VPR;
+                const int64_t m = m0 + e0 + r, n = n0 + (int64_t)cv * 4;
+                if (m >= M || n >= N) continue;
+                const float* src = &sm.c[r][cv * 4];
+                OutT* dst = out + m * g.ldc + n;
+                if (g.vec && n + 4 <= N) {
+                    f32x4 x = *reinterpret_cast<const f32x4*>(src);
+                    if constexpr (ACC) x += *reinterpret_cast<const f32x4*>(dst);
+                    *reinterpret_cast<f32x4*>(dst) = x;
+                } else {
+                    for (int q = 0; q < 4 && n + q < N; ++q) dst[q] = ACC ? dst[q] + src[q] : src[q];
                 }
             }
         }
