@@ -11,7 +11,8 @@
 // stays unscaled, and s enters the factor of the base-2 exponent (s log2 e)
 // and the row maximum (s > 0), so that s = 1 changes no bit.
 //
-//   lmhead_stats_kernel   one 256 x 256 tile of z per workgroup on MFMA
+//   lmhead_stats_kernel   one 256 x 256 tile of z per workgroup (64 or 128 rows
+//                         where T is small) on MFMA
 //                         (v_mfma_f32_32x32x16_bf16, fp32 accumulation), K = d
 //                         in slices of 64 loaded straight into two LDS buffers;
 //                         the tile is reduced in the epilogue to one (max,
@@ -33,7 +34,7 @@
 #include <stdint.h>
 
 #include <type_traits>
-#include <vector>
+#include <utility>
 
 #include "internal.h"
 #include "dart.h"
@@ -94,7 +95,7 @@ __device__ __forceinline__ int swz(int r) { return (r / (16 / CH)) % CH; }
 template <int BM_, int BN_, int WM_, int WN_, int NS_, int BK_ = 64>
 struct Cfg {
     static constexpr int BM = BM_, BN = BN_, BK = BK_, WM = WM_, WN = WN_, NS = NS_;
-    static_assert(NS == 2, "the K loop alternates two LDS buffers");
+    static_assert(NS == 2 || NS == 3, "buffers of the K loop");
     static constexpr int CH = BK / 8;          // 16-byte chunks per row and slice
     static constexpr int LROWS = 64 / CH;      // rows one load instruction fills
     static constexpr int KSTEPS = BK / 16;     // MFMA k-steps per slice
@@ -132,8 +133,19 @@ struct Cfg {
 // loads: 256 x 256 with 8 waves as 4 x 2 (64 x 128 per wave) and two 64-wide
 // buffers is the fastest.
 using LmCfg = Cfg<256, 256, 4, 2, 2>;
-static_assert(sizeof(LmCfg::Smem) <= 160 * 1024, "LDS per workgroup");
+// Tiles of fewer rows, for few rows in all: a third buffer fits the LDS, so that
+// two slices are in flight where W comes from HBM and little is multiplied per
+// byte of it. Measured (d = 3584, V = 152064; statistics and dlogits, us): 64
+// rows 213 and 204 with the 64-row tile (243 and 241 with two buffers), 279 and
+// 270 with the 256-row one; 128 rows 231 and 220 with the 128-row tile (274 and
+// 267 with two buffers), 285 and 281.
+using LmCfg128 = Cfg<128, 256, 2, 4, 3>;
+using LmCfg64 = Cfg<64, 256, 2, 4, 3>;
+static_assert(sizeof(LmCfg::Smem) <= 160 * 1024 && sizeof(LmCfg128::Smem) <= 160 * 1024 &&
+                  sizeof(LmCfg64::Smem) <= 160 * 1024,
+              "LDS per workgroup");
 constexpr int kMergeWaves = 4;
+constexpr int kMergeBatch = 5;
 
 struct Triple {
     float m, s, w;  // reference, sum of e^{z-m}, sum of e^{z-m} (z-m), natural units
@@ -288,8 +300,6 @@ __device__ __forceinline__ void gemm_tile(const uint16_t* __restrict__ A, int64_
         rdb[ks] = b_at + (uint32_t)(rb * BK + (c ^ swz<CH>(rb)) * 8) * 2;
         asm volatile("" : "+v"(rdb[ks]));
     }
-    static_assert((C::NS - 1) * C::BN * BK * 2 + (C::TN - 1) * 32 * BK * 2 < 65536,
-                  "B read immediates");
     bf16x8 af[2][C::TM], bfr[2][C::TN];
     auto read_step = [&](auto bufc, int ks, int set) {
         constexpr int buf = decltype(bufc)::value;
@@ -319,18 +329,22 @@ __device__ __forceinline__ void gemm_tile(const uint16_t* __restrict__ A, int64_
     // the first operand reads of that slice are in flight.
     constexpr int LASTSET = (C::KSTEPS - 1) & 1;
 
-    // two LDS buffers: slice kt+1 loads while slice kt is multiplied
+    // NS LDS buffers: slices kt+1 .. kt+NS-1 load while slice kt is multiplied
+    constexpr int LOADS = 2 * (C::IA + C::IB);  // of an issuing wave and slice
     auto slice = [&](auto bufc, int64_t kt) {
         constexpr int buf = decltype(bufc)::value;
         // slice kt has landed for this wave; the barrier makes it so for all,
-        // and every wave has finished reading the other buffer (slice kt-1)
-        wait_vmcnt<0>();
+        // and every wave has finished reading the buffer of slice kt-1
+        if (C::NS == 2 || kt + C::NS - 2 >= nk)
+            wait_vmcnt<0>();
+        else
+            wait_vmcnt<(C::NS - 2) * LOADS>();
         lds_ring_barrier();
         if ((K % BK) && kt == nk - 1) {
             zero_tail(kt, buf);
             lds_ring_barrier();
         }
-        if (kt + 1 < nk) issue(kt + 1, buf ^ 1);
+        if (kt + C::NS - 1 < nk) issue(kt + C::NS - 1, (buf + C::NS - 1) % C::NS);
         // the operands of k-step ks+1 are read while the MFMAs of k-step ks issue
         read_step(bufc, 0, 0);
         __builtin_amdgcn_s_setprio(1);
@@ -351,16 +365,20 @@ __device__ __forceinline__ void gemm_tile(const uint16_t* __restrict__ A, int64_
         }
         __builtin_amdgcn_s_setprio(0);
     };
-    // the loop body has no condition on the accumulators: an odd last slice
-    // runs after it (a conditional second slice in the body made the compiler
-    // copy every accumulator at the join)
-    issue(0, 0);
+    // the loop body has no condition on the accumulators: the last slices that
+    // do not fill a round of the buffers run after it (a conditional second
+    // slice in the body made the compiler copy every accumulator at the join)
+#pragma unroll
+    for (int b = 0; b < C::NS - 1; ++b)
+        if (b == 0 || b < nk) issue(b, b);
     int64_t kt = 0;
-    for (; kt + 1 < nk; kt += 2) {
+    for (; kt + C::NS - 1 < nk; kt += C::NS) {
         slice(std::integral_constant<int, 0>{}, kt);
         slice(std::integral_constant<int, 1>{}, kt + 1);
+        if constexpr (C::NS > 2) slice(std::integral_constant<int, 2 % C::NS>{}, kt + 2);
     }
     if (kt < nk) slice(std::integral_constant<int, 0>{}, kt);
+    if (C::NS > 2 && kt + 1 < nk) slice(std::integral_constant<int, 1>{}, kt + 1);
     mfmas(LASTSET, C::TM - 1, C::TM);
     __syncthreads();
 #else
@@ -616,9 +634,17 @@ lmhead_merge_kernel(const float4* __restrict__ part, const float* __restrict__ z
     const int64_t t = (int64_t)blockIdx.x * kMergeWaves + (threadIdx.x >> 6);
     if (t >= T) return;
     Triple acc = {-INFINITY, 0.f, 0.f};
-    for (int64_t j = lane; j < nvt; j += 64) {
-        const float4 p = part[t * nvt + j];
-        acc = merge(acc, Triple{p.x, p.y, p.z});
+    // a lane's next kMergeBatch triples are loaded together (an empty triple
+    // past the last): one after the other, their latency was the kernel's time
+    for (int64_t j0 = lane; j0 < nvt; j0 += 64 * kMergeBatch) {
+        float4 p[kMergeBatch];
+#pragma unroll
+        for (int k = 0; k < kMergeBatch; ++k) {
+            const int64_t j = j0 + 64 * k;
+            p[k] = j < nvt ? part[t * nvt + j] : make_float4(-INFINITY, 0.f, 0.f, 0.f);
+        }
+#pragma unroll
+        for (int k = 0; k < kMergeBatch; ++k) acc = merge(acc, Triple{p[k].x, p[k].y, p[k].z});
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
@@ -838,6 +864,7 @@ __device__ __forceinline__ void gemm_tile_bwd(const uint16_t* __restrict__ A, in
         rdb[j] = b_at + tr_off(wc + j * 32);
         asm volatile("" : "+v"(rdb[j]));
     }
+    static_assert(C::NS == 2, "two buffers");
     static_assert((C::NS - 1) * C::BN * BK * 2 + (C::KSTEPS - 1) * 16 * kTw * 2 + 4 * kTw * 2 <
                       65536,
                   "B read immediates");
@@ -1186,6 +1213,26 @@ constexpr int64_t kRowBlocks = 65536;
 // row: (BM - 1) rows of ld elements must stay below 2^31 bytes.
 constexpr int64_t kMaxLd = int64_t(1) << 22;
 
+// Rows of the tile that forms rows x V logits fastest: 64, 128 or 256. One
+// workgroup runs per compute unit, so a launch takes its tiles in rounds of
+// kUnits, and a round of 256-, 128- or 64-row tiles takes 92, 54 or 45 us at
+// d = 3584 (T = 1000, 1000 and 256): the tile with the least rounds x time. So
+// 64 rows go as one 64-row tile, up to 128 and 129 - 384 as 128-row tiles at
+// V = 152064 (300 rows: 7 rounds of 128-row tiles against 5 of 256), more as
+// 256-row ones, unless those would leave units idle (1000 rows of V = 8000).
+constexpr int64_t kUnits = 256;
+int tile_rows(int64_t rows, int64_t V) {
+    const int64_t nvt = (V + LmCfg::BN - 1) / LmCfg::BN;
+    int best = 256;
+    double least = 0;
+    for (const auto& [bm, t] : {std::pair<int, double>{256, 92}, {128, 54}, {64, 45}}) {
+        const int64_t tiles = (rows + bm - 1) / bm * nvt;
+        const double cost = (double)((tiles + kUnits - 1) / kUnits) * t;
+        if (bm == 256 || cost < least) best = bm, least = cost;
+    }
+    return best;
+}
+
 // Host-side argument rules shared by the LM-head entry points.
 bool bad_lmhead_args(const void* hidden, int64_t T, int64_t d, int64_t ld_h, const void* weight,
                      int64_t V, int64_t ld_w) {
@@ -1194,6 +1241,20 @@ bool bad_lmhead_args(const void* hidden, int64_t T, int64_t d, int64_t ld_h, con
         return true;
     if (d % 8 || ld_h < d || ld_w < d || ld_h % 8 || ld_w % 8) return true;
     return reinterpret_cast<uintptr_t>(hidden) % 16 || reinterpret_cast<uintptr_t>(weight) % 16;
+}
+
+// f(tile configuration) for rows x V logits. The launch's limits are checked
+// with 256-row tiles, as ever; smaller ones are taken where they fit too.
+template <class F>
+void with_tile(int64_t rows, int64_t V, F&& f) {
+    int bm = tile_rows(rows, V);
+    if (!grid_fits((rows + bm - 1) / bm * vocab_tiles(V), LmCfg::THREADS)) bm = 256;
+    if (bm == 64)
+        f(LmCfg64{});
+    else if (bm == 128)
+        f(LmCfg128{});
+    else
+        f(LmCfg{});
 }
 
 dart_status_t launch_dlogits(const uint16_t* hidden, int64_t rows, int64_t d, int64_t ld_h,
@@ -1205,10 +1266,13 @@ dart_status_t launch_dlogits(const uint16_t* hidden, int64_t rows, int64_t d, in
     const int64_t nmt = (rows + LmCfg::BM - 1) / LmCfg::BM, nvt = vocab_tiles(V);
     if (!grid_fits(nmt * nvt, LmCfg::THREADS) || ld_h > kMaxLd || ld_w > kMaxLd)
         return DART_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(lmhead_dlogits_kernel<LmCfg>, dim3((unsigned)(nmt * nvt)),
-                       dim3(LmCfg::THREADS), 0, stream, hidden, rows, ld_h, weight, V, ld_w, d,
-                       target, lse, logp, coef, scale, out, ld_out, vbase, nmt, nvt, dyn_rows,
-                       dyn_base);
+    with_tile(rows, V, [&](auto cfg) {
+        using C = decltype(cfg);
+        const int64_t nm = (rows + C::BM - 1) / C::BM;
+        hipLaunchKernelGGL(lmhead_dlogits_kernel<C>, dim3((unsigned)(nm * nvt)), dim3(C::THREADS),
+                           0, stream, hidden, rows, ld_h, weight, V, ld_w, d, target, lse, logp,
+                           coef, scale, out, ld_out, vbase, nm, nvt, dyn_rows, dyn_base);
+    });
     return hipGetLastError() == hipSuccess ? DART_OK : DART_ERR_HIP;
 }
 
@@ -1243,11 +1307,14 @@ dart_status_t dart_lmhead_tok_stats_ex(const void* hidden, int64_t T, int64_t d,
         return DART_ERR_UNSUPPORTED;
     float4* part = static_cast<float4*>(workspace);
     float* z_y = reinterpret_cast<float*>(part + T * nvt);
-    hipLaunchKernelGGL(lmhead_stats_kernel<LmCfg>, dim3((unsigned)(nmt * nvt)), dim3(LmCfg::THREADS),
-                       0, stream,
-                       static_cast<const uint16_t*>(hidden), T, ld_h,
-                       static_cast<const uint16_t*>(weight), V, ld_w, d, target, inv_temp, nmt,
-                       nvt, part, z_y);
+    with_tile(T, V, [&](auto cfg) {
+        using C = decltype(cfg);
+        const int64_t nm = (T + C::BM - 1) / C::BM;
+        hipLaunchKernelGGL(lmhead_stats_kernel<C>, dim3((unsigned)(nm * nvt)), dim3(C::THREADS), 0,
+                           stream, static_cast<const uint16_t*>(hidden), T, ld_h,
+                           static_cast<const uint16_t*>(weight), V, ld_w, d, target, inv_temp, nm,
+                           nvt, part, z_y);
+    });
     hipLaunchKernelGGL(lmhead_merge_kernel, dim3((unsigned)((T + kMergeWaves - 1) / kMergeWaves)),
                        dim3(kMergeWaves * 64), 0, stream, part, z_y, T, nvt, V, target, logp,
                        entropy, lse);
@@ -1326,7 +1393,7 @@ struct BackwardPlan {
 // 56 tiles of 2376 slices, 3.62 ms; in 2, 4 or 9 parts 2.10, 1.95 or 2.02 ms, adding
 // them up 7, 17 or 37 us more). So that at least half
 // and at most all of the units have a part, none shorter than kMinPartSlices.
-constexpr int64_t kUnits = 256, kMinPartSlices = 32;
+constexpr int64_t kMinPartSlices = 32;
 int64_t dh_parts(int64_t rows, int64_t d, int64_t cols) {
     const int64_t tiles =
         ((rows + LmCfg::BM - 1) / LmCfg::BM) * ((d + LmCfg::BN - 1) / LmCfg::BN);

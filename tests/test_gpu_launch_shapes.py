@@ -186,3 +186,36 @@ def test_lmhead_backward_dh_in_parts(T, d, V, rows, cols, parts, flags):
     if bf:
         wide = dart.dart_lmhead_backward_split_workspace_bytes(T, d, V, rows, cols, flags & SKIP)
         assert torch.equal(a, run(wide, flags & SKIP)[0].to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("T,d,V", [
+    (64, 64, 1000),       # one 64-row tile, one K slice
+    (65, 128, 257),       # two 64-row tiles, two slices, one column past a tile
+    (200, 200, 33000),    # 128-row tiles: 130 a row of tiles
+    (256, 320, 40001),    # 128-row tiles, five slices
+    (500, 72, 60000),     # 256-row tiles
+])
+def test_lmhead_tile_rows(T, d, V):
+    """Every tile height: the statistics against the oracle, and dlogits bit for
+    bit those of calls on 64 rows at a time (the K sums run in the same order)."""
+    import torch
+
+    import paper_2509_23866_amd as dart
+    from tests import test_gpu_lmhead_grad as G
+
+    h, w, y, g = G._problem(T, d, V)
+    rlogp, rH, rlse = oracle.lmhead_token_stats(h, w, y)
+    hd, wd, yd, gd = G._dev_bf16(h), G._dev_bf16(w), _cuda(y), _cuda(g)
+    logp, ent, lse = dart.dart_lmhead_tok_stats(hd, wd, yd)
+    for got, ref in ((logp, rlogp), (ent, rH), (lse, rlse)):
+        assert np.abs(got.cpu().numpy() - ref).max() <= 2e-4
+    ld = (V + 7) // 8 * 8
+    out = torch.full((T, ld), 5.0, dtype=torch.bfloat16, device="cuda")
+    dart.dart_lmhead_dlogits(hd, wd, yd, lse, logp, gd, dlogits=out[:, :V])
+    assert bool((out[:, V:] == 5.0).all())
+    for a in range(0, T, 64):
+        b = min(T, a + 64)
+        part = torch.empty((b - a, ld), dtype=torch.bfloat16, device="cuda")
+        dart.dart_lmhead_dlogits(hd[a:b], wd, yd[a:b], lse[a:b], logp[a:b], gd[a:b],
+                                 dlogits=part[:, :V])
+        assert torch.equal(out[a:b, :V], part[:, :V]), (a, b)
