@@ -3,7 +3,9 @@
 Argument marshalling only: every step of the path runs in the HIP kernels of
 ``csrc/dart.hip``. torch supplies device memory and the stream. The library must
 be built (``__graft_entry__.build()``); if it is missing, importing a function
-raises — there is no CPU fallback.
+raises — there is no CPU fallback. Calls whose arguments are plain tensors, with
+the outputs left to the call and on the current stream, are marshalled natively
+(``csrc/binding.cpp``); all others, and every complaint about an argument, here.
 
 Functions carry the C names: ``dart_tok_stats``, ``dart_step_select``,
 ``dart_tis_loss_fwd_bwd`` (and its halves ``dart_tis_loss_fwd`` /
@@ -16,6 +18,7 @@ device calls.
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -152,6 +155,31 @@ def load_library():
     return _lib
 
 
+_native = None
+
+
+def _nat():
+    """The native marshalling (raises if it is not built)."""
+    global _native
+    if _native is None:
+        load_library()
+        _torch()
+        try:
+            native = importlib.import_module("._native", __name__)
+        except ImportError as e:
+            raise RuntimeError("_native.so is not built; run __graft_entry__.build()") from e
+        native.open(LIB_PATH)
+        _native = native
+    return _native
+
+
+def _made(out, *names):
+    """What a native call made, or DartError for the C call that failed."""
+    if type(out) is int:
+        raise DartError(names[out >> 8], out & 255)
+    return out
+
+
 def dart_status_string(code: int) -> str:
     return load_library().dart_status_string(int(code)).decode()
 
@@ -233,6 +261,10 @@ def _logits_meta(logits):
 def dart_tok_stats(logits, target, logp=None, entropy=None, lse=None, stream=None, inv_temp=1.0):
     """Per-token log-prob of the target, entropy and log-normaliser (float32 [T]
     each) of softmax(inv_temp * logits)."""
+    if logp is None and entropy is None and lse is None and stream is None:
+        out = _nat().tok_stats(logits, target, inv_temp)
+        if out is not None:
+            return _made(out, "dart_tok_stats", "dart_tok_stats_ex")
     torch = _torch()
     dt, T, V, ld = _logits_meta(logits)
     dev = logits.device
@@ -407,6 +439,13 @@ def dart_select_tis_loss_fwd(entropy, logp, logp_old, logp_rollout, adv, step_of
     4096 tokens and 8192 steps). Returns (step_entropy, step_mask,
     n_kept_steps, loss, tok_coef, stats). ``workspace`` as for
     dart_tis_loss_fwd_bwd."""
+    if (step_entropy is None and step_mask is None and n_kept_steps is None and loss is None
+            and tok_coef is None and stats is None and stream is None
+            and isinstance(workspace, str) and workspace == "auto"):
+        out = _nat().select_tis_loss_fwd(entropy, logp, logp_old, logp_rollout, adv, step_offsets,
+                                         rho, eps_low, eps_high, C, bool(with_stats))
+        if out is not None:
+            return _made(out, "dart_select_tis_loss_fwd")
     torch = _torch()
     dev = logp.device
     T = logp.numel()
@@ -448,6 +487,13 @@ def dart_tis_loss_fwd_ex(logp, logp_old, logp_rollout, adv, step_offsets, step_m
     """The loss with the KL term, aggregation and ratio level selectable.
     Returns (loss float64 [1], tok_coef float32 [T], stats float32 [6]).
     ``workspace`` as for dart_tis_loss_fwd_bwd."""
+    if (loss is None and tok_coef is None and stats is None and stream is None
+            and isinstance(workspace, str) and workspace == "auto"):
+        out = _nat().tis_loss_fwd_ex(logp, logp_old, logp_rollout, adv, step_offsets, step_mask,
+                                     logp_ref, eps_low, eps_high, C, DART_KL[kl], beta,
+                                     DART_AGG[aggregation], DART_RATIO[ratio], bool(with_stats))
+        if out is not None:
+            return _made(out, "dart_tis_loss_fwd_ex")
     torch = _torch()
     dev = logp.device
     T = logp.numel()
@@ -485,6 +531,11 @@ def dart_tis_grad(logits, target, logp, lse, tok_coef, dlogits=None, stream=None
     """dlogits = inv_temp * tok_coef * (onehot(target) - softmax(inv_temp * logits)),
     dtype of logits; ``skip_zero_rows`` writes rows with a zero coefficient
     without reading them."""
+    if stream is None:
+        out = _nat().tis_grad(logits, target, logp, lse, tok_coef, dlogits, inv_temp,
+                              bool(skip_zero_rows))
+        if out is not None:
+            return _made(out, "dart_tis_grad", "dart_tis_grad_ex")
     torch = _torch()
     dt, T, V, ld = _logits_meta(logits)
     dev = logits.device
@@ -516,6 +567,10 @@ def dart_tis_grad(logits, target, logp, lse, tok_coef, dlogits=None, stream=None
 def dart_grpo_advantage(reward, traj_step_offsets, group_traj_offsets, step_offsets, T=None,
                         adv=None, group_mean=None, group_std=None, stream=None):
     """Step-wise GRPO advantage per token (float32 [T]) and per-group mean/std."""
+    if adv is None and group_mean is None and group_std is None and stream is None:
+        out = _nat().grpo_advantage(reward, traj_step_offsets, group_traj_offsets, step_offsets, T)
+        if out is not None:
+            return _made(out, "dart_grpo_advantage")
     torch = _torch()
     dev = reward.device
     n_traj = reward.numel()
@@ -543,6 +598,10 @@ def dart_grpo_advantage(reward, traj_step_offsets, group_traj_offsets, step_offs
 def dart_step_select_groups(entropy, step_offsets, group_step_offsets, rho, step_entropy=None,
                             step_mask=None, n_kept_steps=None, stream=None):
     """Per-step entropy, mask and kept count per group (top ceil(rho S_g) of each group)."""
+    if step_entropy is None and step_mask is None and n_kept_steps is None and stream is None:
+        out = _nat().step_select_groups(entropy, step_offsets, group_step_offsets, rho)
+        if out is not None:
+            return _made(out, "dart_step_select_groups")
     torch = _torch()
     dev = entropy.device
     T = entropy.numel()
@@ -595,6 +654,11 @@ def dart_lmhead_tok_stats_ex(hidden, weight, target, inv_temp, logp=None, entrop
 
 
 def _lmhead_tok_stats(inv_temp, hidden, weight, target, logp, entropy, lse, workspace, stream):
+    if (logp is None and entropy is None and lse is None and stream is None
+            and isinstance(workspace, str) and workspace == "auto"):
+        out = _nat().lmhead_tok_stats(hidden, weight, target, inv_temp)
+        if out is not None:
+            return _made(out, "dart_lmhead_tok_stats" + ("" if inv_temp is None else "_ex"))
     torch = _torch()
     _matrix_bf16("hidden", hidden)
     dev = hidden.device
@@ -786,10 +850,20 @@ def lmhead_backward_plan(T: int, V: int, budget_bytes: int = 512 << 20):
     return best[1], best[2]
 
 
+_UPDATE = ("logp", "entropy", "lse", "step_entropy", "step_mask", "n_kept_steps", "loss",
+           "dlogits", "tok_coef", "stats")
+
+
 def policy_update(logits, target, logp_old, logp_rollout, adv, step_offsets, rho, eps_low,
                   eps_high, C, dlogits=None, stream=None):
     """tok_stats -> select_tis_loss_fwd -> tis_grad on one stream. Returns a dict
     of device tensors (nothing is synchronised)."""
+    if stream is None:
+        out = _nat().policy_update(logits, target, logp_old, logp_rollout, adv, step_offsets, rho,
+                                   eps_low, eps_high, C, dlogits)
+        if out is not None:
+            out = _made(out, "dart_tok_stats", "dart_select_tis_loss_fwd", "dart_tis_grad")
+            return dict(zip(_UPDATE, out))
     logp, ent, lse = dart_tok_stats(logits, target, stream=stream)
     step_ent, mask, n_kept, loss, coef, stats = dart_select_tis_loss_fwd(
         ent, logp, logp_old, logp_rollout, adv, step_offsets, rho, eps_low, eps_high, C,
