@@ -197,55 +197,63 @@ __device__ __forceinline__ void triple_add(Triple& a, const float* z, float inv_
     triple_add_exact<N>(a, z, inv_temp, k);
 }
 
-__device__ __forceinline__ Triple triple_merge(const Triple a, const Triple b) {
-    if (b.s == 0.f) return a;
-    if (a.s == 0.f) return b;
-    const float m = fmaxf(a.m, b.m);
-    const float da = (a.m - m) * kLog2e;
-    const float db = (b.m - m) * kLog2e;
-    const float ca = __builtin_amdgcn_exp2f(da);
-    const float cb = __builtin_amdgcn_exp2f(db);
-    Triple r;
-    r.m = m;
-    r.s = ca * a.s + cb * b.s;
-    r.w = ca * fmaf(da, a.s, a.w) + cb * fmaf(db, b.s, b.w);
-    return r;
+// Wave reductions in a fixed order on the DPP network (no LDS round trips): pairs
+// (quad_perm 1,0,3,2), quads (quad_perm 2,3,0,1), half-rows (row_half_mirror),
+// rows of 16 (row_mirror), then rows 0+1 and 2+3 (row_bcast15 into rows 1, 3)
+// and all four (row_bcast31 into rows 2, 3); lane 63 holds the result, which
+// every lane receives. The whole wave must be active.
+template <int CTRL, int ROW_MASK, class F>
+__device__ __forceinline__ float dpp_step(float x, float none, F f) {
+    return f(x, __int_as_float(__builtin_amdgcn_update_dpp(
+                    __float_as_int(none), __float_as_int(x), CTRL, ROW_MASK, 0xf, false)));
 }
 
-__device__ __forceinline__ Triple triple_wave_reduce(Triple a) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        Triple b;
-        b.m = __shfl_xor(a.m, off);
-        b.s = __shfl_xor(a.s, off);
-        b.w = __shfl_xor(a.w, off);
-        a = triple_merge(a, b);
+// none: what f leaves alone (lanes without a partner get it).
+template <class F>
+__device__ __forceinline__ float wave_reduce_f32(float x, float none, F f) {
+    x = dpp_step<0xB1, 0xf>(x, none, f);
+    x = dpp_step<0x4E, 0xf>(x, none, f);
+    x = dpp_step<0x141, 0xf>(x, none, f);
+    x = dpp_step<0x140, 0xf>(x, none, f);
+    x = dpp_step<0x142, 0xa>(x, none, f);
+    x = dpp_step<0x143, 0xc>(x, none, f);
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
+}
+
+// The merge of a wave's triples: the largest reference first, each lane rescaled
+// to it once, then two sums. (Merging pairs of triples, six rounds of three
+// exchanges and two exponentials, then the waves one after the other, cost a row
+// ~2 us behind its last load.)
+__device__ __forceinline__ Triple triple_wave_merge(const Triple a) {
+    const float M = wave_reduce_f32(a.s != 0.f ? a.m : -INFINITY, -INFINITY,
+                                    [](float x, float y) { return fmaxf(x, y); });
+    float s = 0.f, w = 0.f;
+    if (a.s != 0.f) {
+        const float d = (a.m - M) * kLog2e;
+        const float c = __builtin_amdgcn_exp2f(d);
+        s = c * a.s;
+        w = c * fmaf(d, a.s, a.w);
     }
-    return a;
+    auto add = [](float x, float y) { return x + y; };
+    return Triple{M, wave_reduce_f32(s, 0.f, add), wave_reduce_f32(w, 0.f, add)};
 }
 
-// The statistics pass uses THREADS threads per row and UNROLL 16-byte vectors
-// per lane per iteration: vector j of the aligned body is read by lane
-// j % THREADS in iteration j / (THREADS * UNROLL), so every wave reads 1 KiB
-// contiguous per load. With PIPE the iteration loop is unrolled twice over two
-// register sets, so the loads of the next iteration are issued before the
-// current one is consumed (2 * UNROLL vectors in flight per lane). NTL / NTS
-// select non-temporal loads / stores. The entry points instantiate the
-// configurations chosen by measurement on MI355X (V = 152064 bf16 rows): the
-// read-only statistics pass peaks with 12 waves per row (768 threads); the
-// read+write gradient pass with one-shot workgroups of 128 threads x 2
-// vectors over 4 KB chunks of a row (best of 32..1024 threads x 1..8 vectors,
-// ~15% faster than one 1024-thread workgroup per row and faster than a plain
-// elementwise copy). Non-temporal loads and stores win in both; register
-// double-buffering does not.
-constexpr int kStatsThreads = 768;
+// The statistics pass gives each row one workgroup and each lane kStatsUnroll
+// 16-byte vectors at a time: vector j of the aligned body is read by lane
+// j % THREADS in iteration j / (THREADS * kStatsUnroll), so every wave reads 1
+// KiB contiguous per load, and the last, partial iteration is one batch too.
+// THREADS follows the row's length, see stats_threads. The gradient pass runs
+// one-shot workgroups of 128 threads x 2 vectors over 4 KB chunks of a row (best
+// of 32..1024 threads x 1..8 vectors, ~15% faster than one 1024-thread workgroup
+// per row and faster than a plain elementwise copy). Non-temporal loads and
+// stores win in both; register double-buffering does not. NTL / NTS select
+// non-temporal loads / stores.
 constexpr int kStatsUnroll = 4;
-constexpr int64_t kStatsMaxRows = int64_t(1) << 22;  // rows per launch of the statistics
-static_assert(kStatsMaxRows * kStatsThreads <= 0xFFFFFFFFll, "statistics grid");
+// rows per launch of the statistics (a dispatch holds at most 2^32 - 1 work-items)
+constexpr int64_t kStatsMaxRows = int64_t(1) << 22;
 constexpr int kGradThreads = 128;
 constexpr int kGradUnroll = 2;
 constexpr int64_t kGradMaxBlocks = 1ll << 24;
-constexpr bool kPipe = false;
 constexpr bool kNtLoad = true;
 constexpr bool kNtStore = true;
 
@@ -300,49 +308,21 @@ __device__ __forceinline__ RowLayout row_layout(const void* row, int64_t V) {
     return L;
 }
 
-// Runs body(v, it) over the full iterations of the aligned body, with the
-// loads of iteration it+1 in flight while iteration it is consumed when PIPE.
-template <int THREADS, int UNROLL, bool PIPE, bool NTL, class Body>
-__device__ __forceinline__ void stream_iterations(const u32x4* vrow, int64_t nfull, int tid,
-                                                  Body&& body) {
-    constexpr int PER_IT = THREADS * UNROLL;
-    auto load = [&](u32x4* v, int64_t it) {
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) v[u] = vload<NTL>(vrow + it * PER_IT + u * THREADS + tid);
-    };
-    if constexpr (!PIPE) {
-        for (int64_t it = 0; it < nfull; ++it) {
-            u32x4 v[UNROLL];
-            load(v, it);
-            body(v, it);
-        }
-    } else {
-        u32x4 a[UNROLL], b[UNROLL];
-        if (nfull > 0) load(a, 0);
-        int64_t it = 0;
-        for (; it + 1 < nfull; it += 2) {
-            load(b, it + 1);
-            body(a, it);
-            if (it + 2 < nfull) load(a, it + 2);
-            body(b, it + 1);
-        }
-        if (it < nfull) body(a, it);
-    }
-}
-
 // ------------------------------------------------------------------------
 // K1: token statistics
 // ------------------------------------------------------------------------
 
-template <dart_dtype_t D, int THREADS, int UNROLL, bool PIPE, bool NTL>
-__global__ void __launch_bounds__(THREADS)
+template <dart_dtype_t D, int THREADS, int UNROLL, bool NTL>
+__global__ void __launch_bounds__(THREADS, 8)  // 8 waves a SIMD: 64 registers
 tok_stats_kernel(const void* __restrict__ logits, int64_t V, int64_t ld,
                  const int32_t* __restrict__ target, float inv_temp, float* __restrict__ logp,
                  float* __restrict__ entropy, float* __restrict__ lse) {
     using E = typename Elt<D>::T;
     constexpr int EPV = Elt<D>::kPerVec;
     constexpr int PER_IT = THREADS * UNROLL;
-    __shared__ Triple partial[THREADS / 64];
+    constexpr int WAVES = THREADS / 64;
+    static_assert(WAVES <= 64, "one wave merges the waves' triples");
+    __shared__ Triple partial[WAVES];
 
     const int64_t t = blockIdx.x;
     const int tid = threadIdx.x;
@@ -358,53 +338,67 @@ tok_stats_kernel(const void* __restrict__ logits, int64_t V, int64_t ld,
     // end, so that 1 - p_target (and logp near 0) keep full relative accuracy.
     const int64_t vy = (y >= L.head && y < L.body_end) ? (y - L.head) / EPV : -1;
     const int64_t it_y = vy >= 0 ? vy / PER_IT : -1;
-    const int64_t nfull = L.nvec / PER_IT;
+    const int y_in_vec = (int)((y - L.head) % EPV);
+    auto drop_target = [&](float* z, int64_t j) {
+        if (j != vy) return;
+#pragma unroll
+        for (int e = 0; e < EPV; ++e)
+            if (e == y_in_vec) z[e] = -INFINITY;
+    };
+    // the target's logit and the head and tail elements (fewer than 2 EPV, one
+    // a lane) are asked for first and used last
+    const float zy_raw = load_one<D>(row, y_ok ? y : 0);
+    const int64_t nscalar = L.head + (V - L.body_end);
+    float z1[1] = {-INFINITY};
+    if (tid < nscalar) {
+        const int64_t col = tid < L.head ? tid : L.body_end + (tid - L.head);
+        if (col != y) z1[0] = load_one<D>(row, col);
+    }
 
     const float k = inv_temp * kLog2e;
     Triple acc = triple_empty();
-    stream_iterations<THREADS, UNROLL, PIPE, NTL>(vrow, nfull, tid, [&](const u32x4* v, int64_t it) {
+    const int64_t nfull = L.nvec / PER_IT;
+    for (int64_t it = 0; it < nfull; ++it) {
+        u32x4 v[UNROLL];
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) v[u] = vload<NTL>(vrow + it * PER_IT + u * THREADS + tid);
         float z[UNROLL * EPV];
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) unpack<D>(v[u], z + u * EPV);
-        if (it == it_y) {
+        if (it == it_y)
 #pragma unroll
-            for (int u = 0; u < UNROLL; ++u)
-#pragma unroll
-                for (int e = 0; e < EPV; ++e) {
-                    const int64_t col = L.head + (it * PER_IT + u * THREADS + tid) * EPV + e;
-                    if (col == y) z[u * EPV + e] = -INFINITY;
-                }
-        }
+            for (int u = 0; u < UNROLL; ++u) drop_target(z + u * EPV, it * PER_IT + u * THREADS + tid);
         triple_add<UNROLL * EPV>(acc, z, inv_temp, k);
-    });
-    for (int64_t j = nfull * PER_IT + tid; j < L.nvec; j += THREADS) {
-        float z[EPV];
-        unpack<D>(vload<NTL>(vrow + j), z);
-        if (j == vy) {
+    }
+    if (nfull * PER_IT < L.nvec) {
+        const int64_t j0 = nfull * PER_IT + tid;
+        u32x4 v[UNROLL];
 #pragma unroll
-            for (int e = 0; e < EPV; ++e)
-                if (L.head + j * EPV + e == y) z[e] = -INFINITY;
-        }
-        triple_add<EPV>(acc, z, inv_temp, k);
+        for (int u = 0; u < UNROLL; ++u)
+            if (j0 + u * THREADS < L.nvec) v[u] = vload<NTL>(vrow + j0 + u * THREADS);
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u)
+            if (j0 + u * THREADS < L.nvec) {
+                float z[EPV];
+                unpack<D>(v[u], z);
+                drop_target(z, j0 + u * THREADS);
+                triple_add<EPV>(acc, z, inv_temp, k);
+            }
     }
-    const int64_t nscalar = L.head + (V - L.body_end);
-    for (int64_t q = tid; q < nscalar; q += THREADS) {
-        const int64_t col = q < L.head ? q : L.body_end + (q - L.head);
-        float z1[1] = {col == y ? -INFINITY : load_one<D>(row, col)};
-        triple_add<1>(acc, z1, inv_temp, k);
-    }
+    if (tid < nscalar) triple_add<1>(acc, z1, inv_temp, k);
 
-    acc = triple_wave_reduce(acc);
-    const int wave = tid >> 6;
-    if ((tid & 63) == 0) partial[wave] = acc;
-    __syncthreads();
+    Triple x = triple_wave_merge(acc);
+    if constexpr (WAVES > 1) {
+        const int lane = tid & 63;
+        if (lane == 0) partial[tid >> 6] = x;
+        __syncthreads();
+        if (tid >= 64) return;
+        x = triple_wave_merge(lane < WAVES ? partial[lane] : triple_empty());
+    }
     if (tid != 0) return;
-    Triple x = partial[0];
-#pragma unroll
-    for (int i = 1; i < THREADS / 64; ++i) x = triple_merge(x, partial[i]);
 
     // add the target element
-    const float zy = y_ok ? load_one<D>(row, y) * inv_temp : __builtin_nanf("");
+    const float zy = y_ok ? zy_raw * inv_temp : __builtin_nanf("");
     const float M = fmaxf(x.m, zy);
     float sx = 0.f, wx = 0.f;
     if (x.s > 0.f) {
@@ -435,12 +429,8 @@ constexpr int kSelLdsKeys = 8192;  // groups up to this many steps keep their ke
 constexpr int kSelLdsTokens = 16384;  // one group of up to this many tokens: means fused in
 constexpr int kSelRankMax = 256;   // groups up to this many steps are ranked directly
 
-// Wave sums in a fixed order on the DPP network (no LDS round trips): pairs
-// (quad_perm 1,0,3,2), quads (quad_perm 2,3,0,1), half-rows (row_half_mirror),
-// rows of 16 (row_mirror), then rows 0+1 and 2+3 (row_bcast15 into rows 1, 3)
-// and all four (row_bcast31 into rows 2, 3); lane 63 holds the total, which
-// every lane receives. The whole wave must be active. A 64-bit value moves as
-// two 32-bit halves under the same control.
+// Wave sums of 64-bit values in the order of wave_reduce_f32: a value moves as two
+// 32-bit halves under the same control.
 template <int CTRL, int ROW_MASK = 0xf>
 __device__ __forceinline__ uint64_t dpp_u64(uint64_t x) {
     const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, CTRL, ROW_MASK, 0xf, false);
@@ -1450,6 +1440,44 @@ dart_status_t launch_status() {
     return hipGetLastError() == hipSuccess ? DART_OK : DART_ERR_HIP;
 }
 
+// Threads per row of the statistics pass for T rows of nvec vectors. A row is a
+// chain of loads, reduction and finish, so short rows want many small workgroups
+// on a compute unit and long ones enough loads in flight to need few iterations.
+// Measured (us; 768 threads as every row had before, then the choice, its
+// neighbours in brackets):
+//   T 16384, V   2048 bf16 (256 vectors)   110 -> 128: 18 [256: 21]
+//   T 16000, V   8000 bf16 (1000)          147 -> 256: 44 [128: 45, 512: 54]
+//   T  6000, V  32003 bf16 (4000)           94 -> 512: 60 [256: 66, 768: 73]
+//   T  4096, V 152064 bf16 (19008)         183 -> 768: 183 [512: 187, 1024: 184]
+// Up to 256 rows each has a compute unit to itself and wants its width: T = 200, V
+// = 32000 fp32 (8000 vectors) 9.1 -> 768: 7.1 [512: 8.6].
+int stats_threads(int64_t T, int64_t nvec) {
+    if (nvec <= 512) return 128;
+    if (nvec <= 2048) return 256;
+    return nvec <= 8192 && T > 256 ? 512 : 768;
+}
+
+template <int THREADS>
+void launch_tok_stats(const void* logits, dart_dtype_t dtype, int64_t T, int64_t V, int64_t ld,
+                      const int32_t* target, float inv_temp, float* logp, float* entropy,
+                      float* lse, hipStream_t stream) {
+    constexpr int64_t most = kStatsMaxRows;
+    static_assert(most * THREADS <= 0xFFFFFFFFll, "statistics grid");
+    for (int64_t r0 = 0; r0 < T; r0 += most) {
+        const dim3 grid((unsigned)(T - r0 < most ? T - r0 : most)), block(THREADS);
+        const void* lr =
+            static_cast<const char*>(logits) + (size_t)r0 * (size_t)ld * elem_size(dtype);
+        if (dtype == DART_BF16)
+            hipLaunchKernelGGL((tok_stats_kernel<DART_BF16, THREADS, kStatsUnroll, kNtLoad>), grid,
+                               block, 0, stream, lr, V, ld, target + r0, inv_temp, logp + r0,
+                               entropy + r0, lse + r0);
+        else
+            hipLaunchKernelGGL((tok_stats_kernel<DART_F32, THREADS, kStatsUnroll, kNtLoad>), grid,
+                               block, 0, stream, lr, V, ld, target + r0, inv_temp, logp + r0,
+                               entropy + r0, lse + r0);
+    }
+}
+
 // K3 and the loss reduction for one configuration: up to kCoefMaxBlocks
 // workgroups plus the finalize kernel when a workspace is given and T >
 // kCoefOneBlockMaxT (token ratios) or S > kStepCoefOneBlockMaxS (step ratios),
@@ -1609,23 +1637,11 @@ dart_status_t dart_tok_stats_ex(const void* logits, dart_dtype_t dtype, int64_t 
     if (const dart_status_t ck = dart_check::run(
             stream, {{dart_check::Item::Ids, target, T, V}}); ck != DART_OK)
         return ck;
-    // one workgroup per row, at most kStatsMaxRows rows per launch (a dispatch
-    // holds at most 2^32 - 1 work-items)
-    const size_t esz = elem_size(dtype);
-    for (int64_t r0 = 0; r0 < T; r0 += kStatsMaxRows) {
-        const int64_t rows = T - r0 < kStatsMaxRows ? T - r0 : kStatsMaxRows;
-        const void* lr = static_cast<const char*>(logits) + (size_t)r0 * (size_t)ld * esz;
-        const dim3 grid((unsigned)rows), block(kStatsThreads);
-        if (dtype == DART_BF16)
-            hipLaunchKernelGGL(
-                (tok_stats_kernel<DART_BF16, kStatsThreads, kStatsUnroll, kPipe, kNtLoad>), grid,
-                block, 0, stream, lr, V, ld, target + r0, inv_temp, logp + r0, entropy + r0,
-                lse + r0);
-        else
-            hipLaunchKernelGGL(
-                (tok_stats_kernel<DART_F32, kStatsThreads, kStatsUnroll, kPipe, kNtLoad>), grid,
-                block, 0, stream, lr, V, ld, target + r0, inv_temp, logp + r0, entropy + r0,
-                lse + r0);
+    switch (stats_threads(T, V / (int64_t)(16 / elem_size(dtype)))) {
+        case 128: launch_tok_stats<128>(logits, dtype, T, V, ld, target, inv_temp, logp, entropy, lse, stream); break;
+        case 256: launch_tok_stats<256>(logits, dtype, T, V, ld, target, inv_temp, logp, entropy, lse, stream); break;
+        case 512: launch_tok_stats<512>(logits, dtype, T, V, ld, target, inv_temp, logp, entropy, lse, stream); break;
+        default: launch_tok_stats<768>(logits, dtype, T, V, ld, target, inv_temp, logp, entropy, lse, stream);
     }
     return launch_status();
 }

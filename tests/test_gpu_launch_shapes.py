@@ -219,3 +219,46 @@ def test_lmhead_tile_rows(T, d, V):
         dart.dart_lmhead_dlogits(hd[a:b], wd, yd[a:b], lse[a:b], logp[a:b], gd[a:b],
                                  dlogits=part[:, :V])
         assert torch.equal(out[a:b, :V], part[:, :V]), (a, b)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("T,vecs,extra", [
+    (5, 512, 0), (5, 512, 3),        # 128 threads: one full iteration, no tail and a tail
+    (5, 513, 0),                     # 256 threads, an iteration of 513 of 1024 vectors
+    (5, 2048, 7), (256, 2049, 0),    # 256 and 768 threads
+    (257, 2049, 1), (257, 8192, 0),  # 512 threads
+    (257, 8193, 5), (600, 8193, 0),  # 768 threads
+    (7, 1, 0), (7, 0, 3),            # one vector a row, none
+])
+def test_token_statistics_by_row_length(T, vecs, extra, dtype):
+    """Every workgroup size of the statistics pass at both ends of its range of
+    rows, at a 16-byte aligned and a misaligned row start, with the target in
+    the row's head, first and last vector, last full iteration and tail."""
+    import torch
+
+    import paper_2509_23866_amd as dart
+
+    per = 8 if dtype == "bf16" else 4
+    V = vecs * per + extra % per
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(V + T)
+    for shift in (0, 1):
+        ld = -(-V // per) * per + (per if shift else 0)
+        buf = torch.full((T * ld + 2 * per,), float("nan"), dtype=dt, device="cuda")
+        z = buf[shift:shift + T * ld].view(T, ld)[:, :V]
+        z.copy_((torch.randn(T, V, generator=g, device="cuda") * 3).to(dt))
+        y = torch.randint(V, (T,), generator=g, device="cuda", dtype=torch.int32)
+        for i, col in enumerate((0, V - 1, V // 2, max(0, (vecs - 1) * per), V - extra % per - 1)):
+            y[i % T] = min(V - 1, max(0, col))
+        z[torch.arange(T, device="cuda"), y.long()] += 4
+        z[0, : V // 3] = float("-inf")
+        if V // 3 and int(y[0]) < V // 3:
+            y[0] = V - 1
+        zh = z.contiguous().cpu()
+        host = zh.view(torch.int16).numpy().view(np.uint16) if dtype == "bf16" else zh.numpy()
+        logp, H_, lse = oracle.token_stats(host, y.cpu().numpy())
+        got = dart.dart_tok_stats(z, y)
+        for name, a, b in zip(("logp", "entropy", "lse"), got, (logp, H_, lse)):
+            err = np.abs(a.cpu().numpy() - b).max()
+            # a few fp32 roundings of values up to ~20
+            assert err <= 1.5e-5, (name, shift, err)
