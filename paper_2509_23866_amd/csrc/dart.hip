@@ -246,16 +246,21 @@ __device__ __forceinline__ Triple triple_wave_merge(const Triple a) {
 // one-shot workgroups of 128 threads x 2 vectors over 4 KB chunks of a row (best
 // of 32..1024 threads x 1..8 vectors, ~15% faster than one 1024-thread workgroup
 // per row and faster than a plain elementwise copy). Non-temporal loads and
-// stores win in both; register double-buffering does not. NTL / NTS select
-// non-temporal loads / stores.
+// stores win in both (see kCachedLogits); register double-buffering does not. NTL
+// / NTS select non-temporal loads / stores.
 constexpr int kStatsUnroll = 4;
 // rows per launch of the statistics (a dispatch holds at most 2^32 - 1 work-items)
 constexpr int64_t kStatsMaxRows = int64_t(1) << 22;
 constexpr int kGradThreads = 128;
 constexpr int kGradUnroll = 2;
 constexpr int64_t kGradMaxBlocks = 1ll << 24;
-constexpr bool kNtLoad = true;
 constexpr bool kNtStore = true;
+// Logits up to this size are loaded as any other data, larger ones
+// non-temporally: what fits the caches beside the gradient is still there when
+// the gradient pass reads it again. Measured for the two passes (us): 29 MB 24.0 ->
+// 21.8, 64 MB 36.2 -> 34.0, 91 MB 53.8 -> 51.0; but the statistics alone lose 8%
+// at 91 MB (23.0 -> 24.9, 12% at 1.2 GB) where they gain 5% at 29 MB.
+constexpr int64_t kCachedLogits = int64_t(64) << 20;
 
 template <bool NT>
 __device__ __forceinline__ u32x4 vload(const u32x4* p) {
@@ -1457,6 +1462,18 @@ int stats_threads(int64_t T, int64_t nvec) {
     return nvec <= 8192 && T > 256 ? 512 : 768;
 }
 
+// f(dtype, non-temporal loads) as compile-time constants.
+template <class F>
+void with_logits(dart_dtype_t dtype, int64_t T, int64_t V, F&& f) {
+    using BF16 = std::integral_constant<dart_dtype_t, DART_BF16>;
+    using F32 = std::integral_constant<dart_dtype_t, DART_F32>;
+    const bool nt = V > kCachedLogits / (T * (int64_t)elem_size(dtype));
+    if (dtype == DART_BF16)
+        nt ? f(BF16{}, std::true_type{}) : f(BF16{}, std::false_type{});
+    else
+        nt ? f(F32{}, std::true_type{}) : f(F32{}, std::false_type{});
+}
+
 template <int THREADS>
 void launch_tok_stats(const void* logits, dart_dtype_t dtype, int64_t T, int64_t V, int64_t ld,
                       const int32_t* target, float inv_temp, float* logp, float* entropy,
@@ -1467,14 +1484,13 @@ void launch_tok_stats(const void* logits, dart_dtype_t dtype, int64_t T, int64_t
         const dim3 grid((unsigned)(T - r0 < most ? T - r0 : most)), block(THREADS);
         const void* lr =
             static_cast<const char*>(logits) + (size_t)r0 * (size_t)ld * elem_size(dtype);
-        if (dtype == DART_BF16)
-            hipLaunchKernelGGL((tok_stats_kernel<DART_BF16, THREADS, kStatsUnroll, kNtLoad>), grid,
-                               block, 0, stream, lr, V, ld, target + r0, inv_temp, logp + r0,
+        auto go = [&](auto dt, auto nt) {
+            hipLaunchKernelGGL((tok_stats_kernel<decltype(dt)::value, THREADS, kStatsUnroll,
+                                                 decltype(nt)::value>),
+                               grid, block, 0, stream, lr, V, ld, target + r0, inv_temp, logp + r0,
                                entropy + r0, lse + r0);
-        else
-            hipLaunchKernelGGL((tok_stats_kernel<DART_F32, THREADS, kStatsUnroll, kNtLoad>), grid,
-                               block, 0, stream, lr, V, ld, target + r0, inv_temp, logp + r0,
-                               entropy + r0, lse + r0);
+        };
+        with_logits(dtype, T, V, go);
     }
 }
 
@@ -1846,14 +1862,12 @@ dart_status_t dart_tis_grad_ex(const void* logits, dart_dtype_t dtype, int64_t T
     const int64_t nchunk = nvec > 0 ? (nvec + per - 1) / per : 1;
     const int64_t nblocks = T * nchunk < kGradMaxBlocks ? T * nchunk : kGradMaxBlocks;
     const dim3 grid((unsigned)nblocks), block(kGradThreads);
-    if (dtype == DART_BF16)
-        hipLaunchKernelGGL((tis_grad_kernel<DART_BF16, kGradThreads, kGradUnroll, kNtLoad, kNtStore>),
+    with_logits(dtype, T, V, [&](auto dt, auto nt) {
+        hipLaunchKernelGGL((tis_grad_kernel<decltype(dt)::value, kGradThreads, kGradUnroll,
+                                            decltype(nt)::value, kNtStore>),
                            grid, block, 0, stream, logits, V, ld, target, lse, logp, tok_coef,
                            inv_temp, flags, dlogits, ld_out, T, nchunk);
-    else
-        hipLaunchKernelGGL((tis_grad_kernel<DART_F32, kGradThreads, kGradUnroll, kNtLoad, kNtStore>),
-                           grid, block, 0, stream, logits, V, ld, target, lse, logp, tok_coef,
-                           inv_temp, flags, dlogits, ld_out, T, nchunk);
+    });
     return launch_status();
 }
 
