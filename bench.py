@@ -8,9 +8,11 @@ a second pass of K steps with HIP events around each kernel. The default workloa
 action tokens in 64 steps, V = 152064, bf16 logits, separate gradient buffer.
 
 Prints one JSON line. `value` is logit elements per second (T*V per step
-time); `hbm_frac_step` counts 2 reads + 1 write of the T x V logits per step
-against 8 TB/s; `roofline` covers the dominant kernel (the gradient pass, one
-read + one write of T x V), timed with HIP events on its own stream;
+time); `hbm_frac_step` counts the bytes a step moves, 2 reads + 1 write of the T
+x V logits less the second read of the rows whose coefficient is zero, against
+8 TB/s; `roofline` covers the dominant kernel (the gradient pass, one write of T
+x V and one read of the rows with a coefficient), timed with HIP events on its
+own stream;
 `cpu_baseline` times the float64 oracle on the host cores.
 """
 
@@ -663,16 +665,17 @@ def measure_workload(wl, args, dev, headline):
     mid_ms = [e[1].elapsed_time(e[2]) for e in evs]
     grad_ms = [e[2].elapsed_time(e[3]) for e in evs]
     elems = T * V
-    grad_bytes = 2 * elems * esize
+    zero_frac = float((coef == 0).float().mean().item())
+    # the gradient pass does not read the logits of rows with a zero coefficient
+    grad_bytes = (2 - zero_frac) * elems * esize
     achieved = grad_bytes / (float(np.mean(grad_ms)) * 1e-3) / 1e9
     rec = measured_profile(DOMINANT, wl.name)
-    zero_frac = float((coef == 0).float().mean().item())
     out = {
         "wl": wl, "T": T, "V": V, "S": S, "dtype": wl.dtype, "in_place": wl.inplace,
         "logits_bytes": elems * esize, "ms_per_step": ms_per_step,
         "zero_row_fraction": zero_frac,
         "value": elems / (ms_per_step * 1e-3),
-        "hbm_frac_step": (3 * elems * esize / (ms_per_step * 1e-3) / 1e9) / HBM_PEAK_GBS,
+        "hbm_frac_step": ((3 - zero_frac) * elems * esize / (ms_per_step * 1e-3) / 1e9) / HBM_PEAK_GBS,
         "kernel_ms": {"tok_stats_kernel": float(np.mean(k1_ms)),
                       "tis_grad_kernel": float(np.mean(grad_ms)),
                       "step_select+tis_loss_fwd": float(np.mean(mid_ms))},

@@ -269,9 +269,9 @@ typedef struct {
 } dart_loss_config_t;
 
 /* Gradient flag: a row whose coefficient is exactly 0 (dropped step, clipped
- * token, zero advantage) is written as zeros without reading its logits. The
- * result is the same (+0 in place of -0); HBM traffic drops by the share of
- * such rows. */
+ * token, zero advantage) is written as +0 without reading its logits, whatever
+ * its lse. Without the flag such a row is not read either where its lse is
+ * finite: every element is then the zero of the sign that the product has. */
 #define DART_GRAD_SKIP_ZERO_ROWS 1u
 
 /* dart_tok_stats for softmax(inv_temp * z): inv_temp is an inverse sampling
@@ -288,8 +288,8 @@ dart_status_t dart_tok_stats_ex(const void* logits, dart_dtype_t dtype, int64_t 
  * required when config->kl != DART_KL_NONE, else ignored (may be NULL).
  * stats: [6] float32 or NULL: clip fraction, mean TIS weight, fraction at the
  * cap, N, mean KL, K (over kept tokens / steps). Other arguments and errors as
- * dart_tis_loss_fwd (step-level ratios run on one workgroup and leave the
- * workspace unused); also INVALID_ARG for a null config, an unknown enum value,
+ * dart_tis_loss_fwd (step-level ratios of up to 32 steps leave the workspace
+ * unused); also INVALID_ARG for a null config, an unknown enum value,
  * or beta < 0 / non-finite. */
 dart_status_t dart_tis_loss_fwd_ex(int64_t T, const float* logp, const float* logp_old,
                                    const float* logp_rollout, const float* logp_ref,

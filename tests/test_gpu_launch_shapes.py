@@ -262,3 +262,54 @@ def test_token_statistics_by_row_length(T, vecs, extra, dtype):
             err = np.abs(a.cpu().numpy() - b).max()
             # a few fp32 roundings of values up to ~20
             assert err <= 1.5e-5, (name, shift, err)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V,shift", [(1, 0), (9, 1), (2049, 3), (20000, 0)])
+def test_gradient_of_rows_with_a_zero_coefficient(V, shift, dtype):
+    """Rows whose coefficient is zero are written unread: the bits of
+    -g exp(z - lse), a zero of -g's sign (the target: of g's), with the logits
+    replaced by NaN; where lse is not finite, what the formula gives (NaN from
+    NaN or -inf), and plain zeros under the skip flag."""
+    import torch
+
+    import paper_2509_23866_amd as dart
+
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    per = 8 if dtype == "bf16" else 4
+    T, ld = 12, V + per + shift
+    g = torch.Generator(device="cuda").manual_seed(V)
+    base = torch.zeros(shift + T * ld, dtype=dt, device="cuda")
+    z = base[shift:].view(T, ld)[:, :V]
+    z.copy_((torch.randn(T, V, generator=g, device="cuda") * 3).to(dt))
+    y = torch.randint(V, (T,), generator=g, device="cuda", dtype=torch.int32)
+    logp, _, lse = dart.dart_tok_stats(z, y)
+    coef = torch.randn(T, generator=g, device="cuda") * 0.1
+    full = dart.dart_tis_grad(z, y, logp, lse, coef)
+    coef[[1, 4]], coef[[2, 7]] = 0.0, -0.0
+    zero = [1, 2, 4, 7]
+    z[zero] = float("nan")  # never read
+    bits = torch.int16 if dtype == "bf16" else torch.int32
+    for it in (1.0, 0.5):
+        dz = dart.dart_tis_grad(z, y, logp, lse, coef, inv_temp=it)
+        want = torch.zeros(T, V, device="cuda")
+        want[[1, 4]] = -0.0
+        want[[2, 7], y[[2, 7]].long()] = -0.0
+        want[[1, 4], y[[1, 4]].long()] = 0.0
+        # a target with all the mass (V = 1): g (-expm1(0)) turns the sign
+        sure = [t for t in zero if float(logp[t]) == 0.0]
+        want[sure, y[sure].long()] *= -1.0
+        assert torch.equal(dz[zero].view(bits), want[zero].to(dt).view(bits))
+        rest = [t for t in range(T) if t not in zero]
+        if it == 1.0:
+            assert torch.equal(dz[rest], full[rest])
+    bad = lse.clone()
+    bad[1], bad[2], bad[4] = float("nan"), float("-inf"), float("inf")
+    z[zero] = 1.0
+    dz = dart.dart_tis_grad(z, y, logp, bad, coef)
+    keep = torch.ones(T, V, dtype=torch.bool, device="cuda")
+    keep[torch.arange(T, device="cuda"), y.long()] = False
+    assert bool(dz[1][keep[1]].isnan().all()) and bool(dz[2][keep[2]].isnan().all())
+    assert bool((dz[4] == 0).all()) and bool((dz[7] == 0).all())
+    skipped = dart.dart_tis_grad(z, y, logp, bad, coef, skip_zero_rows=True)
+    assert bool((skipped[zero].view(bits) == 0).all())
