@@ -537,9 +537,12 @@ size_t dart_lmhead_backward_ex_workspace_bytes(int64_t T, int64_t d, int64_t V,
  * 0 for bad arguments or flags): the value above and, where a block has few
  * rows, room for dhidden's sum over the vocabulary in several fp32 parts of
  * min(chunk_rows, T) * d that run beside each other (together at most 64 MiB
- * where T and d are multiples of 256). A workspace of at least this size takes
- * the parts (one more rounding to fp32 per part in dhidden's sum), a smaller
- * one sums each element in one run. */
+ * where T and d are multiples of 256), and, in large calls without
+ * DART_LMHEAD_SKIP_ZERO_ROWS, at most 128 MiB for the compact rows: rows with a
+ * zero coefficient and a finite lse, whose dlogits are zeros, are then left out
+ * as under that flag. With a workspace of at least this size both are done: the
+ * fp32 sums of dhidden and dweight then run over fewer terms or in parts, with
+ * the same values up to the order of summation. */
 size_t dart_lmhead_backward_split_workspace_bytes(int64_t T, int64_t d, int64_t V,
                                                   int64_t chunk_rows, int64_t chunk_cols,
                                                   uint32_t flags);

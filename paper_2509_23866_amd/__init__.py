@@ -818,7 +818,7 @@ def dart_lmhead_backward_ex(hidden, weight, target, lse, logp, tok_coef, chunk_r
     ``workspace`` is "auto" or a uint8 device tensor of
     dart_lmhead_backward_ex_workspace_bytes(T, d, V, chunk_rows, chunk_cols, flags)
     bytes; one of dart_lmhead_backward_split_workspace_bytes(...), as "auto" allocates, is
-    faster where a block has few rows."""
+    faster where a block has few rows, and leaves zero rows out of large calls unasked."""
     if chunk_rows is None and chunk_cols is None:
         chunk_rows, chunk_cols = lmhead_backward_plan(hidden.shape[0], weight.shape[0])
     elif chunk_rows is None or chunk_cols is None:

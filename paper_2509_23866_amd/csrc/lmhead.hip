@@ -1096,19 +1096,27 @@ lmhead_bwd_gemms_kernel(BwdGemm dh, BwdGemm dw, int64_t n_dh) {
 
 int64_t vocab_tiles(int64_t V) { return (V + LmCfg::BN - 1) / LmCfg::BN; }
 
-// Rows whose coefficient is not 0, in increasing order: map[0 .. n) and
-// count[0] = n. One workgroup walks the rows 1024 at a time; the position of
-// each kept row is its wave's ballot prefix plus the earlier waves' counts.
+// Whether row t takes part in the compact problem. Its dlogits are zeros when
+// its coefficient is 0: by the caller's word under the skip flag (lse null),
+// else where lse is finite (an infinity or a NaN in the row would give NaNs).
+__device__ __forceinline__ bool row_counts(const float* __restrict__ coef,
+                                           const float* __restrict__ lse, int64_t t) {
+    return coef[t] != 0.f || (lse && !(fabsf(lse[t]) < INFINITY));
+}
+
+// The rows that count, in increasing order: map[0 .. n) and count[0] = n. One
+// workgroup walks the rows 1024 at a time; the position of each kept row is its
+// wave's ballot prefix plus the earlier waves' counts.
 constexpr int kCompactThreads = 1024;
 __global__ void __launch_bounds__(kCompactThreads)
-compact_rows_kernel(const float* __restrict__ coef, int64_t T, int32_t* __restrict__ map,
-                    int32_t* __restrict__ count) {
+compact_rows_kernel(const float* __restrict__ coef, const float* __restrict__ lse, int64_t T,
+                    int32_t* __restrict__ map, int32_t* __restrict__ count) {
     __shared__ int wave_n[kCompactThreads / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int64_t base = 0;
     for (int64_t t0 = 0; t0 < T; t0 += kCompactThreads) {
         const int64_t t = t0 + tid;
-        const bool keep = t < T && coef[t] != 0.f;
+        const bool keep = t < T && row_counts(coef, lse, t);
         const uint64_t ballot = __ballot(keep);
         const int before = __popcll(ballot & ((uint64_t(1) << lane) - 1));
         if (lane == 0) wave_n[wave] = __popcll(ballot);
@@ -1125,51 +1133,38 @@ compact_rows_kernel(const float* __restrict__ coef, int64_t T, int32_t* __restri
     if (tid == 0) count[0] = (int32_t)base;
 }
 
+// An element of a gradient output: fp32, or bf16 bits rounded to nearest even.
+__device__ __forceinline__ void put(float* p, float v) { *p = v; }
+__device__ __forceinline__ void put(uint16_t* p, float v) { *p = bf16_bits(v); }
+
 // Row i < count of the compact problem: hidden row map[i] and its per-row
-// values, one workgroup per row (grid-stride over the rows).
-__global__ void __launch_bounds__(64)
-gather_rows_kernel(const int32_t* __restrict__ map, const int32_t* __restrict__ count,
+// values; and row i of dh set to 0 where it does not count: one workgroup per row
+// (grid-stride over the rows). lse_word: lse or null, as row_counts takes it.
+template <class O>
+__global__ void __launch_bounds__(128)
+gather_rows_kernel(const int32_t* __restrict__ map, const int32_t* __restrict__ count, int64_t T,
                    const uint16_t* __restrict__ h, int64_t ld_h, int64_t d,
                    const int32_t* __restrict__ target, const float* __restrict__ lse,
                    const float* __restrict__ logp, const float* __restrict__ coef,
-                   uint16_t* __restrict__ h_c, int32_t* __restrict__ target_c,
-                   float* __restrict__ lse_c, float* __restrict__ logp_c, float* __restrict__ coef_c) {
+                   const float* __restrict__ lse_word, uint16_t* __restrict__ h_c,
+                   int32_t* __restrict__ target_c, float* __restrict__ lse_c,
+                   float* __restrict__ logp_c, float* __restrict__ coef_c, O* __restrict__ dh,
+                   int64_t ld_dh) {
     const int64_t n = count[0];
-    for (int64_t i = blockIdx.x; i < n; i += gridDim.x) {
+    for (int64_t i = blockIdx.x; i < T; i += gridDim.x) {
+        if (!row_counts(coef, lse_word, i))
+            for (int64_t c = threadIdx.x; c < d; c += 128) put(dh + i * ld_dh + c, 0.f);
+        if (i >= n) continue;
         const int64_t t = map[i];
         const u32x4* src = reinterpret_cast<const u32x4*>(h + t * ld_h);
         u32x4* dst = reinterpret_cast<u32x4*>(h_c + i * d);
-        for (int64_t j = threadIdx.x; j < d / 8; j += 64) dst[j] = src[j];
+        for (int64_t j = threadIdx.x; j < d / 8; j += 128) dst[j] = src[j];
         if (threadIdx.x == 0) {
             target_c[i] = target[t];
             lse_c[i] = lse[t];
             logp_c[i] = logp[t];
             coef_c[i] = coef[t];
         }
-    }
-}
-
-// An element of a gradient output: fp32, or bf16 bits rounded to nearest even.
-__device__ __forceinline__ void put(float* p, float v) { *p = v; }
-__device__ __forceinline__ void put(uint16_t* p, float v) { *p = bf16_bits(v); }
-
-// Rows [0, rows) of a row-major matrix set to 0 (columns [0, cols)).
-template <class O>
-__global__ void __launch_bounds__(256)
-zero_rows_kernel(O* __restrict__ m, int64_t rows, int64_t cols, int64_t ld) {
-    for (int64_t r = blockIdx.x; r < rows; r += gridDim.x)
-        for (int64_t c = threadIdx.x; c < cols; c += 256) put(m + r * ld + c, 0.f);
-}
-
-// dh[map[i]] = dh_c[i] for i < count (grid-stride over the rows).
-template <class O>
-__global__ void __launch_bounds__(256)
-scatter_rows_kernel(const int32_t* __restrict__ map, const int32_t* __restrict__ count,
-                    const float* __restrict__ dh_c, int64_t d, O* __restrict__ dh, int64_t ld_dh) {
-    const int64_t n = count[0];
-    for (int64_t i = blockIdx.x; i < n; i += gridDim.x) {
-        const int64_t t = map[i];
-        for (int64_t c = threadIdx.x; c < d; c += 256) put(dh + t * ld_dh + c, dh_c[i * d + c]);
     }
 }
 
@@ -1184,11 +1179,12 @@ to_bf16_kernel(const float* __restrict__ src, int64_t ld_src, int64_t rows, int6
 
 // The sum of the ksplit parts of dh (each [rows, d] fp32, part_stride elements
 // apart) in part order, for rows [0, rows), with dyn_rows those below
-// *dyn_rows - dyn_base: four columns a work-item.
+// *dyn_rows - dyn_base; row r goes to row r of out, or (map, its first entry
+// that of row 0) to row map[r]. Four columns a work-item.
 template <class O>
 __global__ void __launch_bounds__(256)
 sum_parts_kernel(const float* __restrict__ part, int64_t ksplit, int64_t part_stride, int64_t rows,
-                 int64_t d, O* __restrict__ out, int64_t ld_out,
+                 int64_t d, const int32_t* __restrict__ map, O* __restrict__ out, int64_t ld_out,
                  const int32_t* __restrict__ dyn_rows, int64_t dyn_base) {
     if (dyn_rows) {
         const int64_t live = (int64_t)*dyn_rows - dyn_base;
@@ -1201,7 +1197,7 @@ sum_parts_kernel(const float* __restrict__ part, int64_t ksplit, int64_t part_st
 #pragma unroll 8
     for (int64_t k = 1; k < ksplit; ++k) x += p[k * (part_stride / 4)];
     const int64_t r = i * 4 / d;
-    O* o = out + r * ld_out + (i * 4 - r * d);
+    O* o = out + (map ? (int64_t)map[r] : r) * ld_out + (i * 4 - r * d);
 #pragma unroll
     for (int q = 0; q < 4; ++q) put(o + q, x[q]);
 }
@@ -1381,10 +1377,26 @@ struct BackwardPlan {
     bool acc_h;          // dh summed over vocabulary blocks into bf16: through fp32
     size_t dz, accw, acch, h_c, dh_c, target_c, lse_c, logp_c, coef_c, map, count, total;
     // beyond total, used where the caller's workspace reaches split_total: dh's
-    // sum over the vocabulary in ksplit parts (1: no parts, split_total = total)
+    // sum over the vocabulary in ksplit parts (1: none), and room to leave out
+    // rows with zero dlogits without being told to (compact)
     int64_t ksplit;
+    bool compact;
     size_t parts, split_total;
 };
+
+// Whether a call that is not told to skip zero rows leaves them out all the
+// same, as the gradient pass on logits does: where that is worth the kernels
+// around it (7 - 10 us at d = 3584, against the share of zero rows of a backward
+// that takes at least 0.5 ms) and the compact rows fit 128 MiB. Few rows are
+// bound by W and dW, not by their number.
+// Measured at d = 3584, V = 152064, bf16 gradients: with 20% zero rows 2738 -> 2568
+// us at T = 1000 and 10107 -> 8629 at 4096, with 50% 2668 -> 1658 and 9830 -> 5626;
+// with none 2801 -> 2808 and 10322 -> 10331 (1585 -> 1592 at 512). Below the line,
+// at T = 1500, V = 14000, d = 1776 (3.7e10), leaving none out costs 3%.
+bool leaves_zero_rows_out(int64_t T, int64_t d, int64_t V) {
+    return T >= 256 && (double)T * (double)V * (double)d >= 1e11 &&
+           (double)T * (double)(6 * d + 20) <= double(128 << 20);
+}
 
 // Parts of a block's dh sum. dh has rows / 256 x d / 256 tiles, each a sum over
 // the block's whole vocabulary, and one launch holds them and dW's tiles, the
@@ -1426,7 +1438,7 @@ BackwardPlan plan_backward(int64_t T, int64_t d, int64_t V, int64_t chunk_rows,
     P.dz = take((size_t)P.rows * (size_t)ceil8(P.cols) * 2);
     if (P.acc_w) P.accw = take((size_t)V * (size_t)d * 4);
     if (P.acc_h) P.acch = take((size_t)T * (size_t)d * 4);
-    if (P.skip) {
+    auto take_rows = [&] {
         P.h_c = take((size_t)T * (size_t)d * 2);
         P.dh_c = take((size_t)T * (size_t)d * 4);
         P.target_c = take((size_t)T * 4);
@@ -1435,9 +1447,12 @@ BackwardPlan plan_backward(int64_t T, int64_t d, int64_t V, int64_t chunk_rows,
         P.coef_c = take((size_t)T * 4);
         P.map = take((size_t)T * 4);
         P.count = take(4);
-    }
+    };
+    if (P.skip) take_rows();
     P.total = end;
     P.ksplit = dh_parts(P.rows, d, P.cols);
+    P.compact = !P.skip && leaves_zero_rows_out(T, d, V);
+    if (P.compact) take_rows();
     if (P.ksplit > 1) P.parts = take((size_t)P.ksplit * (size_t)P.rows * (size_t)d * 4);
     P.split_total = end;
     return P;
@@ -1542,19 +1557,32 @@ void launch_to_bf16(const float* src, int64_t rows, int64_t cols, const Grad& ds
 // count is read on the device: blocks past it have nothing to do, and the
 // first row block writes dW even when it holds no rows). With parts (ksplit > 1),
 // a row block's dh is summed there, [ksplit][R, d], and added up once its last
-// vocabulary block is in.
+// vocabulary block is in. With map (and dyn_rows), the rows are compact ones and
+// row i of dh belongs at row map[i]: dh's sums stay in acc_h ([T, d]) or the parts
+// and are put there at the end.
 dart_status_t backward_core(const uint16_t* h, int64_t T, int64_t d,
                             int64_t ld_h, const uint16_t* w, int64_t V, int64_t ld_w,
                             const int32_t* target, const float* lse, const float* logp,
                             const float* coef, float scale, const Grad& dh, const Grad& dw,
                             int64_t R,
                             int64_t C, uint16_t* dz, float* acc_h, float* acc_w, float* parts,
-                            int64_t ksplit, hipStream_t stream,
+                            int64_t ksplit, hipStream_t stream, const int32_t* map = nullptr,
                             const int32_t* dyn_rows = nullptr) {
     if (R > T) R = T;
     if (C > V) C = V;
     const int64_t ld_dz = ceil8(C);
-    const bool via_h = dh.bf16 && C < V && !parts, via_w = dw.bf16 && R < T;
+    const bool via_h = !parts && (map || (dh.bf16 && C < V)), via_w = dw.bf16 && R < T;
+    auto sum_parts = [&](const float* p, int64_t n, int64_t stride, int64_t r0, int64_t rows) {
+        const dim3 grid((unsigned)((rows * d / 4 + 255) / 256));
+        const int32_t* m = map ? map + r0 : nullptr;
+        void* out = map ? dh.p : dh.row(r0);
+        if (dh.bf16)
+            hipLaunchKernelGGL(sum_parts_kernel<uint16_t>, grid, dim3(256), 0, stream, p, n, stride,
+                               rows, d, m, static_cast<uint16_t*>(out), dh.ld, dyn_rows, r0);
+        else
+            hipLaunchKernelGGL(sum_parts_kernel<float>, grid, dim3(256), 0, stream, p, n, stride,
+                               rows, d, m, static_cast<float*>(out), dh.ld, dyn_rows, r0);
+    };
     const Grad sum_h = via_h ? Grad{acc_h, d, false} : dh;
     const Grad sum_w = via_w ? Grad{acc_w, d, false} : dw;
     for (int64_t r0 = 0; r0 < T; r0 += R) {
@@ -1573,28 +1601,14 @@ dart_status_t backward_core(const uint16_t* h, int64_t T, int64_t d,
                 parts ? ksplit : 1, R * d, Grad{sum_w.row(c0), sum_w.ld, sum_w.bf16}, r0 > 0, stream, dyn_rows, r0);
             if (sg != DART_OK) return sg;
         }
-        if (parts) {
-            const dim3 grid((unsigned)((rows * d / 4 + 255) / 256));
-            if (dh.bf16)
-                hipLaunchKernelGGL(sum_parts_kernel<uint16_t>, grid, dim3(256), 0, stream, parts,
-                                   ksplit, R * d, rows, d, static_cast<uint16_t*>(dh.row(r0)),
-                                   dh.ld, dyn_rows, r0);
-            else
-                hipLaunchKernelGGL(sum_parts_kernel<float>, grid, dim3(256), 0, stream, parts,
-                                   ksplit, R * d, rows, d, static_cast<float*>(dh.row(r0)), dh.ld,
-                                   dyn_rows, r0);
-        }
+        if (parts) sum_parts(parts, ksplit, R * d, r0, rows);
     }
-    if (via_h) launch_to_bf16(acc_h, T, d, dh, stream);
+    if (via_h && map)
+        sum_parts(acc_h, 1, 0, 0, T);
+    else if (via_h)
+        launch_to_bf16(acc_h, T, d, dh, stream);
     if (via_w) launch_to_bf16(acc_w, V, d, dw, stream);
     return hipGetLastError() == hipSuccess ? DART_OK : DART_ERR_HIP;
-}
-
-template <class O>
-void launch_zero_rows(void* m, int64_t rows, int64_t cols, int64_t ld, hipStream_t stream) {
-    const unsigned blocks = (unsigned)(rows < kRowBlocks ? rows : kRowBlocks);
-    hipLaunchKernelGGL(zero_rows_kernel<O>, dim3(blocks), dim3(256), 0, stream,
-                       static_cast<O*>(m), rows, cols, ld);
 }
 
 }  // namespace
@@ -1652,7 +1666,7 @@ dart_status_t dart_lmhead_backward_ex(const void* hidden, int64_t T, int64_t d, 
     const bool split = P.ksplit > 1 && workspace_bytes >= P.split_total;
     float* parts = split ? reinterpret_cast<float*>(ws + P.parts) : nullptr;
     const Grad dh{dhidden, ld_dh, P.bf16}, dw{dweight, ld_dw, P.bf16};
-    if (!P.skip)
+    if (!P.skip && !(P.compact && workspace_bytes >= P.split_total))
         return backward_core(h, T, d, ld_h, w, V, ld_w, target, lse, logp, tok_coef, inv_temp, dh,
                              dw, P.rows, P.cols, dz, acc_h, acc_w, parts, P.ksplit, stream);
 
@@ -1666,30 +1680,22 @@ dart_status_t dart_lmhead_backward_ex(const void* hidden, int64_t T, int64_t d, 
     float* lse_c = reinterpret_cast<float*>(ws + P.lse_c);
     float* logp_c = reinterpret_cast<float*>(ws + P.logp_c);
     float* coef_c = reinterpret_cast<float*>(ws + P.coef_c);
+    const float* lse_word = P.skip ? nullptr : lse;
     hipLaunchKernelGGL(compact_rows_kernel, dim3(1), dim3(kCompactThreads), 0, stream, tok_coef,
-                       T, map, count);
-    const unsigned row_blocks = (unsigned)(T < kRowBlocks ? T : kRowBlocks);
-    hipLaunchKernelGGL(gather_rows_kernel, dim3(row_blocks), dim3(64), 0, stream, map, count, h,
-                       ld_h, d, target, lse, logp, tok_coef, h_c, target_c, lse_c, logp_c, coef_c);
+                       lse_word, T, map, count);
+    const dim3 row_blocks((unsigned)(T < kRowBlocks ? T : kRowBlocks));
     if (P.bf16)
-        launch_zero_rows<uint16_t>(dhidden, T, d, ld_dh, stream);
+        hipLaunchKernelGGL(gather_rows_kernel<uint16_t>, row_blocks, dim3(128), 0, stream, map,
+                           count, T, h, ld_h, d, target, lse, logp, tok_coef, lse_word, h_c,
+                           target_c, lse_c, logp_c, coef_c, static_cast<uint16_t*>(dhidden), ld_dh);
     else
-        launch_zero_rows<float>(dhidden, T, d, ld_dh, stream);
+        hipLaunchKernelGGL(gather_rows_kernel<float>, row_blocks, dim3(128), 0, stream, map, count,
+                           T, h, ld_h, d, target, lse, logp, tok_coef, lse_word, h_c, target_c,
+                           lse_c, logp_c, coef_c, static_cast<float*>(dhidden), ld_dh);
     if (hipGetLastError() != hipSuccess) return DART_ERR_HIP;
     // the kernels read the kept-row count on the device: T rows at most
-    const dart_status_t st =
-        backward_core(h_c, T, d, d, w, V, ld_w, target_c, lse_c, logp_c, coef_c, inv_temp,
-                      Grad{dh_c, d, false}, dw, P.rows, P.cols, dz, nullptr, acc_w, parts,
-                      P.ksplit, stream, count);
-    if (st != DART_OK) return st;
-    const unsigned nb = (unsigned)(T < kRowBlocks ? T : kRowBlocks);
-    if (P.bf16)
-        hipLaunchKernelGGL(scatter_rows_kernel<uint16_t>, dim3(nb), dim3(256), 0, stream, map,
-                           count, dh_c, d, static_cast<uint16_t*>(dhidden), ld_dh);
-    else
-        hipLaunchKernelGGL(scatter_rows_kernel<float>, dim3(nb), dim3(256), 0, stream, map, count,
-                           dh_c, d, static_cast<float*>(dhidden), ld_dh);
-    return hipGetLastError() == hipSuccess ? DART_OK : DART_ERR_HIP;
+    return backward_core(h_c, T, d, d, w, V, ld_w, target_c, lse_c, logp_c, coef_c, inv_temp, dh,
+                         dw, P.rows, P.cols, dz, dh_c, acc_w, parts, P.ksplit, stream, map, count);
 }
 
 dart_status_t dart_lmhead_backward(const void* hidden, int64_t T, int64_t d, int64_t ld_h,

@@ -313,3 +313,56 @@ def test_gradient_of_rows_with_a_zero_coefficient(V, shift, dtype):
     assert bool((dz[4] == 0).all()) and bool((dz[7] == 0).all())
     skipped = dart.dart_tis_grad(z, y, logp, bad, coef, skip_zero_rows=True)
     assert bool((skipped[zero].view(bits) == 0).all())
+
+
+@pytest.mark.parametrize("flags", [0, BF16])
+@pytest.mark.parametrize("rows,cols,kept", [(700, 143000, "some"), (700, 100000, "some"),
+                                            (512, 143000, "some"), (700, 143000, "none"),
+                                            (700, 143000, "nan")])
+def test_lmhead_backward_leaves_zero_rows_out(rows, cols, kept, flags):
+    """A large call without the skip flag leaves rows with a zero coefficient out
+    where its workspace has the room: against the exact products of the GPU's own
+    bf16 dlogits (64-bit, by torch), and against the call on a smaller workspace,
+    which forms every row; a zero row with a NaN in it still gives its NaNs."""
+    import torch
+
+    import paper_2509_23866_amd as dart
+
+    T, d, V = 700, 1024, 143000
+    g = torch.Generator(device="cuda").manual_seed(rows + cols)
+    h = torch.randn(T, d, generator=g, device="cuda").to(torch.bfloat16)
+    w = (torch.randn(V, d, generator=g, device="cuda") * 3 / d ** 0.5).to(torch.bfloat16)
+    y = torch.randint(V, (T,), generator=g, device="cuda", dtype=torch.int32)
+    coef = torch.randn(T, generator=g, device="cuda") * 1e-2
+    zero = torch.rand(T, generator=g, device="cuda") < 0.2
+    zero[100:260] = True
+    if kept == "none":
+        zero[:] = True
+    coef[zero] = 0.0
+    if kept == "nan":
+        h[150, 7] = float("nan")
+    logp, _, lse = dart.dart_lmhead_tok_stats(h, w, y)
+    need = dart.dart_lmhead_backward_ex_workspace_bytes(T, d, V, rows, cols, flags)
+    full = dart.dart_lmhead_backward_split_workspace_bytes(T, d, V, rows, cols, flags)
+    assert full >= need + T * (6 * d + 20)
+
+    def run(nbytes):
+        ws = torch.full((nbytes,), 0x7F, dtype=torch.uint8, device="cuda")
+        return dart.dart_lmhead_backward_ex(h, w, y, lse, logp, coef, chunk_rows=rows,
+                                            chunk_cols=cols, flags=flags, workspace=ws)
+
+    (dh, dw), (dh0, dw0) = run(full), run(need)
+    if kept == "nan":
+        for a, b in ((dh, dh0), (dw, dw0)):
+            assert torch.equal(a.isnan(), b.isnan()) and bool(a.isnan().any())
+        return
+    assert bool((dh[zero] == 0).all())
+    buf = torch.empty((T, V), dtype=torch.bfloat16, device="cuda")
+    dz = dart.dart_lmhead_dlogits(h, w, y, lse, logp, coef, dlogits=buf).double()
+    h64, w64 = h.double(), w.double()
+    A, U = 2.0 ** -13, 2.0 ** -8  # fp32 sums over |terms|; the bf16 output's rounding
+    for got, dense, ref, bound in ((dh, dh0, dz @ w64, dz.abs() @ w64.abs()),
+                                   (dw, dw0, dz.t() @ h64, dz.abs().t() @ h64.abs())):
+        tol = A * bound + (U * ref.abs() if flags & BF16 else 0)
+        assert bool(((got.double() - ref).abs() <= tol + 1e-30).all())
+        assert bool(((dense.double() - ref).abs() <= tol + 1e-30).all())
