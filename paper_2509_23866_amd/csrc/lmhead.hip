@@ -415,11 +415,12 @@ __device__ __forceinline__ void tile_to_lds_bf16(const f32x16 (&acc)[C::TM][C::T
 // slices of W in its L2. (Token tile fastest over all of them made each XCD
 // read a different h tile per workgroup: at T = 152569 that re-read the 1.09
 // GB of h from HBM once per vocabulary slice, 15% slower than groups of 4.)
+constexpr int64_t kTileGroup = 4;  // token tiles per group
 __device__ __forceinline__ void tile_of_block(int64_t nmt, int64_t nvt, int64_t& mt, int64_t& vt) {
     const int64_t nb = nmt * nvt, q = nb / 8, rr = nb % 8;
     const int64_t b = blockIdx.x, x = b % 8, sl = b / 8;
     const int64_t lg = x * q + min(x, rr) + sl;
-    constexpr int64_t G = 4;  // token tiles per group
+    constexpr int64_t G = kTileGroup;
     const int64_t g = lg / (G * nvt), first = g * G;
     const int64_t gm = nmt - first < G ? nmt - first : G;
     const int64_t in = lg - first * nvt;
@@ -427,18 +428,50 @@ __device__ __forceinline__ void tile_of_block(int64_t nmt, int64_t nvt, int64_t&
     vt = in / gm;
 }
 
+// The configuration of a last row tile of at most 128 rows where the others have
+// 256: the 128-row one, in the place the order gives it, among the tiles that read
+// the same slice of W. Only with 3 or 4 row tiles, one group of the order: with 2
+// it saves nothing, beyond 4 the last group's tiles are one XCD's, and the gain
+// is lost waiting for the others. Measured at d = 3584, V = 152064 (statistics,
+// us): 800 rows 945 -> 832, 600 rows 639 -> 616; put after all others, where they
+// read W from HBM once more, 600 rows 655.
+__host__ __device__ constexpr bool has_rest(int64_t nmt) { return nmt == 3 || nmt == 4; }
+template <class C>
+struct Rest {
+    using type = typename std::conditional<C::BM == LmCfg::BM, LmCfg128, C>::type;
+};
+// f(configuration, LDS, first row, vocabulary tile) for this workgroup's tile of M
+// rows x nvt vocabulary tiles, if it has one.
+template <class C, class F>
+__device__ __forceinline__ void with_row_tile(int64_t M, int64_t nvt, F&& f) {
+    using R = typename Rest<C>::type;
+    __shared__ union {
+        typename C::Smem full;
+        typename R::Smem rest;
+    } sm;
+    const int64_t nmt = (M + C::BM - 1) / C::BM;
+    if ((int64_t)blockIdx.x >= nmt * nvt) return;
+    int64_t mt, vt;
+    tile_of_block(nmt, nvt, mt, vt);
+    const int64_t m0 = mt * C::BM;
+    if constexpr (R::BM < C::BM) {
+        if (has_rest(nmt) && M - m0 <= R::BM) {
+            f(R{}, sm.rest, m0, vt);
+            return;
+        }
+    }
+    f(C{}, sm.full, m0, vt);
+}
+
 // part[t * nvt + vt] receives the triple of row t over the tile's columns
 // other than target[t]; the workgroup holding target[t] writes z_y[t].
 template <class C>
-__global__ void __launch_bounds__(C::THREADS)
-lmhead_stats_kernel(const uint16_t* __restrict__ h, int64_t T, int64_t ldh,
-                    const uint16_t* __restrict__ w, int64_t V, int64_t ldw, int64_t d,
-                    const int32_t* __restrict__ target, float scale, int64_t nmt, int64_t nvt,
-                    float4* __restrict__ part, float* __restrict__ z_y) {
-    __shared__ typename C::Smem sm;
-    int64_t mt, vt;
-    tile_of_block(nmt, nvt, mt, vt);
-    const int64_t m0 = mt * C::BM, n0 = vt * C::BN;
+__device__ __forceinline__ void lmhead_stats_tile(
+    const uint16_t* __restrict__ h, int64_t T, int64_t ldh, const uint16_t* __restrict__ w,
+    int64_t V, int64_t ldw, int64_t d, const int32_t* __restrict__ target, float scale,
+    int64_t nvt, float4* __restrict__ part, float* __restrict__ z_y, typename C::Smem& sm,
+    int64_t m0, int64_t vt) {
+    const int64_t n0 = vt * C::BN;
     f32x16 acc[C::TM][C::TN];
     gemm_tile<C>(h, T, ldh, w, V, ldw, d, m0, n0, sm, acc);
 
@@ -537,6 +570,18 @@ lmhead_stats_kernel(const uint16_t* __restrict__ h, int64_t T, int64_t ldh,
     }
 }
 
+template <class C>
+__global__ void __launch_bounds__(C::THREADS)
+lmhead_stats_kernel(const uint16_t* __restrict__ h, int64_t T, int64_t ldh,
+                    const uint16_t* __restrict__ w, int64_t V, int64_t ldw, int64_t d,
+                    const int32_t* __restrict__ target, float scale, int64_t nvt,
+                    float4* __restrict__ part, float* __restrict__ z_y) {
+    with_row_tile<C>(T, nvt, [&](auto cfg, auto& sm, int64_t m0, int64_t vt) {
+        lmhead_stats_tile<decltype(cfg)>(h, T, ldh, w, V, ldw, d, target, scale, nvt, part, z_y,
+                                         sm, m0, vt);
+    });
+}
+
 // dlogits = s g_t (onehot(y_t) - exp(s z - lse_t)) (s = scale, the inverse
 // temperature; lse_t that of s z) for rows [0, M) of the block
 // (h and out already offset to the block's first row) and the V vocabulary
@@ -545,28 +590,13 @@ lmhead_stats_kernel(const uint16_t* __restrict__ h, int64_t T, int64_t ldh,
 // path with the logits formed on the fly. The target element is
 // s g_t * -expm1(logp_t), accurate when p_y -> 1.
 template <class C>
-__global__ void __launch_bounds__(C::THREADS)
-lmhead_dlogits_kernel(const uint16_t* __restrict__ h, int64_t M, int64_t ldh,
-                      const uint16_t* __restrict__ w, int64_t V, int64_t ldw, int64_t d,
-                      const int32_t* __restrict__ target, const float* __restrict__ lse,
-                      const float* __restrict__ logp, const float* __restrict__ coef,
-                      float scale, uint16_t* __restrict__ out, int64_t ld_out, int64_t vbase,
-                      int64_t nmt, int64_t nvt, const int32_t* __restrict__ dyn_rows,
-                      int64_t dyn_base) {
-    __shared__ typename C::Smem sm;
-    // with dyn_rows, the block holds only rows below *dyn_rows - dyn_base (the
-    // grid covers the most it can hold): the tiles are laid over the live rows'
-    // tiles, so that they spread over every XCD, and the workgroups past them
-    // (the last ones dispatched) have nothing to do
-    if (dyn_rows) {
-        const int64_t live = (int64_t)*dyn_rows - dyn_base;
-        M = live < M ? (live > 0 ? live : 0) : M;
-        nmt = (M + C::BM - 1) / C::BM;
-        if ((int64_t)blockIdx.x >= nmt * nvt) return;
-    }
-    int64_t mt, vt;
-    tile_of_block(nmt, nvt, mt, vt);
-    const int64_t m0 = mt * C::BM, n0 = vt * C::BN;
+__device__ __forceinline__ void lmhead_dlogits_tile(
+    const uint16_t* __restrict__ h, int64_t M, int64_t ldh, const uint16_t* __restrict__ w,
+    int64_t V, int64_t ldw, int64_t d, const int32_t* __restrict__ target,
+    const float* __restrict__ lse, const float* __restrict__ logp, const float* __restrict__ coef,
+    float scale, uint16_t* __restrict__ out, int64_t ld_out, int64_t vbase, typename C::Smem& sm,
+    int64_t m0, int64_t vt) {
+    const int64_t n0 = vt * C::BN;
     f32x16 acc[C::TM][C::TN];
     gemm_tile<C>(h, M, ldh, w, V, ldw, d, m0, n0, sm, acc);
 
@@ -619,6 +649,28 @@ lmhead_dlogits_kernel(const uint16_t* __restrict__ h, int64_t M, int64_t ldh,
         else
             for (int q = 0; q < 8 && col0 + q < V; ++q) dst[q] = sm.c16[r][ch * 8 + q];
     }
+}
+
+// With dyn_rows, the block holds only rows below *dyn_rows - dyn_base (the grid
+// covers the most it can hold): the tiles are laid over the live rows' tiles,
+// so that they spread over every XCD, and the workgroups past them (the last
+// ones dispatched) have nothing to do.
+template <class C>
+__global__ void __launch_bounds__(C::THREADS)
+lmhead_dlogits_kernel(const uint16_t* __restrict__ h, int64_t M, int64_t ldh,
+                      const uint16_t* __restrict__ w, int64_t V, int64_t ldw, int64_t d,
+                      const int32_t* __restrict__ target, const float* __restrict__ lse,
+                      const float* __restrict__ logp, const float* __restrict__ coef,
+                      float scale, uint16_t* __restrict__ out, int64_t ld_out, int64_t vbase,
+                      int64_t nvt, const int32_t* __restrict__ dyn_rows, int64_t dyn_base) {
+    if (dyn_rows) {
+        const int64_t live = (int64_t)*dyn_rows - dyn_base;
+        M = live < M ? (live > 0 ? live : 0) : M;
+    }
+    with_row_tile<C>(M, nvt, [&](auto cfg, auto& sm, int64_t m0, int64_t vt) {
+        lmhead_dlogits_tile<decltype(cfg)>(h, M, ldh, w, V, ldw, d, target, lse, logp, coef, scale,
+                                           out, ld_out, vbase, sm, m0, vt);
+    });
 }
 
 // One wave per row: the row's nvt triples merged lane-strided in index order,
@@ -1213,19 +1265,23 @@ constexpr int64_t kMaxLd = int64_t(1) << 22;
 // workgroup runs per compute unit, so a launch takes its tiles in rounds of
 // kUnits, and a round of 256-, 128- or 64-row tiles takes 92, 54 or 45 us at
 // d = 3584 (T = 1000, 1000 and 256): the tile with the least rounds x time. So
-// 64 rows go as one 64-row tile, up to 128 and 129 - 384 as 128-row tiles at
-// V = 152064 (300 rows: 7 rounds of 128-row tiles against 5 of 256), more as
-// 256-row ones, unless those would leave units idle (1000 rows of V = 8000).
+// 64 rows go as one 64-row tile, up to 128 and 129 - 256 as 128-row tiles at
+// V = 152064, more as 256-row ones (the last one of up to 128 rows as in Rest),
+// unless those would leave units idle (1000 rows of V = 8000).
 constexpr int64_t kUnits = 256;
 int tile_rows(int64_t rows, int64_t V) {
-    const int64_t nvt = (V + LmCfg::BN - 1) / LmCfg::BN;
+    const double nvt = (double)((V + LmCfg::BN - 1) / LmCfg::BN), t256 = 92, t128 = 54, t64 = 45;
+    auto rounds = [](double tiles) { return ceil(tiles / kUnits); };
+    const int64_t nmt = (rows + 255) / 256, r = rows % 256;
+    double least = rounds((double)nmt * nvt) * t256;
+    // short tiles among the long ones take 71 us, and half a tile's wait at the end
+    if (has_rest(nmt) && r > 0 && r <= 128)
+        least = fmin(least, fmax(((double)(nmt - 1) * t256 + 71) * nvt / kUnits + 27, t256));
     int best = 256;
-    double least = 0;
-    for (const auto& [bm, t] : {std::pair<int, double>{256, 92}, {128, 54}, {64, 45}}) {
-        const int64_t tiles = (rows + bm - 1) / bm * nvt;
-        const double cost = (double)((tiles + kUnits - 1) / kUnits) * t;
-        if (bm == 256 || cost < least) best = bm, least = cost;
-    }
+    const double c128 = rounds((double)((rows + 127) / 128) * nvt) * t128;
+    const double c64 = rounds((double)((rows + 63) / 64) * nvt) * t64;
+    if (c128 < least) best = 128, least = c128;
+    if (c64 < least) best = 64;
     return best;
 }
 
@@ -1267,7 +1323,7 @@ dart_status_t launch_dlogits(const uint16_t* hidden, int64_t rows, int64_t d, in
         const int64_t nm = (rows + C::BM - 1) / C::BM;
         hipLaunchKernelGGL(lmhead_dlogits_kernel<C>, dim3((unsigned)(nm * nvt)), dim3(C::THREADS),
                            0, stream, hidden, rows, ld_h, weight, V, ld_w, d, target, lse, logp,
-                           coef, scale, out, ld_out, vbase, nm, nvt, dyn_rows, dyn_base);
+                           coef, scale, out, ld_out, vbase, nvt, dyn_rows, dyn_base);
     });
     return hipGetLastError() == hipSuccess ? DART_OK : DART_ERR_HIP;
 }
@@ -1308,8 +1364,8 @@ dart_status_t dart_lmhead_tok_stats_ex(const void* hidden, int64_t T, int64_t d,
         const int64_t nm = (T + C::BM - 1) / C::BM;
         hipLaunchKernelGGL(lmhead_stats_kernel<C>, dim3((unsigned)(nm * nvt)), dim3(C::THREADS), 0,
                            stream, static_cast<const uint16_t*>(hidden), T, ld_h,
-                           static_cast<const uint16_t*>(weight), V, ld_w, d, target, inv_temp, nm,
-                           nvt, part, z_y);
+                           static_cast<const uint16_t*>(weight), V, ld_w, d, target, inv_temp, nvt,
+                           part, z_y);
     });
     hipLaunchKernelGGL(lmhead_merge_kernel, dim3((unsigned)((T + kMergeWaves - 1) / kMergeWaves)),
                        dim3(kMergeWaves * 64), 0, stream, part, z_y, T, nvt, V, target, logp,

@@ -194,6 +194,8 @@ def test_lmhead_backward_dh_in_parts(T, d, V, rows, cols, parts, flags):
     (200, 200, 33000),    # 128-row tiles: 130 a row of tiles
     (256, 320, 40001),    # 128-row tiles, five slices
     (500, 72, 60000),     # 256-row tiles
+    (600, 72, 60000),     # 256-row tiles and a last 128-row one
+    (640, 136, 60000),    # the last one full
 ])
 def test_lmhead_tile_rows(T, d, V):
     """Every tile height: the statistics against the oracle, and dlogits bit for
