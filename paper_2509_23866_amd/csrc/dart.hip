@@ -17,7 +17,7 @@
 //                       (tis_coef_step_kernel: step-level ratios, one wave per step).
 //   tis_loss_finalize_kernel  adds the partial sums in a fixed order.
 //   select_coef_kernel  one workgroup: step_select_kernel's and tis_coef_kernel's
-//                       device code back to back (up to 4096 tokens), the
+//                       device code back to back (up to 4096 tokens and 80 steps), the
 //                       offsets and mask handed over in LDS.
 //   tis_grad_kernel     one workgroup per 4 KB chunk of a row; second streaming
 //                       pass writing coef * (onehot - softmax) in the logits dtype.
@@ -431,7 +431,12 @@ tok_stats_kernel(const void* __restrict__ logits, int64_t V, int64_t ld,
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
 constexpr int kSelLdsKeys = 8192;  // groups up to this many steps keep their keys in LDS
-constexpr int kSelLdsTokens = 16384;  // one group of up to this many tokens: means fused in
+constexpr int kSelLdsTokens = 16384;  // one group of up to this many tokens: means fused in,
+// up to this many steps: the one workgroup takes ~1 us for every 16 of them, as long
+// as a launch of step_mean_kernel at 48. Measured (fused against two launches, us):
+// 42 steps of 96 tokens 4.8 and 4.8, 62 of 96 6.5 and 5.9, 170 of 96 13.5 and 6.1,
+// 512 of 32 23.8 and 7.6
+constexpr int64_t kSelFusedMaxS = 48;
 constexpr int kSelRankMax = 256;   // groups up to this many steps are ranked directly
 
 // Wave sums of 64-bit values in the order of wave_reduce_f32: a value moves as two
@@ -528,14 +533,18 @@ __device__ __forceinline__ int64_t kept_steps_dev(int64_t n, double rho) {
 // highest mean entropy (step_H, from step_mean_kernel) among its own, equal
 // means lower step index first: by direct rank in small groups, else by a
 // radix select of the k-th key and a scan over the keys equal to it.
-// FUSED (one group, T <= kSelLdsTokens, S <= kSelLdsKeys): the workgroup first
+// FUSED (one group, T <= kSelLdsTokens, S <= kSelFusedSteps): the workgroup first
 // computes the step means itself, from the token entropies and offsets staged
 // in LDS, in the order of step_mean_kernel (so with bit-identical results),
 // and writes them to step_H.
-// LDS of the selection; with the means fused in, also the token entropies
-// and the clamped offsets (off_l[s] = first token of step s, off_l[S] = end)
+// LDS of the selection for groups of up to KEYS steps staged there; with the
+// means fused in, also the token entropies and the clamped offsets (off_l[s] =
+// first token of step s, off_l[S] = end)
+constexpr int kSelFusedSteps = 128;  // most steps of a fused launch
+static_assert(kSelFusedMaxS <= kSelFusedSteps, "steps of a fused selection");
+template <int KEYS>
 struct SelLds {
-    uint32_t keys[kSelLdsKeys];
+    uint32_t keys[KEYS];
     uint32_t hist[256];
     uint32_t sel_bin;
     int64_t sel_remaining;
@@ -548,7 +557,8 @@ __device__ __forceinline__ void select_steps(const float* __restrict__ H, int64_
                                              const int32_t* __restrict__ grp, double rho,
                                              int64_t k_all, float* __restrict__ step_H,
                                              uint8_t* __restrict__ mask,
-                                             int32_t* __restrict__ n_kept, SelLds& sl,
+                                             int32_t* __restrict__ n_kept,
+                                             SelLds<FUSED ? kSelFusedSteps : kSelLdsKeys>& sl,
                                              float* H_l, int32_t* off_l,
                                              uint8_t* mask_l = nullptr) {
     uint32_t* keys = sl.keys;
@@ -601,7 +611,7 @@ __device__ __forceinline__ void select_steps(const float* __restrict__ H, int64_
     }
 
     // the group's keys, read once (LDS when they fit)
-    const bool staged = Sg <= kSelLdsKeys;
+    const bool staged = FUSED || Sg <= kSelLdsKeys;
     if (staged && !FUSED) {
         for (int64_t i = tid; i < Sg; i += kSelThreads) keys[i] = float_key(step_H[gs + i]);
         __syncthreads();
@@ -610,18 +620,37 @@ __device__ __forceinline__ void select_steps(const float* __restrict__ H, int64_
         return staged ? keys[i] : float_key(step_H[gs + i]);
     };
 
-    if (Sg <= kSelRankMax) {
+    if (FUSED || Sg <= kSelRankMax) {
         // small group: the rank of each step among the group (higher key
-        // first, equal keys lower index first) decides directly
-        for (int64_t i = tid; i < Sg; i += kSelThreads) {
+        // first, equal keys lower index first) decides directly; beyond 64
+        // steps four work-items (of four waves) share a step's comparisons
+        // (one alone: 256 steps took 4 us longer than the radix select)
+        static_assert(kSelThreads == 4 * kSelRankMax, "four work-items a step");
+        const int n = (int)Sg, i = tid % kSelRankMax, way = tid / kSelRankMax;
+        auto rank_of = [&](auto ways) {
             const uint32_t ki = keys[i];
-            int64_t rank = 0;
-            for (int64_t j = 0; j < Sg; ++j) {
+            uint32_t r = 0;
+#pragma unroll 8
+            for (int j = ways.value > 1 ? way : 0; j < n; j += ways.value) {
                 const uint32_t kj = keys[j];
-                rank += (kj > ki || (kj == ki && j < i)) ? 1 : 0;
+                r += (kj > ki || (kj == ki && j < i)) ? 1 : 0;
             }
-            mask[gs + i] = rank < k ? 1 : 0;
-            if (mask_l) mask_l[gs + i] = rank < k ? 1 : 0;
+            return r;
+        };
+        uint32_t rank = 0;
+        if (n <= 64) {
+            if (tid < n) rank = rank_of(std::integral_constant<int, 1>{});
+        } else {
+            if (i < n) rank = rank_of(std::integral_constant<int, 4>{});
+            if (tid < n) hist[tid] = 0;
+            __syncthreads();
+            if (i < n) atomicAdd(&hist[i], rank);
+            __syncthreads();
+            if (tid < n) rank = hist[tid];
+        }
+        if (tid < n) {
+            mask[gs + tid] = (int64_t)rank < k ? 1 : 0;
+            if (mask_l) mask_l[gs + tid] = (int64_t)rank < k ? 1 : 0;
         }
         if (tid == 0 && n_kept) n_kept[blockIdx.x] = (int32_t)k;
         return;
@@ -710,10 +739,10 @@ step_select_kernel(const float* __restrict__ H, int64_t T, const int32_t* __rest
                    int64_t S, const int32_t* __restrict__ grp, double rho, int64_t k_all,
                    float* __restrict__ step_H, uint8_t* __restrict__ mask,
                    int32_t* __restrict__ n_kept) {
-    __shared__ SelLds sl;
+    __shared__ SelLds<FUSED ? kSelFusedSteps : kSelLdsKeys> sl;
     if constexpr (FUSED) {
         __shared__ float H_l[kSelLdsTokens];
-        __shared__ int32_t off_l[kSelLdsKeys + 1];
+        __shared__ int32_t off_l[kSelFusedSteps + 1];
         select_steps<true>(H, T, off, S, grp, rho, k_all, step_H, mask, n_kept, sl, H_l, off_l);
     } else {
         select_steps<false>(H, T, off, S, grp, rho, k_all, step_H, mask, n_kept, sl, nullptr,
@@ -835,11 +864,12 @@ constexpr int kCoefMaxBlocks = 1024;
 // MI355X: at T = 512 one workgroup saves ~2.5 us a step; at T = 4096 the
 // many-workgroup launch saves ~5 us.
 constexpr int64_t kCoefOneBlockMaxT = 2048;
-// up to this many tokens the selection and the loss run in one workgroup in
-// dart_select_tis_loss_fwd. Measured on MI355X (back to back, S = T / 64):
-// 11.0 vs 14.8 us for the two calls at T = 2048, 14.2 vs 16.6 at 4096, 21.0 vs
-// 17.7 at 6144, 44 vs 29 at 16384 (the one workgroup's arithmetic grows with T).
-constexpr int64_t kSelCoefMaxT = 4096;
+// up to this many tokens and steps the selection and the loss run in one workgroup
+// in dart_select_tis_loss_fwd (its arithmetic grows with T, its step means with
+// S). Measured on MI355X against the two calls (us): T = 2048, S = 64 13.0 and
+// 13.6; T = 4096, S = 42 12.5 and 13.7, S = 128 18.6 and 14.1; T = 3000, S = 93
+// 16.1 and 14.0; T = 6000, S = 62 15.2 and 14.5.
+constexpr int64_t kSelCoefMaxT = 4096, kSelCoefMaxS = 80;
 constexpr int kCoefLdsSteps = 8192;  // offsets and mask of up to this many steps go to LDS
 constexpr int kStepCoefThreads = 1024;
 constexpr int kStepCoefWaves = kStepCoefThreads / 64;
@@ -1172,7 +1202,7 @@ tis_coef_kernel(int64_t T, const float* __restrict__ logp, const float* __restri
 }
 
 // Step selection and token coefficients of one group in one workgroup (T <=
-// kSelCoefMaxT <= kSelLdsTokens, S <= kSelLdsKeys, token ratios, token mean
+// kSelCoefMaxT <= kSelLdsTokens, S <= kSelCoefMaxS, token ratios, token mean
 // over kept tokens): select_steps with the means fused in, then coef_tokens of the
 // one-workgroup launch, the two sharing the staged offsets. Its outputs are
 // those of step_select_kernel<true> followed by tis_coef_kernel<false,
@@ -1187,11 +1217,12 @@ select_coef_kernel(const float* __restrict__ H, int64_t T, const int32_t* __rest
                    float* __restrict__ stats, int nstats) {
     static_assert(kSelThreads == kCoefOneThreads, "one workgroup size for both parts");
     static_assert(kSelCoefMaxT <= kSelLdsTokens, "the entropies fit the selection's LDS");
-    static_assert(kSelLdsKeys <= kCoefLdsSteps, "the staged offsets serve both parts");
-    __shared__ SelLds sl;
-    __shared__ float H_l[kSelLdsTokens];
-    __shared__ int32_t off_l[kSelLdsKeys + 1];
-    __shared__ uint8_t mask_l[kCoefLdsSteps];
+    static_assert(kSelCoefMaxS <= kSelFusedSteps && kSelFusedSteps <= kCoefLdsSteps,
+                  "the staged offsets serve both parts");
+    __shared__ SelLds<kSelFusedSteps> sl;
+    __shared__ float H_l[kSelCoefMaxT];
+    __shared__ int32_t off_l[kSelFusedSteps + 1];
+    __shared__ uint8_t mask_l[kSelFusedSteps];
     __shared__ CoefRed<kCoefOneThreads> red;
     // the first chunk of tokens is in flight during the selection
     CoefTokens x;
@@ -1685,7 +1716,7 @@ dart_status_t dart_step_select(const float* entropy, int64_t T, const int32_t* s
             stream, {{dart_check::Item::Offsets, step_offsets, S, T}}); ck != DART_OK)
         return ck;
     if (!grid_fits((S + kSelWaves - 1) / kSelWaves, kSelThreads)) return DART_ERR_UNSUPPORTED;
-    if (T <= kSelLdsTokens && S <= kSelLdsKeys) {
+    if (T <= kSelLdsTokens && S <= kSelFusedMaxS) {
         hipLaunchKernelGGL(step_select_kernel<true>, dim3(1), dim3(kSelThreads), 0, stream,
                            entropy, T, step_offsets, S, nullptr, rho, k, step_entropy, step_mask,
                            n_kept_steps);
@@ -1826,7 +1857,7 @@ dart_status_t dart_select_tis_loss_fwd(int64_t T, const float* entropy, const fl
     if (k < 0) return DART_ERR_INVALID_ARG;
     if (!(eps_low >= 0.f) || !(eps_high >= 0.f) || !(C > 0.f)) return DART_ERR_INVALID_ARG;
     if (bad_workspace(workspace, workspace_bytes, T)) return DART_ERR_INVALID_ARG;
-    if (T > kSelCoefMaxT || S > kSelLdsKeys) {
+    if (T > kSelCoefMaxT || S > kSelCoefMaxS) {
         // beyond what one workgroup does faster: the two calls in turn
         const dart_status_t st = dart_step_select(entropy, T, step_offsets, S, rho, step_entropy,
                                                   step_mask, n_kept_steps, stream);

@@ -368,3 +368,34 @@ def test_lmhead_backward_leaves_zero_rows_out(rows, cols, kept, flags):
         tol = A * bound + (U * ref.abs() if flags & BF16 else 0)
         assert bool(((got.double() - ref).abs() <= tol + 1e-30).all())
         assert bool(((dense.double() - ref).abs() <= tol + 1e-30).all())
+
+
+@pytest.mark.parametrize("S", [1, 48, 49, 64, 65, 80, 81, 128, 256, 257])
+@pytest.mark.parametrize("rho", [0.3, 0.8])
+def test_selection_by_number_of_steps(S, rho):
+    """Step means and mask exactly the oracle's, ties between whole steps
+    included, on both sides of the one-launch, four-way-rank and direct-rank
+    limits; and the selection and loss in one call bit for bit the two calls'."""
+    import torch
+
+    import paper_2509_23866_amd as dart
+
+    rng = np.random.default_rng(S)
+    lens = rng.choice([1, 2, 7, 40], S)
+    T = int(lens.sum())
+    ent = rng.choice([0.0, 0.5, 1.25, 3.0], T).astype(np.float32)
+    off = np.r_[0, np.cumsum(lens)].astype(np.int32)
+    Hs, Hs32 = oracle.step_entropy(ent.astype(np.float64), off)
+    mask, k = oracle.step_mask(Hs32, rho)
+    sh, m, nk = dart.dart_step_select(_cuda(ent), _cuda(off), rho)
+    assert np.array_equal(sh.cpu().numpy().view(np.uint32) & 0x7FFFFFFF,
+                          Hs32.view(np.uint32) & 0x7FFFFFFF)
+    assert np.array_equal(m.cpu().numpy(), mask) and int(nk.item()) == k
+    logp, lp_old, lp_roll, _, adv, _, _ = _loss_inputs(rng, lens)
+    x = [_cuda(a) for a in (logp, lp_old, lp_roll, adv, off)]
+    got = dart.dart_select_tis_loss_fwd(_cuda(ent), *x, rho, 0.2, 0.28, 2.0)
+    loss, coef, stats = dart.dart_tis_loss_fwd(*x, m, 0.2, 0.28, 2.0)
+    assert torch.equal(got[0], sh) and torch.equal(got[1], m) and torch.equal(got[2], nk)
+    assert torch.equal(got[4].view(torch.int32), coef.view(torch.int32))
+    assert abs(got[3].item() - loss.item()) <= 1e-12 * max(abs(loss.item()), 1e-300)
+    assert torch.allclose(got[5], stats, rtol=1e-6, atol=0)
