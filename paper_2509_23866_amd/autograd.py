@@ -35,7 +35,7 @@ def _scaled(coef, grad):
     the gradient is 1)."""
     if grad.numel() != 1:
         raise ValueError("the DART loss is a scalar")
-    return coef * grad.reshape(()).to(torch.float32)
+    return coef * grad.reshape(())  # in float32: a 0-dim factor keeps the vector's type
 
 
 def _loss(logp, ent, logp_old, logp_rollout, adv, step_offsets, rho, eps_low, eps_high, C):
