@@ -399,3 +399,23 @@ def test_selection_by_number_of_steps(S, rho):
     assert torch.equal(got[4].view(torch.int32), coef.view(torch.int32))
     assert abs(got[3].item() - loss.item()) <= 1e-12 * max(abs(loss.item()), 1e-300)
     assert torch.allclose(got[5], stats, rtol=1e-6, atol=0)
+
+
+@pytest.mark.parametrize("V", [2048, 8000, 32003])
+def test_lse_close_to_its_rounding(V):
+    """lse lies in [8, 16) here, where float32 values are u = 2^-20 apart: its own
+    rounding is uniform, u / sqrt(12) = 2.75e-7 in the root mean square. What the
+    sums and the row's finish add is held to 2e-7, in quadrature 3.4e-7 in all
+    (a finish by one log2f of the whole sum reaches 3.5e-7 to 4.3e-7)."""
+    import torch
+
+    import paper_2509_23866_amd as dart
+
+    rng = np.random.default_rng(V)
+    T = 4096
+    z = _cuda((2.0 * rng.standard_normal((T, V), dtype=np.float32)))
+    y = _cuda(rng.integers(0, V, T).astype(np.int32))
+    lse = dart.dart_tok_stats(z, y)[2].double()
+    ref = torch.cat([torch.logsumexp(z[a:a + 512].double(), 1) for a in range(0, T, 512)])
+    assert 8 < float(ref.min()) and float(ref.max()) < 16
+    assert float((lse - ref).square().mean().sqrt()) < 3.4e-7
