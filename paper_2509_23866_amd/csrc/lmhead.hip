@@ -92,6 +92,9 @@ __device__ __forceinline__ __attribute__((address_space(3))) void* lds_ptr(void*
 template <int CH>
 __device__ __forceinline__ int swz(int r) { return (r / (16 / CH)) % CH; }
 
+// Columns of a row that the statistics reduce together, in every configuration.
+constexpr int kStatsUnit = 64;
+
 template <int BM_, int BN_, int WM_, int WN_, int NS_, int BK_ = 64>
 struct Cfg {
     static constexpr int BM = BM_, BN = BN_, BK = BK_, WM = WM_, WN = WN_, NS = NS_;
@@ -124,7 +127,7 @@ struct Cfg {
             } in;
             float c[EPI][CROW];
             uint16_t c16[BM][CROW16];
-            float4 red[WN][BM];  // per-row partial triples of the statistics
+            float4 red[BN / kStatsUnit][BM];  // per-row partial triples of the statistics
         };
     };
 };
@@ -166,16 +169,18 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, v);
 }
 
-// Exact merge of two partial triples; an empty triple has s == 0.
+// Exact merge of two partial triples; an empty triple has s == 0. Contracted by
+// hand alone, so that every kernel it is inlined into rounds the same.
 __device__ __forceinline__ Triple merge(const Triple& a, const Triple& b) {
+#pragma clang fp contract(off)
     if (b.s == 0.f) return a;
     if (a.s == 0.f) return b;
     const float m = fmaxf(a.m, b.m);
     const float ca = expf(a.m - m), cb = expf(b.m - m);
     Triple r;
     r.m = m;
-    r.s = ca * a.s + cb * b.s;
-    r.w = ca * fmaf(a.m - m, a.s, a.w) + cb * fmaf(b.m - m, b.s, b.w);
+    r.s = fmaf(ca, a.s, cb * b.s);
+    r.w = fmaf(ca, fmaf(a.m - m, a.s, a.w), cb * fmaf(b.m - m, b.s, b.w));
     return r;
 }
 
@@ -471,98 +476,111 @@ __device__ __forceinline__ void lmhead_stats_tile(
     int64_t V, int64_t ldw, int64_t d, const int32_t* __restrict__ target, float scale,
     int64_t nvt, float4* __restrict__ part, float* __restrict__ z_y, typename C::Smem& sm,
     int64_t m0, int64_t vt) {
+#pragma clang fp contract(off)  // the same roundings in every configuration
     const int64_t n0 = vt * C::BN;
     f32x16 acc[C::TM][C::TN];
     gemm_tile<C>(h, T, ldh, w, V, ldw, d, m0, n0, sm, acc);
 
-    // A lane's columns of one row: their maximum, then the sums in base-2 units
-    // against it, one partial sum per 32-column block; merged with the lane
-    // that holds the row's other columns of the wave, then across the WN waves
-    // of the row through LDS. The whole epilogue stays in registers until there.
+    // The row's 256 columns are reduced in units of 64, in whatever configuration:
+    // a lane's 32 columns of a unit (two 32-column blocks of its half-wave): their
+    // maximum, then the sums in base-2 units against it, one partial sum per
+    // block; merged with the lane that holds the unit's other columns; the four
+    // units merged in column order through LDS. So a row's triple does not depend
+    // on the tile height its call takes, or on the tile the row falls in: equal
+    // rows have equal statistics, and a step recomputed in another batch the same.
+    // (Reducing all of a wave's columns of a row at once, 64 or 128 by the
+    // configuration, is 0.3 to 0.7% faster: 3373 against 3384 us at T = 4096, 913
+    // against 922 at 1000, d = 3584, V = 152064.) The whole epilogue stays in
+    // registers until the last merge.
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5;
     const int wr = (wave / C::WN) * 32 + (lane & 31), wc = (wave % C::WN) * (C::BN / C::WN);
-    // columns below vlim (counted from the wave's first) exist
-    const int vlim = (int)min(V - n0 - wc, (int64_t)C::BN);
     // the inverse temperature enters the base-2 exponent's factor (1 at scale
     // 1: the same bits)
     const float c2 = scale * 1.4426950408889634f;
+    static_assert(C::TN % 2 == 0, "units of two 32-column blocks");
 #pragma unroll
     for (int i = 0; i < C::TM; ++i) {
         const int64_t t = m0 + wr + i * C::RS;
-        const int64_t yrel = (t < T ? (int64_t)target[t] : -1) - n0 - wc;
-        // the target's column within the wave's (-1: not here)
-        const int y32 = yrel >= 0 && yrel < min(vlim, C::BN / C::WN) ? (int)yrel : -1;
-        // only the tile's last columns past V and a row's target column drop
-        // out: the selects run only in lanes that hold such a column
-        const bool masked = vlim < C::BN / C::WN || (y32 >= 0 && ((y32 >> 2) & 1) == half);
-        if (masked) {
-            float zy = 0.f;
-            // opaque, so that the compiler does not take the comparisons of
-            // every row block's columns together, and spill their masks
-            int vl = vlim - half * 4, yl = y32 - half * 4;
-            asm volatile("" : "+v"(vl), "+v"(yl));
+        const int64_t y = t < T ? (int64_t)target[t] : -1;
 #pragma unroll
-            for (int j = 0; j < C::TN; ++j)
+        for (int u = 0; u < C::TN / 2; ++u) {
+            const int64_t u0 = n0 + wc + u * kStatsUnit;
+            // columns below vlim (counted from the unit's first) exist
+            const int vlim = (int)max(min(V - u0, (int64_t)kStatsUnit), (int64_t)0);
+            // the target's column within the unit's (-1: not here)
+            const int64_t yrel = y - u0;
+            const int y64 = yrel >= 0 && yrel < vlim ? (int)yrel : -1;
+            // only the tile's last columns past V and a row's target column drop
+            // out: the selects run only in lanes that hold such a column
+            const bool masked = vlim < kStatsUnit || (y64 >= 0 && ((y64 >> 2) & 1) == half);
+            if (masked) {
+                float zy = 0.f;
+                // opaque, so that the compiler does not take the comparisons of
+                // every row block's columns together, and spill their masks
+                int vl = vlim - half * 4, yl = y64 - half * 4;
+                asm volatile("" : "+v"(vl), "+v"(yl));
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int col = j * 32 + (v >> 2) * 8 + (v & 3);
-                    const bool at_y = col == yl;
-                    zy = at_y ? acc[i][j][v] : zy;
-                    acc[i][j][v] = col >= vl || at_y ? -INFINITY : acc[i][j][v];
-                }
-            if (y32 >= 0 && ((y32 >> 2) & 1) == half) z_y[t] = zy * scale;
-        }
-        float mx = -INFINITY;
-#pragma unroll
-        for (int j = 0; j < C::TN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) mx = fmaxf(mx, acc[i][j][v]);
-        // scale > 0: the maximum of the scaled row is the scaled maximum
-        Triple mine = {mx * scale, 0.f, 0.f};
-        if (mx > -INFINITY) {
-            // e = 2^xl with xl = (x - mx) scale log2(e); where a column was
-            // dropped (-inf) xl is floored at -200, where 2^xl is already 0 in
-            // fp32, so that it adds 0 (other columns are finite)
-            const float ml = mx * c2;
-            float s2[C::TN], w2[C::TN];
-            auto sums = [&](auto floored) {
-#pragma unroll
-                for (int j = 0; j < C::TN; ++j) {
-                    s2[j] = w2[j] = 0.f;
+                for (int j = 0; j < 2; ++j)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) {
-                        float xl = fmaf(acc[i][j][v], c2, -ml);
-                        if constexpr (decltype(floored)::value) xl = fmaxf(xl, -200.f);
-                        const float e = __builtin_amdgcn_exp2f(xl);
-                        s2[j] += e;
-                        w2[j] = fmaf(e, xl, w2[j]);
+                        const int col = j * 32 + (v >> 2) * 8 + (v & 3);
+                        const float x = acc[i][2 * u + j][v];
+                        const bool at_y = col == yl;
+                        zy = at_y ? x : zy;
+                        acc[i][2 * u + j][v] = col >= vl || at_y ? -INFINITY : x;
                     }
-                }
-            };
-            if (masked)
-                sums(std::true_type{});
-            else
-                sums(std::false_type{});
-#pragma unroll
-            for (int j = 0; j < C::TN; ++j) {
-                mine.s += s2[j];
-                mine.w += w2[j];
+                if (y64 >= 0 && ((y64 >> 2) & 1) == half) z_y[t] = zy * scale;
             }
-            mine.w *= 0.6931471805599453f;
+            float mx = -INFINITY;
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) mx = fmaxf(mx, acc[i][2 * u + j][v]);
+            // scale > 0: the maximum of the scaled row is the scaled maximum
+            Triple mine = {mx * scale, 0.f, 0.f};
+            if (mx > -INFINITY) {
+                // e = 2^xl with xl = (x - mx) scale log2(e); where a column was
+                // dropped (-inf) xl is floored at -200, where 2^xl is already 0 in
+                // fp32, so that it adds 0 (other columns are finite)
+                const float ml = mx * c2;
+                float s2[2], w2[2];
+                auto sums = [&](auto floored) {
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        s2[j] = w2[j] = 0.f;
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) {
+                            float xl = fmaf(acc[i][2 * u + j][v], c2, -ml);
+                            if constexpr (decltype(floored)::value) xl = fmaxf(xl, -200.f);
+                            const float e = __builtin_amdgcn_exp2f(xl);
+                            s2[j] += e;
+                            w2[j] = fmaf(e, xl, w2[j]);
+                        }
+                    }
+                };
+                if (masked)
+                    sums(std::true_type{});
+                else
+                    sums(std::false_type{});
+                mine.s = s2[0] + s2[1];
+                mine.w = (w2[0] + w2[1]) * 0.6931471805599453f;
+            }
+            Triple o;
+            o.m = __shfl_xor(mine.m, 32);
+            o.s = __shfl_xor(mine.s, 32);
+            o.w = __shfl_xor(mine.w, 32);
+            mine = half ? merge(o, mine) : merge(mine, o);
+            if (half == 0)
+                sm.red[wc / kStatsUnit + u][wr + i * C::RS] =
+                    make_float4(mine.m, mine.s, mine.w, 0.f);
         }
-        Triple o;
-        o.m = __shfl_xor(mine.m, 32);
-        o.s = __shfl_xor(mine.s, 32);
-        o.w = __shfl_xor(mine.w, 32);
-        mine = half ? merge(o, mine) : merge(mine, o);
-        if (half == 0) sm.red[wave % C::WN][wr + i * C::RS] = make_float4(mine.m, mine.s, mine.w, 0.f);
     }
     lds_ring_barrier();
     for (int r = tid; r < C::BM && m0 + r < T; r += C::THREADS) {
         Triple x = {-INFINITY, 0.f, 0.f};
 #pragma unroll
-        for (int k = 0; k < C::WN; ++k) {
+        for (int k = 0; k < C::BN / kStatsUnit; ++k) {
             const float4 q = sm.red[k][r];
             x = merge(x, Triple{q.x, q.y, q.z});
         }

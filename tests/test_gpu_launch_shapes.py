@@ -419,3 +419,34 @@ def test_lse_close_to_its_rounding(V):
     ref = torch.cat([torch.logsumexp(z[a:a + 512].double(), 1) for a in range(0, T, 512)])
     assert 8 < float(ref.min()) and float(ref.max()) < 16
     assert float((lse - ref).square().mean().sqrt()) < 3.4e-7
+
+
+def _same_bits(a, b):
+    import torch
+
+    return all(torch.equal(x.view(torch.int32), y.view(torch.int32)) for x, y in zip(a, b))
+
+
+@pytest.mark.parametrize("V", [60000, 59963])  # a last tile of 96 columns and of 59
+@pytest.mark.parametrize("inv_temp", [1.0, 1.3])
+def test_lmhead_statistics_of_equal_rows(V, inv_temp):
+    """Equal rows have the same bits wherever they stand, in the 256-row tiles or
+    the last short one of a call, and in calls of every tile height: 64 different
+    rows, repeated."""
+    import torch
+
+    import paper_2509_23866_amd as dart
+
+    d, n = 72, 64
+    g = torch.Generator(device="cuda").manual_seed(V)
+    h = torch.randn(n, d, generator=g, device="cuda").to(torch.bfloat16)
+    w = (torch.randn(V, d, generator=g, device="cuda") * 3 / d ** 0.5).to(torch.bfloat16)
+    y = torch.randint(V, (n,), generator=g, device="cuda", dtype=torch.int32)
+    y[:4] = torch.tensor([0, 63, 64, V - 1], dtype=torch.int32)
+    want = None
+    # 64- and 128-row tiles; 256-row ones; with a last tile of 88 rows; with a full one
+    for T in (64, 128, 500, 600, 640):
+        i = torch.arange(T, device="cuda") % n
+        got = dart.dart_lmhead_tok_stats_ex(h[i], w, y[i], inv_temp)
+        want = want or [x.clone() for x in got]
+        assert _same_bits(got, [x[i] for x in want]), T
