@@ -41,7 +41,8 @@
  *   are launched 2^22 at a time).
  * - Results are deterministic: no atomics on any floating-point result, fixed
  *   reduction orders; identical rows at identical alignment give bit-identical
- *   entropies.
+ *   entropies (and log-probs and normalisers), in one call or in calls of
+ *   different T.
  */
 #ifndef DART_H
 #define DART_H

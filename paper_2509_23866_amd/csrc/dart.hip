@@ -1496,7 +1496,7 @@ dart_status_t launch_status() {
     return hipGetLastError() == hipSuccess ? DART_OK : DART_ERR_HIP;
 }
 
-// Threads per row of the statistics pass for T rows of nvec vectors. A row is a
+// Threads per row of the statistics pass for rows of nvec vectors. A row is a
 // chain of loads, reduction and finish, so short rows want many small workgroups
 // on a compute unit and long ones enough loads in flight to need few iterations.
 // Measured (us; 768 threads as every row had before, then the choice, its
@@ -1505,12 +1505,14 @@ dart_status_t launch_status() {
 //   T 16000, V   8000 bf16 (1000)          147 -> 256: 44 [128: 45, 512: 54]
 //   T  6000, V  32003 bf16 (4000)           94 -> 512: 60 [256: 66, 768: 73]
 //   T  4096, V 152064 bf16 (19008)         183 -> 768: 183 [512: 187, 1024: 184]
-// Up to 256 rows each has a compute unit to itself and wants its width: T = 200, V
-// = 32000 fp32 (8000 vectors) 9.1 -> 768: 7.1 [512: 8.6].
-int stats_threads(int64_t T, int64_t nvec) {
+// The number of rows does not enter: the threads are the order of a row's sums, and
+// the same row has the same statistics in a call of any size. (Few rows have a compute
+// unit each and want its width, but not by much: T = 200, V = 32000 fp32, 8000
+// vectors, 7.9 -> 512: 5.8 [768: 5.6].)
+int stats_threads(int64_t nvec) {
     if (nvec <= 512) return 128;
     if (nvec <= 2048) return 256;
-    return nvec <= 8192 && T > 256 ? 512 : 768;
+    return nvec <= 8192 ? 512 : 768;
 }
 
 // f(dtype, non-temporal loads) as compile-time constants.
@@ -1704,7 +1706,7 @@ dart_status_t dart_tok_stats_ex(const void* logits, dart_dtype_t dtype, int64_t 
     if (const dart_status_t ck = dart_check::run(
             stream, {{dart_check::Item::Ids, target, T, V}}); ck != DART_OK)
         return ck;
-    switch (stats_threads(T, V / (int64_t)(16 / elem_size(dtype)))) {
+    switch (stats_threads(V / (int64_t)(16 / elem_size(dtype)))) {
         case 128: launch_tok_stats<128>(logits, dtype, T, V, ld, target, inv_temp, logp, entropy, lse, stream); break;
         case 256: launch_tok_stats<256>(logits, dtype, T, V, ld, target, inv_temp, logp, entropy, lse, stream); break;
         case 512: launch_tok_stats<512>(logits, dtype, T, V, ld, target, inv_temp, logp, entropy, lse, stream); break;

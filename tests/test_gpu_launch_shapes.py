@@ -450,3 +450,23 @@ def test_lmhead_statistics_of_equal_rows(V, inv_temp):
         got = dart.dart_lmhead_tok_stats_ex(h[i], w, y[i], inv_temp)
         want = want or [x.clone() for x in got]
         assert _same_bits(got, [x[i] for x in want]), T
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("vecs", [512, 2048, 2049, 8000, 8193])
+def test_token_statistics_do_not_depend_on_the_number_of_rows(vecs, dtype):
+    """A row has the same bits in a call of one row, of some hundred, and of more
+    logits than are loaded cacheably (64 MB)."""
+    import torch
+
+    import paper_2509_23866_amd as dart
+
+    per = 8 if dtype == "bf16" else 4
+    V, dt = vecs * per + 1, torch.bfloat16 if dtype == "bf16" else torch.float32
+    T = (64 << 20) // (vecs * 16) + 300
+    g = torch.Generator(device="cuda").manual_seed(vecs)
+    z = (torch.randn(T, V + per - 1, generator=g, device="cuda") * 3).to(dt)[:, :V]
+    y = torch.randint(V, (T,), generator=g, device="cuda", dtype=torch.int32)
+    want = [x[:300] for x in dart.dart_tok_stats(z, y)]
+    for n in (1, 100, 256, 257, 300):
+        assert _same_bits(dart.dart_tok_stats(z[:n], y[:n]), [x[:n] for x in want]), n
