@@ -1250,7 +1250,9 @@ to_bf16_kernel(const float* __restrict__ src, int64_t ld_src, int64_t rows, int6
 // The sum of the ksplit parts of dh (each [rows, d] fp32, part_stride elements
 // apart) in part order, for rows [0, rows), with dyn_rows those below
 // *dyn_rows - dyn_base; row r goes to row r of out, or (map, its first entry
-// that of row 0) to row map[r]. Four columns a work-item.
+// that of row 0) to row map[r]. Four columns a work-item at a time, grid-stride: all
+// T rows at once (the compact rows of one sum) are more than a dispatch holds from
+// T d = 2^34 on.
 template <class O>
 __global__ void __launch_bounds__(256)
 sum_parts_kernel(const float* __restrict__ part, int64_t ksplit, int64_t part_stride, int64_t rows,
@@ -1260,19 +1262,21 @@ sum_parts_kernel(const float* __restrict__ part, int64_t ksplit, int64_t part_st
         const int64_t live = (int64_t)*dyn_rows - dyn_base;
         rows = live < rows ? live : rows;
     }
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;  // d % 8 == 0
-    if (i * 4 >= rows * d) return;
-    const f32x4* p = reinterpret_cast<const f32x4*>(part) + i;
-    f32x4 x = p[0];
+    const int64_t step = (int64_t)gridDim.x * 256;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i * 4 < rows * d; i += step) {
+        const f32x4* p = reinterpret_cast<const f32x4*>(part) + i;  // d % 8 == 0
+        f32x4 x = p[0];
 #pragma unroll 8
-    for (int64_t k = 1; k < ksplit; ++k) x += p[k * (part_stride / 4)];
-    const int64_t r = i * 4 / d;
-    O* o = out + (map ? (int64_t)map[r] : r) * ld_out + (i * 4 - r * d);
+        for (int64_t k = 1; k < ksplit; ++k) x += p[k * (part_stride / 4)];
+        const int64_t r = i * 4 / d;
+        O* o = out + (map ? (int64_t)map[r] : r) * ld_out + (i * 4 - r * d);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) put(o + q, x[q]);
+        for (int q = 0; q < 4; ++q) put(o + q, x[q]);
+    }
 }
 
-// Workgroups of the row kernels above: one per row up to this many.
+// Workgroups of the row kernels above: one per row (of the sum of parts: per 1024
+// elements) up to this many.
 constexpr int64_t kRowBlocks = 65536;
 
 // The MFMA tile addresses its rows by 32-bit byte offsets from the tile's first
@@ -1647,7 +1651,8 @@ dart_status_t backward_core(const uint16_t* h, int64_t T, int64_t d,
     const int64_t ld_dz = ceil8(C);
     const bool via_h = !parts && (map || (dh.bf16 && C < V)), via_w = dw.bf16 && R < T;
     auto sum_parts = [&](const float* p, int64_t n, int64_t stride, int64_t r0, int64_t rows) {
-        const dim3 grid((unsigned)((rows * d / 4 + 255) / 256));
+        const int64_t blocks = (rows * d / 4 + 255) / 256;
+        const dim3 grid((unsigned)(blocks < kRowBlocks ? blocks : kRowBlocks));
         const int32_t* m = map ? map + r0 : nullptr;
         void* out = map ? dh.p : dh.row(r0);
         if (dh.bf16)

@@ -470,3 +470,28 @@ def test_token_statistics_do_not_depend_on_the_number_of_rows(vecs, dtype):
     want = [x[:300] for x in dart.dart_tok_stats(z, y)]
     for n in (1, 100, 256, 257, 300):
         assert _same_bits(dart.dart_tok_stats(z[:n], y[:n]), [x[:n] for x in want]), n
+
+
+@pytest.mark.parametrize("flags", [SKIP, SKIP | BF16])
+def test_lmhead_backward_puts_back_more_rows_than_one_sweep(flags):
+    """Skipped rows: the kept rows' dhidden, more than the 65,536 workgroups of one
+    sweep put back, bit for bit those of the dense call (the sums over one short
+    vocabulary block run in the same order)."""
+    import torch
+
+    import paper_2509_23866_amd as dart
+
+    T, d, V = 9000, 8192, 40
+    g = torch.Generator(device="cuda").manual_seed(3)
+    h = torch.randn(T, d, generator=g, device="cuda").to(torch.bfloat16)
+    w = (torch.randn(V, d, generator=g, device="cuda") * 3 / d ** 0.5).to(torch.bfloat16)
+    y = torch.randint(V, (T,), generator=g, device="cuda", dtype=torch.int32)
+    coef = torch.randn(T, generator=g, device="cuda") * 1e-2
+    coef[torch.rand(T, generator=g, device="cuda") < 0.05] = 0.0
+    logp, _, lse = dart.dart_lmhead_tok_stats(h, w, y)
+    run = lambda f: dart.dart_lmhead_backward_ex(h, w, y, lse, logp, coef, chunk_rows=T,  # noqa: E731
+                                                 chunk_cols=V, flags=f)[0]
+    got, dense = run(flags), run(flags & BF16)
+    kept = coef != 0
+    assert int(kept.sum()) * d > 65536 * 1024
+    assert torch.equal(got[kept], dense[kept]) and bool((got[~kept] == 0).all())
