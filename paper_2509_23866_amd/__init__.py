@@ -75,6 +75,10 @@ def load_library():
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(f"{LIB_PATH} is not built; run __graft_entry__.build()")
+        try:
+            _torch()  # its HIP runtime first: libdart.so alone would bring another
+        except ImportError:
+            pass  # the host helpers do without
         lib = ctypes.CDLL(LIB_PATH)
         lib.dart_tok_stats.restype = ctypes.c_int
         lib.dart_tok_stats.argtypes = [_P, ctypes.c_int, _I64, _I64, _I64, _P, _P, _P, _P, _P]
@@ -163,7 +167,6 @@ def _nat():
     global _native
     if _native is None:
         load_library()
-        _torch()
         try:
             native = importlib.import_module("._native", __name__)
         except ImportError as e:
