@@ -5,7 +5,8 @@ Argument marshalling only: every step of the path runs in the HIP kernels of
 be built (``__graft_entry__.build()``); if it is missing, importing a function
 raises — there is no CPU fallback. Calls whose arguments are plain tensors, with
 the outputs left to the call and on the current stream, are marshalled natively
-(``csrc/binding.cpp``); all others, and every complaint about an argument, here.
+(``csrc/binding.cpp``, where it is built); all others, and every complaint about an
+argument, here.
 
 Functions carry the C names: ``dart_tok_stats``, ``dart_step_select``,
 ``dart_tis_loss_fwd_bwd`` (and its halves ``dart_tis_loss_fwd`` /
@@ -20,6 +21,7 @@ from __future__ import annotations
 import ctypes
 import importlib
 import os
+import warnings
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libdart.so")
@@ -162,16 +164,30 @@ def load_library():
 _native = None
 
 
-def _nat():
-    """The native marshalling (raises if it is not built)."""
+class _NoNative:
+    """Stands for the native marshalling where it is not built: takes no call."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _nat(required=False):
+    """The native marshalling. Without it (only libdart.so is built, or _native.so
+    was built against another torch) every call is marshalled in Python, which is
+    said once; with ``required`` that raises."""
     global _native
-    if _native is None:
+    if _native is None or required and isinstance(_native, _NoNative):
         load_library()
         try:
             native = importlib.import_module("._native", __name__)
         except ImportError as e:
-            raise RuntimeError("_native.so is not built; run __graft_entry__.build()") from e
-        native.open(LIB_PATH)
+            if required:
+                raise RuntimeError("_native.so is not built; run __graft_entry__.build()") from e
+            warnings.warn(f"calls are marshalled in Python (an update: 46 us of host time in place "
+                          f"of 19): {e}; run __graft_entry__.build()", RuntimeWarning, stacklevel=3)
+            native = _NoNative()
+        else:
+            native.open(LIB_PATH)
         _native = native
     return _native
 
