@@ -1,12 +1,40 @@
 """The binding's two host paths: a call that leaves its outputs to the library
-(marshalled natively) gives the bits of the same call with its outputs given
+(marshalled natively) gives the bits of the same call with its stream given
 (marshalled in Python), and arguments that the native path does not take end
-where they ended before: converted, or refused with the same exception."""
+where they ended before: converted, or refused with the same exception. Which path
+a call took is read off the native functions, which return None for what they do
+not take."""
 
 import numpy as np
 import pytest
 
 pytestmark = pytest.mark.gpu
+
+
+class _Recorder:
+    """The native functions, noting of each call whether it was taken."""
+
+    def __init__(self, native):
+        self.native, self.taken = native, []
+
+    def __getattr__(self, name):
+        f = getattr(self.native, name)
+
+        def call(*args):
+            out = f(*args)
+            self.taken.append(out is not None)
+            return out
+
+        return call
+
+
+@pytest.fixture
+def native(monkeypatch):
+    import paper_2509_23866_amd as dart
+
+    rec = _Recorder(dart._nat(required=True))
+    monkeypatch.setattr(dart, "_native", rec)
+    return rec
 
 
 def _case(T=300, V=1003, dtype="bf16"):
@@ -66,23 +94,60 @@ def _calls(c):
     }
 
 
-@pytest.mark.parametrize("dtype", ["bf16", "f32"])
-def test_native_and_python_calls_agree(dtype):
+def _equal(a, b, name):
     import torch
 
-    for name, (native, python) in _calls(_case(dtype=dtype)).items():
-        a, b = native(), python()
+    assert len(a) == len(b), name
+    for x, y in zip(a, b):
+        assert (x is None) == (y is None), name
+        if x is not None:
+            assert x.dtype == y.dtype and x.shape == y.shape and x.device == y.device, name
+            raw = lambda t: t.contiguous().view(torch.uint8)  # noqa: E731
+            assert torch.equal(raw(x), raw(y)), name
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_native_and_python_calls_agree(dtype, native):
+    import torch
+
+    for name, (ordinary, python) in _calls(_case(dtype=dtype)).items():
+        native.taken.clear()
+        a = ordinary()
+        # T read from the device is the Python path's
+        assert native.taken == ["from the device" not in name], name
+        native.taken.clear()
+        b = python()
+        assert native.taken == [], name
         torch.cuda.synchronize()
-        assert len(a) == len(b), name
-        for x, y in zip(a, b):
-            assert (x is None) == (y is None), name
+        _equal(a, b, name)
+
+
+def test_native_calls_run_on_the_current_stream(native):
+    """Captured into a graph: a replay computes what it finds in the inputs, so every
+    launch went to the capturing stream."""
+    import torch
+
+    c = _case()
+    s = torch.cuda.Stream()
+    for name, (ordinary, python) in _calls(c).items():
+        if "from the device" in name:  # reads back: not for a capture
+            continue
+        ordinary()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        native.taken.clear()
+        with torch.cuda.graph(graph, stream=s):
+            a = ordinary()
+        assert native.taken == [True], name
+        for x in a:
             if x is not None:
-                assert x.dtype == y.dtype and x.shape == y.shape and x.device == y.device, name
-                raw = lambda t: t.contiguous().view(torch.uint8)  # noqa: E731
-                assert torch.equal(raw(x), raw(y)), name
+                x.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        _equal(a, python(), name)
 
 
-def test_gradient_into_a_given_tensor():
+def test_gradient_into_a_given_tensor(native):
     import torch
 
     import paper_2509_23866_amd as dart
@@ -97,9 +162,10 @@ def test_gradient_into_a_given_tensor():
     own = c["z"].clone()
     dz = dart.dart_tis_grad(own, c["y"], out["logp"], out["lse"], out["tok_coef"], dlogits=own)
     assert dz is own and torch.equal(own, buf)
+    assert native.taken == [True] * 3
 
 
-def test_what_the_native_path_does_not_take():
+def test_what_the_native_path_does_not_take(native):
     """Numbers of other types are converted; wrong types, shapes, devices and
     layouts raise what they raised, and a failing C call names itself."""
     import torch
@@ -109,6 +175,9 @@ def test_what_the_native_path_does_not_take():
     c = _case()
     z, y = c["z"], c["y"]
     want = dart.dart_tok_stats(z, y, inv_temp=1.5)
+    plain = dart.dart_tok_stats(z, y)
+    assert native.taken == [True, True]
+    native.taken.clear()
     for it in (np.float32(1.5), torch.tensor(1.5)):
         for a, b in zip(dart.dart_tok_stats(z, y, inv_temp=it), want):
             assert torch.equal(a, b)
@@ -116,14 +185,14 @@ def test_what_the_native_path_does_not_take():
     class Sub(torch.Tensor):
         pass
 
-    assert torch.equal(dart.dart_tok_stats(z.as_subclass(Sub), y)[0],
-                       dart.dart_tok_stats(z, y)[0])
+    assert torch.equal(dart.dart_tok_stats(z.as_subclass(Sub), y)[0], plain[0])
     for bad, exc in (((z, y.long()), ValueError), ((z, y[:-1]), ValueError),
                      ((z, y.cpu()), ValueError), ((z.half(), y), TypeError),
                      ((z.t(), y), ValueError), ((z, [0] * 300), TypeError),
                      ((z.cpu(), y.cpu()), ValueError)):
         with pytest.raises(exc):
             dart.dart_tok_stats(*bad)
+    assert native.taken and not any(native.taken)
     for it in (0.0, -1.0, float("nan"), float("inf")):
         with pytest.raises(dart.DartError, match="dart_tok_stats_ex"):
             dart.dart_tok_stats(z, y, inv_temp=it)
