@@ -316,7 +316,7 @@ def objective_variant(wl, dev, stream, logits, target, off, adv, lp_old, lp_roll
     mask = torch.empty(S, dtype=torch.uint8, device=dev)
     nk = torch.empty(1, dtype=torch.int32, device=dev)
     loss = torch.empty(1, dtype=torch.float64, device=dev)
-    ws = torch.empty(dart.dart_tis_loss_workspace_bytes(T), dtype=torch.uint8, device=dev)
+    ws = torch.empty(dart.dart_tis_loss_split_workspace_bytes(T), dtype=torch.uint8, device=dev)
     inv_temp = 1.25
     dart.dart_tok_stats(logits, target, logp, ent, lse, stream=stream, inv_temp=inv_temp)
     torch.cuda.synchronize(dev)

@@ -153,6 +153,13 @@ dart_status_t dart_tis_loss_fwd_bwd(const void* logits, dart_dtype_t dtype, int6
  * T < 1 or T > INT32_MAX). Host only. */
 size_t dart_tis_loss_workspace_bytes(int64_t T);
 
+/* Bytes of workspace with which every loss call is fastest: twice the value above
+ * (0 for T < 1 or T > INT32_MAX). The second half takes the partial sums of the
+ * two cases that leave a smaller workspace untouched and run on one workgroup
+ * there: step-level ratios of more than 32 steps (dart_tis_loss_fwd_ex), and the
+ * loss of dart_select_tis_loss_fwd with T <= 4096 and 80 < S <= 8192. Host only. */
+size_t dart_tis_loss_split_workspace_bytes(int64_t T);
+
 /* dart_tis_loss_fwd_bwd for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): the same computation, checks, kernels and results, bit for bit,
@@ -213,7 +220,8 @@ dart_status_t dart_tis_grad(const void* logits, dart_dtype_t dtype, int64_t T, i
  *              logp, logp_old, logp_rollout, adv, eps_low, eps_high, C, loss,
  *              tok_coef, stats, workspace, workspace_bytes as for
  *              dart_tis_loss_fwd. The workspace is used only when the problem
- *              is too large for one workgroup.
+ *              is too large for one workgroup: T > 4096, S > 8192, or S > 80
+ *              with a workspace of dart_tis_loss_split_workspace_bytes(T).
  *   Results:   step_entropy, step_mask, n_kept_steps and tok_coef equal those
  *              of the two calls bit for bit; loss and stats are the same sums
  *              in float64 in the one-workgroup order (the two calls with a
@@ -289,9 +297,9 @@ dart_status_t dart_tok_stats_ex(const void* logits, dart_dtype_t dtype, int64_t 
  * required when config->kl != DART_KL_NONE, else ignored (may be NULL).
  * stats: [6] float32 or NULL: clip fraction, mean TIS weight, fraction at the
  * cap, N, mean KL, K (over kept tokens / steps). Other arguments and errors as
- * dart_tis_loss_fwd (step-level ratios of up to 32 steps leave the workspace
- * unused); also INVALID_ARG for a null config, an unknown enum value,
- * or beta < 0 / non-finite. */
+ * dart_tis_loss_fwd (step-level ratios leave the workspace unused, unless it has
+ * dart_tis_loss_split_workspace_bytes(T) and there are more than 32 steps); also
+ * INVALID_ARG for a null config, an unknown enum value, or beta < 0 / non-finite. */
 dart_status_t dart_tis_loss_fwd_ex(int64_t T, const float* logp, const float* logp_old,
                                    const float* logp_rollout, const float* logp_ref,
                                    const float* adv, const int32_t* step_offsets, int64_t S,

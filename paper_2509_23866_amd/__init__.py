@@ -44,6 +44,7 @@ EXPORTED = ("dart_tok_stats", "dart_step_select", "dart_tis_loss_fwd_bwd", "dart
             "dart_tis_grad", "dart_tis_loss_fwd_bwd_noalloc", "dart_select_tis_loss_fwd",
             "dart_tok_stats_ex", "dart_tis_loss_fwd_ex", "dart_tis_grad_ex",
             "dart_grpo_advantage", "dart_step_select_groups", "dart_tis_loss_workspace_bytes",
+            "dart_tis_loss_split_workspace_bytes",
             "dart_lmhead_tok_stats", "dart_lmhead_tok_stats_ex", "dart_lmhead_stats_workspace_bytes",
             "dart_lmhead_dlogits", "dart_lmhead_dlogits_ex",
             "dart_lmhead_backward", "dart_lmhead_backward_workspace_bytes",
@@ -105,6 +106,8 @@ def load_library():
             ctypes.c_float, _P, _P, _P, _P, _P, _P, _P, ctypes.c_size_t, _P]
         lib.dart_tis_loss_workspace_bytes.restype = ctypes.c_size_t
         lib.dart_tis_loss_workspace_bytes.argtypes = [_I64]
+        lib.dart_tis_loss_split_workspace_bytes.restype = ctypes.c_size_t
+        lib.dart_tis_loss_split_workspace_bytes.argtypes = [_I64]
         lib.dart_tis_grad.restype = ctypes.c_int
         lib.dart_tis_grad.argtypes = [_P, ctypes.c_int, _I64, _I64, _I64, _P, _P, _P, _P, _P,
                                       _I64, _P]
@@ -235,6 +238,10 @@ def dart_tis_loss_workspace_bytes(T: int) -> int:
     return int(load_library().dart_tis_loss_workspace_bytes(int(T)))
 
 
+def dart_tis_loss_split_workspace_bytes(T: int) -> int:
+    return int(load_library().dart_tis_loss_split_workspace_bytes(int(T)))
+
+
 def _workspace(workspace, T, device, stream):
     """(pointer, bytes, tensor) for the loss workspace: "auto" allocates one
     from torch's caching allocator (kept for the stream the call runs on),
@@ -245,7 +252,8 @@ def _workspace(workspace, T, device, stream):
     if isinstance(workspace, str):
         if workspace != "auto":
             raise ValueError('workspace must be "auto", None or a uint8 device tensor')
-        workspace = torch.empty(dart_tis_loss_workspace_bytes(T), dtype=torch.uint8, device=device)
+        workspace = torch.empty(dart_tis_loss_split_workspace_bytes(T), dtype=torch.uint8,
+                                device=device)
         if isinstance(stream, torch.cuda.Stream):
             workspace.record_stream(stream)
     if (not isinstance(workspace, torch.Tensor) or workspace.dtype != torch.uint8
@@ -340,7 +348,8 @@ def dart_tis_loss_fwd_bwd(logits, target, logp, lse, logp_old, logp_rollout, adv
     for the in-place gradient), per-token coefficient (float32 [T]) and stats
     (float32 [4]: clip fraction, mean TIS weight, capped fraction, N).
     ``workspace``: "auto" (allocated here), None (one-workgroup loss, no
-    workspace) or a uint8 device tensor of dart_tis_loss_workspace_bytes(T)."""
+    workspace) or a uint8 device tensor of dart_tis_loss_workspace_bytes(T), or of
+    dart_tis_loss_split_workspace_bytes(T), as "auto" allocates."""
     torch = _torch()
     dt, T, V, ld = _logits_meta(logits)
     dev = logits.device

@@ -26,7 +26,7 @@ namespace {
     F(dart_tis_grad) F(dart_tis_grad_ex) F(dart_grpo_advantage)                  \
     F(dart_step_select_groups) F(dart_tis_loss_fwd_ex)                           \
     F(dart_lmhead_tok_stats) F(dart_lmhead_tok_stats_ex)                         \
-    F(dart_tis_loss_workspace_bytes) F(dart_lmhead_stats_workspace_bytes)
+    F(dart_tis_loss_split_workspace_bytes) F(dart_lmhead_stats_workspace_bytes)
 
 struct Lib {
 #define DECLARE(name) decltype(&::name) name = nullptr;
@@ -174,7 +174,7 @@ struct SelectLoss {
         n_kept = empty({1}, at::kInt, dev), loss = empty({1}, at::kDouble, dev);
         coef = empty({T}, at::kFloat, dev);
         if (with_stats) stats = empty({4}, at::kFloat, dev);
-        const size_t bytes = lib.dart_tis_loss_workspace_bytes(T);
+        const size_t bytes = lib.dart_tis_loss_split_workspace_bytes(T);
         workspace = empty({(int64_t)bytes}, at::kByte, dev);
         return call([&] {
             return lib.dart_select_tis_loss_fwd(
@@ -374,7 +374,7 @@ NATIVE(tis_loss_fwd_ex, 15)
     const Tensor loss = empty({1}, at::kDouble, dev), coef = empty({T}, at::kFloat, dev);
     Tensor stats;
     if (a[14] == Py_True) stats = empty({6}, at::kFloat, dev);
-    const size_t bytes = lib.dart_tis_loss_workspace_bytes(T);
+    const size_t bytes = lib.dart_tis_loss_split_workspace_bytes(T);
     const Tensor ws = empty({(int64_t)bytes}, at::kByte, dev);
     const hipStream_t s = stream_of(dev);
     const dart_status_t st = call([&] {

@@ -1547,20 +1547,30 @@ void launch_tok_stats(const void* logits, dart_dtype_t dtype, int64_t T, int64_t
     }
 }
 
+// The second half of a loss workspace of the split size, null where it is smaller.
+// Step ratios and small fused selections leave their partial sums there: the first
+// half is untouched by them, so that a caller may share it with them unordered.
+double* spare_part(void* workspace, size_t bytes, int64_t T) {
+    const size_t half = dart_tis_loss_workspace_bytes(T);
+    return workspace && bytes >= 2 * half
+               ? reinterpret_cast<double*>(static_cast<char*>(workspace) + half)
+               : nullptr;
+}
+
 // K3 and the loss reduction for one configuration: up to kCoefMaxBlocks
-// workgroups plus the finalize kernel when a workspace is given and T >
-// kCoefOneBlockMaxT (token ratios) or S > kStepCoefOneBlockMaxS (step ratios),
-// else one workgroup.
+// workgroups plus the finalize kernel when a workspace (step ratios: a spare part) is
+// given and T > kCoefOneBlockMaxT (token ratios) or S > kStepCoefOneBlockMaxS (step
+// ratios), else one workgroup.
 dart_status_t launch_tis_coef(bool general, int64_t T, const float* logp, const float* lp_old,
                               const float* lp_roll, const float* lp_ref, const float* adv,
                               const int32_t* off, int64_t S, const uint8_t* mask,
                               const LossConfig& cfg, float* coef, double* loss, float* stats,
-                              int nstats, void* workspace, hipStream_t stream) {
+                              int nstats, void* workspace, double* spare, hipStream_t stream) {
     if (general && cfg.ratio != DART_RATIO_TOKEN) {
-        // never more workgroups than the workspace has room for
+        // never more workgroups than the spare part has room for
         const int64_t want = (S + kStepCoefWaves - 1) / kStepCoefWaves, room = coef_blocks(T);
-        const int64_t nb = !workspace || S <= kStepCoefOneBlockMaxS ? 1 : want < room ? want : room;
-        double* part = nb > 1 ? static_cast<double*>(workspace) : nullptr;
+        const int64_t nb = !spare || S <= kStepCoefOneBlockMaxS ? 1 : want < room ? want : room;
+        double* part = nb > 1 ? spare : nullptr;
         hipLaunchKernelGGL(tis_coef_step_kernel, dim3((unsigned)nb), dim3(kStepCoefThreads), 0,
                            stream, T, logp, lp_old, lp_roll, lp_ref, adv, off, S, mask, cfg, coef,
                            part, loss, stats, nstats);
@@ -1693,6 +1703,10 @@ int64_t dart_kept_steps(int64_t S, double rho) {
 size_t dart_tis_loss_workspace_bytes(int64_t T) {
     if (T < 1 || T > 0x7FFFFFFFll) return 0;
     return (size_t)coef_workspace_doubles(coef_blocks(T)) * sizeof(double);
+}
+
+size_t dart_tis_loss_split_workspace_bytes(int64_t T) {
+    return 2 * dart_tis_loss_workspace_bytes(T);
 }
 
 dart_status_t dart_tok_stats_ex(const void* logits, dart_dtype_t dtype, int64_t T, int64_t V,
@@ -1831,7 +1845,8 @@ dart_status_t dart_tis_loss_fwd_ex(int64_t T, const float* logp, const float* lo
     cfg.ratio = c.ratio;
     return launch_tis_coef(true, T, logp, logp_old, logp_rollout,
                            c.kl == DART_KL_NONE ? nullptr : logp_ref, adv, step_offsets, S,
-                           step_mask, cfg, tok_coef, loss, stats, 6, workspace, stream);
+                           step_mask, cfg, tok_coef, loss, stats, 6, workspace,
+                           spare_part(workspace, workspace_bytes, T), stream);
 }
 
 dart_status_t dart_tis_loss_fwd(int64_t T, const float* logp, const float* logp_old,
@@ -1852,7 +1867,7 @@ dart_status_t dart_tis_loss_fwd(int64_t T, const float* logp, const float* logp_
         return ck;
     return launch_tis_coef(false, T, logp, logp_old, logp_rollout, nullptr, adv, step_offsets, S,
                            step_mask, plain_loss_config(eps_low, eps_high, C), tok_coef, loss,
-                           stats, 4, workspace, stream);
+                           stats, 4, workspace, nullptr, stream);
 }
 
 dart_status_t dart_select_tis_loss_fwd(int64_t T, const float* entropy, const float* logp,
@@ -1878,9 +1893,15 @@ dart_status_t dart_select_tis_loss_fwd(int64_t T, const float* entropy, const fl
         const dart_status_t st = dart_step_select(entropy, T, step_offsets, S, rho, step_entropy,
                                                   step_mask, n_kept_steps, stream);
         if (st != DART_OK) return st;
+        void* part = workspace;
+        size_t part_bytes = workspace_bytes;
+        if (T <= kSelCoefMaxT && S <= kSelLdsKeys) {
+            part = spare_part(workspace, workspace_bytes, T);
+            part_bytes = part ? dart_tis_loss_workspace_bytes(T) : 0;
+        }
         return dart_tis_loss_fwd(T, logp, logp_old, logp_rollout, adv, step_offsets, S, step_mask,
-                                 eps_low, eps_high, C, loss, tok_coef, stats, workspace,
-                                 workspace_bytes, stream);
+                                 eps_low, eps_high, C, loss, tok_coef, stats, part, part_bytes,
+                                 stream);
     }
     if (const dart_status_t ck = dart_check::run(
             stream, {{dart_check::Item::Offsets, step_offsets, S, T}}); ck != DART_OK)

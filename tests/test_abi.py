@@ -490,3 +490,12 @@ def test_hip_builds_disable_packed_fp32():
         flags = list(flags)
         assert "--offload-arch=gfx950" in flags
         assert any(flags[i:i + 4] == want for i in range(len(flags) - 3)), flags
+
+
+def test_split_workspace_bytes():
+    """Room for the partial sums behind the workspace of every size."""
+    for T in (1, 512, 4096, 152569, 0x7FFFFFFF):
+        assert (dart.dart_tis_loss_split_workspace_bytes(T)
+                == 2 * dart.dart_tis_loss_workspace_bytes(T) > 0)
+    for T in (0, -1, 0x80000000):
+        assert dart.dart_tis_loss_split_workspace_bytes(T) == 0

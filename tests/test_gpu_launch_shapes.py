@@ -495,3 +495,37 @@ def test_lmhead_backward_puts_back_more_rows_than_one_sweep(flags):
     kept = coef != 0
     assert int(kept.sum()) * d > 65536 * 1024
     assert torch.equal(got[kept], dense[kept]) and bool((got[~kept] == 0).all())
+
+
+@pytest.mark.parametrize("call", ["step ratios", "selection"])
+def test_workspace_that_stays_untouched(call):
+    """Step ratios, and the loss of a small fused selection, leave a workspace of
+    dart_tis_loss_workspace_bytes alone, and of one of the split size the first half;
+    with either, the same coefficients bit for bit and the same loss."""
+    import torch
+
+    import paper_2509_23866_amd as dart
+
+    rng = np.random.default_rng(5)
+    lens = rng.integers(20, 31, 120)  # 120 steps, more than 2048 and less than 4096 tokens
+    logp, lp_old, lp_roll, lp_ref, adv, off, mask = _loss_inputs(rng, lens)
+    T = int(lens.sum())
+    assert 2048 < T <= 4096
+    ent = _cuda(rng.random(T).astype(np.float32))
+    x = [_cuda(a) for a in (logp, lp_old, lp_roll, adv, off)]
+    small, full = dart.dart_tis_loss_workspace_bytes(T), dart.dart_tis_loss_split_workspace_bytes(T)
+    got = []
+    for nbytes, alone in ((small, small), (full, small)):
+        ws = torch.full((nbytes,), 0xA5, dtype=torch.uint8, device="cuda")
+        if call == "selection":
+            out = dart.dart_select_tis_loss_fwd(ent, *x, 0.6, 0.2, 0.28, 2.0, workspace=ws)[3:5]
+        else:
+            out = dart.dart_tis_loss_fwd_ex(*x, _cuda(mask), 0.2, 0.28, 2.0, logp_ref=_cuda(lp_ref),
+                                            kl="k3", beta=0.05, ratio="step_geomean",
+                                            workspace=ws)[:2]
+        assert bool((ws[:alone] == 0xA5).all())
+        assert nbytes == small or bool((ws[alone:] != 0xA5).any())
+        got.append(out)
+    (la, ca), (lb, cb) = got
+    assert torch.equal(ca.view(torch.int32), cb.view(torch.int32))
+    assert abs(la.item() - lb.item()) <= 1e-12 * abs(lb.item())
