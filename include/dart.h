@@ -280,7 +280,10 @@ typedef struct {
 /* Gradient flag: a row whose coefficient is exactly 0 (dropped step, clipped
  * token, zero advantage) is written as +0 without reading its logits, whatever
  * its lse. Without the flag such a row is not read either where its lse is
- * finite: every element is then the zero of the sign that the product has. */
+ * finite: every element is then the zero of the sign that the product has for
+ * logits that dart_tok_stats takes (finite, or -inf). A NaN or +inf logit in such
+ * a row shows in its gradient only where lse, which need not carry it, is not
+ * finite. */
 #define DART_GRAD_SKIP_ZERO_ROWS 1u
 
 /* dart_tok_stats for softmax(inv_temp * z): inv_temp is an inverse sampling

@@ -529,3 +529,31 @@ def test_workspace_that_stays_untouched(call):
     (la, ca), (lb, cb) = got
     assert torch.equal(ca.view(torch.int32), cb.view(torch.int32))
     assert abs(la.item() - lb.item()) <= 1e-12 * abs(lb.item())
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_a_nan_or_infinite_logit_of_a_dropped_row(dtype, value):
+    """What the header says of logits that the statistics do not take: in a row that
+    counts they give a NaN in the gradient, in a row with a zero coefficient zeros
+    where lse is finite; other rows do not change."""
+    import torch
+
+    import paper_2509_23866_amd as dart
+
+    T, V = 6, 20011
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(1)
+    z = (torch.randn(T, V, generator=g, device="cuda") * 3).to(dt)
+    y = torch.full((T,), 5, dtype=torch.int32, device="cuda")
+    coef = torch.full((T,), 0.1, device="cuda")
+    coef[[1, 3]] = 0.0
+    logp, _, lse = dart.dart_tok_stats(z, y)
+    clean = dart.dart_tis_grad(z, y, logp, lse, coef)
+    z[[1, 2], 9000] = value
+    got = dart.dart_tok_stats(z, y)
+    dz = dart.dart_tis_grad(z, y, got[0], got[2], coef)
+    assert bool(dz[2].isnan().any()) or bool(dz[2].isinf().any())
+    assert not bool(got[2][1].isfinite()) or bool((dz[1] == 0).all())
+    for rows in ([0], [3], [4], [5]):
+        assert torch.equal(dz[rows], clean[rows])
