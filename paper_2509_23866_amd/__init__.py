@@ -801,7 +801,12 @@ def _lmhead_backward(name, flags, hidden, weight, target, lse, logp, tok_coef, c
         nbytes = dart_lmhead_backward_split_workspace_bytes(T, d, V, chunk_rows, chunk_cols, f)
         if nbytes == 0:
             raise ValueError(f"{name}: bad sizes or flags")
-        workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev)
+        try:
+            workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev)
+        except torch.OutOfMemoryError:
+            # the least that does: up to 192 MiB less, slower
+            nbytes = dart_lmhead_backward_ex_workspace_bytes(T, d, V, chunk_rows, chunk_cols, f)
+            workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev)
         if isinstance(stream, torch.cuda.Stream):
             workspace.record_stream(stream)
     if (not isinstance(workspace, torch.Tensor) or workspace.dtype != torch.uint8
@@ -845,8 +850,9 @@ def dart_lmhead_backward_ex(hidden, weight, target, lse, logp, tok_coef, chunk_r
     (the call synchronises the stream once).
     ``workspace`` is "auto" or a uint8 device tensor of
     dart_lmhead_backward_ex_workspace_bytes(T, d, V, chunk_rows, chunk_cols, flags)
-    bytes; one of dart_lmhead_backward_split_workspace_bytes(...), as "auto" allocates, is
-    faster where a block has few rows, and leaves zero rows out of large calls unasked."""
+    bytes; one of dart_lmhead_backward_split_workspace_bytes(...), as "auto" allocates where
+    there is the memory, is faster where a block has few rows, and leaves zero rows out of
+    large calls unasked."""
     if chunk_rows is None and chunk_cols is None:
         chunk_rows, chunk_cols = lmhead_backward_plan(hidden.shape[0], weight.shape[0])
     elif chunk_rows is None or chunk_cols is None:

@@ -557,3 +557,40 @@ def test_a_nan_or_infinite_logit_of_a_dropped_row(dtype, value):
     assert not bool(got[2][1].isfinite()) or bool((dz[1] == 0).all())
     for rows in ([0], [3], [4], [5]):
         assert torch.equal(dz[rows], clean[rows])
+
+
+@pytest.mark.parametrize("flags", [None, 0, BF16])
+def test_lmhead_backward_where_memory_is_short(flags, monkeypatch):
+    """With no room for the larger workspace the call runs in the one that every call
+    needs, and gives the bits of a call that is handed that one."""
+    import torch
+
+    import paper_2509_23866_amd as dart
+
+    T, d, V = 300, 136, 9001
+    g = torch.Generator(device="cuda").manual_seed(2)
+    h = torch.randn(T, d, generator=g, device="cuda").to(torch.bfloat16)
+    w = (torch.randn(V, d, generator=g, device="cuda") * 3 / d ** 0.5).to(torch.bfloat16)
+    y = torch.randint(V, (T,), generator=g, device="cuda", dtype=torch.int32)
+    coef = torch.randn(T, generator=g, device="cuda") * 1e-2
+    logp, _, lse = dart.dart_lmhead_tok_stats(h, w, y)
+    least = dart.dart_lmhead_backward_ex_workspace_bytes(T, d, V, T, V, flags or 0)
+    assert least < dart.dart_lmhead_backward_split_workspace_bytes(T, d, V, T, V, flags or 0)
+
+    def run(**kw):
+        if flags is None:
+            return dart.dart_lmhead_backward(h, w, y, lse, logp, coef, chunk_rows=T, **kw)
+        return dart.dart_lmhead_backward_ex(h, w, y, lse, logp, coef, chunk_rows=T, chunk_cols=V,
+                                            flags=flags, **kw)
+
+    want = run(workspace=torch.empty(least, dtype=torch.uint8, device="cuda"))
+    empty = torch.empty
+
+    def short(*size, **kw):
+        if kw.get("dtype") == torch.uint8 and size[0] > least:
+            raise torch.OutOfMemoryError("no room")
+        return empty(*size, **kw)
+
+    monkeypatch.setattr(torch, "empty", short)
+    got = run()
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
