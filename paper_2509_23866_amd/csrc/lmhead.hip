@@ -62,6 +62,15 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const void* base, in
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)n, 0x00020000);
 }
 
+// Bytes from a matrix's row to the end of the last of `rows` rows of K bf16: the
+// padding after that one need not belong to the caller's allocation (the last
+// columns of a wider matrix), so a K slice that runs past K must not read it.
+__host__ __device__ constexpr int64_t rows_bytes(int64_t rows, int64_t ld, int64_t K) {
+    return ((rows - 1) * ld + K) * 2;
+}
+static_assert(rows_bytes(1, 80, 72) == 72 * 2 && rows_bytes(3, 80, 72) == (2 * 80 + 72) * 2,
+              "the last row's padding is left out");
+
 __device__ __forceinline__ __attribute__((address_space(3))) void* lds_ptr(void* p) {
     return (__attribute__((address_space(3))) void*)p;
 }
@@ -233,8 +242,8 @@ __device__ __forceinline__ void gemm_tile(const uint16_t* __restrict__ A, int64_
     const uint32_t voff_b = (uint32_t)((r_lane * ldb + (lslot ^ swz<CH>(r_lane)) * 8) * 2);
     const uint32_t qstride_a = (uint32_t)(C::WAVES * C::LROWS * lda * 2);
     const uint32_t qstride_b = (uint32_t)(C::WAVES * C::LROWS * ldb * 2);
-    const __amdgpu_buffer_rsrc_t rsrc_a = tile_rsrc(A + m0 * lda, (M - m0) * lda * 2);
-    const __amdgpu_buffer_rsrc_t rsrc_b = tile_rsrc(B + n0 * ldb, (N - n0) * ldb * 2);
+    const __amdgpu_buffer_rsrc_t rsrc_a = tile_rsrc(A + m0 * lda, rows_bytes(M - m0, lda, K));
+    const __amdgpu_buffer_rsrc_t rsrc_b = tile_rsrc(B + n0 * ldb, rows_bytes(N - n0, ldb, K));
     // rows of instruction q of wave `wave + hh * HW`
     auto lds_a = [&](int buf, int q, int hh) {
         return &sm.in.a[buf][(q * C::WAVES + wave + hh * (C::WAVES / 2)) * C::LROWS][0];

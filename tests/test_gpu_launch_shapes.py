@@ -594,3 +594,26 @@ def test_lmhead_backward_where_memory_is_short(flags, monkeypatch):
     monkeypatch.setattr(torch, "empty", short)
     got = run()
     assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
+@pytest.mark.parametrize("T,d,V", [(64, 72, 300), (300, 136, 700), (257, 8, 513)])
+def test_lmhead_operands_that_end_their_buffers(T, d, V):
+    """Hidden states and weight as the last columns of wider matrices, d no multiple
+    of a K slice: the last row ends the buffer, and nothing past it is read. The bits
+    of the call on contiguous copies."""
+    import torch
+
+    import paper_2509_23866_amd as dart
+
+    g = torch.Generator(device="cuda").manual_seed(d)
+    wide = lambda n: torch.randn(n, d + 8, generator=g, device="cuda").to(torch.bfloat16)[:, 8:]  # noqa: E731
+    h, w = wide(T), wide(V)
+    y = torch.randint(V, (T,), generator=g, device="cuda", dtype=torch.int32)
+    coef = torch.randn(T, generator=g, device="cuda") * 1e-2
+    a, b = [dart.dart_lmhead_tok_stats(*x, y) for x in ((h, w), (h.contiguous(), w.contiguous()))]
+    assert _same_bits(a, b)
+    ld = (V + 7) // 8 * 8
+    out = [torch.empty((T, ld), dtype=torch.bfloat16, device="cuda")[:, :V] for _ in range(2)]
+    dart.dart_lmhead_dlogits(h, w, y, a[2], a[0], coef, dlogits=out[0])
+    dart.dart_lmhead_dlogits(h.contiguous(), w.contiguous(), y, a[2], a[0], coef, dlogits=out[1])
+    assert torch.equal(out[0], out[1])
