@@ -847,7 +847,7 @@ def dart_lmhead_backward_ex(hidden, weight, target, lse, logp, tok_coef, chunk_r
     with flags (bitwise or):
     DART_LMHEAD_BF16_GRADS: dhidden and dweight in bfloat16;
     DART_LMHEAD_SKIP_ZERO_ROWS: the GEMMs over the rows with tok_coef != 0 only
-    (the call synchronises the stream once).
+    (their count is read on the device: the call stays asynchronous).
     ``workspace`` is "auto" or a uint8 device tensor of
     dart_lmhead_backward_ex_workspace_bytes(T, d, V, chunk_rows, chunk_cols, flags)
     bytes; one of dart_lmhead_backward_split_workspace_bytes(...), as "auto" allocates where

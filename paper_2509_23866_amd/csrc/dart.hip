@@ -293,22 +293,21 @@ struct RowLayout {
     int64_t head;      // scalar elements before the first 16-byte boundary
     int64_t nvec;      // aligned 16-byte vectors
     int64_t body_end;  // first element after the vectors
-    bool vector_ok;
 };
 
+// row is aligned to its elements (the entry points refuse others), so fewer than
+// kPerVec elements lie before the first boundary and fewer than that after the last
+// vector: the statistics load them one a lane.
 template <dart_dtype_t D>
 __device__ __forceinline__ RowLayout row_layout(const void* row, int64_t V) {
     using E = typename Elt<D>::T;
     constexpr int EPV = Elt<D>::kPerVec;
     RowLayout L;
     const uintptr_t addr = reinterpret_cast<uintptr_t>(row);
-    L.vector_ok = (addr % sizeof(E)) == 0;
-    int64_t head = (int64_t)(((16 - (addr & 15)) & 15) / sizeof(E));
-    if (!L.vector_ok) head = V;
-    if (head > V) head = V;
-    L.head = head;
-    L.nvec = (V - head) / EPV;
-    L.body_end = head + L.nvec * EPV;
+    const int64_t head = (int64_t)(((16 - (addr & 15)) & 15) / sizeof(E));
+    L.head = head < V ? head : V;
+    L.nvec = (V - L.head) / EPV;
+    L.body_end = L.head + L.nvec * EPV;
     return L;
 }
 
@@ -326,6 +325,7 @@ tok_stats_kernel(const void* __restrict__ logits, int64_t V, int64_t ld,
     constexpr int PER_IT = THREADS * UNROLL;
     constexpr int WAVES = THREADS / 64;
     static_assert(WAVES <= 64, "one wave merges the waves' triples");
+    static_assert(2 * EPV <= THREADS, "a lane for every element beside the vectors");
     __shared__ Triple partial[WAVES];
 
     const int64_t t = blockIdx.x;
@@ -771,10 +771,13 @@ step_select_kernel(const float* __restrict__ H, int64_t T, const int32_t* __rest
 constexpr int kAdvThreads = 256;
 constexpr int64_t kAdvTokens = 2048, kAdvMaxPer = 16;
 
-// One workgroup per group. Over the group's steps (each step counts its
+// gridDim.y workgroups per group, one for every kAdvTokens tokens of the average
+// group and at most kAdvMaxPer. Over the group's steps (each step counts its
 // trajectory's reward once): mean and population standard deviation, summed
-// per trajectory with weight = its step count, in fp64, in a fixed order; then
-// every token of trajectory i gets (R_i - mean) / sd (0 when sd == 0).
+// per trajectory with weight = its step count, in fp64, in a fixed order, in each
+// of them; then every token of trajectory i gets (R_i - mean) / sd (0 when sd == 0),
+// runs of 64 tokens dealt out to the group's workgroups. (One workgroup a group wrote
+// 152,569 tokens of 4 groups in 9.6 us.)
 __global__ void __launch_bounds__(kAdvThreads)
 grpo_advantage_kernel(const float* __restrict__ reward, const int32_t* __restrict__ traj_off,
                       int64_t n_traj, const int32_t* __restrict__ grp_off,

@@ -1299,6 +1299,11 @@ constexpr int64_t kMaxLd = int64_t(1) << 22;
 // 64 rows go as one 64-row tile, up to 128 and 129 - 256 as 128-row tiles at
 // V = 152064, more as 256-row ones (the last one of up to 128 rows as in Rest),
 // unless those would leave units idle (1000 rows of V = 8000).
+// The times' ratios at d = 3584 serve every depth: of 99 sizes (d = 512, 1024 and 2048;
+// V = 8000, 32000 and 152064; T from 16 to 2100) the choice is within 5% of the fastest
+// of the three but for 600 rows of V = 32000 (58.1 against 54.4 us at d = 1024, 96.6
+// against 88.3 at 2048, by the last tile's rule), and none takes longer than with
+// 256-row tiles alone (statistics).
 constexpr int64_t kUnits = 256;
 int tile_rows(int64_t rows, int64_t V) {
     const double nvt = (double)((V + LmCfg::BN - 1) / LmCfg::BN), t256 = 92, t128 = 54, t64 = 45;

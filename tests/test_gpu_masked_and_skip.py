@@ -234,8 +234,9 @@ def test_tis_grad_bf16_rounding(V, ld, out_ld):
     (-expm1(-inf) = 1). The coefficients sit on and beside rounding ties, in
     the fp32 denormal range and at the top of the range. Rows ld = 1011
     elements apart start unaligned: with the output rows as far apart their
-    heads and tails take the kernel's scalar paths around the vector body,
-    with contiguous output rows (other heads) the whole row takes them."""
+    heads and tails take the kernel's scalar paths around the vector body; with
+    contiguous output rows (other heads) the vectors are the output's, and the
+    logits are loaded at their own alignment."""
     import torch
 
     import paper_2509_23866_amd as dart
