@@ -401,25 +401,24 @@ __device__ __forceinline__ void gemm_tile(const uint16_t* __restrict__ A, int64_
 #endif
 }
 
-// The workgroup's result tile in LDS, rounded to bf16: four adjacent columns
-// of a row leave a lane as one 8-byte write.
-template <class C>
-__device__ __forceinline__ void tile_to_lds_bf16(const f32x16 (&acc)[C::TM][C::TN],
-                                                 typename C::Smem& sm) {
+// NJ 32-column blocks (acc[0] is block j0) of the wave's row block i in the
+// workgroup's result tile in LDS, rounded to bf16: four adjacent columns of a row
+// leave a lane as one 8-byte write.
+template <class C, int NJ>
+__device__ __forceinline__ void blocks_to_lds_bf16(const f32x16* acc, int i, int j0,
+                                                   typename C::Smem& sm) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wr = (wave / C::WN) * 32 + (lane & 31), wc = (wave % C::WN) * (C::BN / C::WN);
 #pragma unroll
-    for (int i = 0; i < C::TM; ++i)
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
-        for (int j = 0; j < C::TN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; v += 4) {
-                u32x2 pk;
-                pk.x = pack_bf16x2(acc[i][j][v], acc[i][j][v + 1]);
-                pk.y = pack_bf16x2(acc[i][j][v + 2], acc[i][j][v + 3]);
-                *reinterpret_cast<u32x2*>(
-                    &sm.c16[wr + i * C::RS][wc + j * 32 + (v >> 2) * 8 + (lane >> 5) * 4]) = pk;
-            }
+        for (int v = 0; v < 16; v += 4) {
+            u32x2 pk;
+            pk.x = pack_bf16x2(acc[j][v], acc[j][v + 1]);
+            pk.y = pack_bf16x2(acc[j][v + 2], acc[j][v + 3]);
+            *reinterpret_cast<u32x2*>(
+                &sm.c16[wr + i * C::RS][wc + (j0 + j) * 32 + (v >> 2) * 8 + (lane >> 5) * 4]) = pk;
+        }
 }
 
 // Logical tile of workgroup b: the hardware places workgroup b on XCD b % 8,
@@ -624,57 +623,73 @@ __device__ __forceinline__ void lmhead_dlogits_tile(
     float scale, uint16_t* __restrict__ out, int64_t ld_out, int64_t vbase, typename C::Smem& sm,
     int64_t m0, int64_t vt) {
     const int64_t n0 = vt * C::BN;
-    f32x16 acc[C::TM][C::TN];
-    gemm_tile<C>(h, M, ldh, w, V, ldw, d, m0, n0, sm, acc);
-
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5;
     const int wr = (wave / C::WN) * 32 + (lane & 31), wc = (wave % C::WN) * (C::BN / C::WN);
+    f32x16 acc[C::TM][C::TN];
+    gemm_tile<C>(h, M, ldh, w, V, ldw, d, m0, n0, sm, acc);
+
     // the inverse temperature enters the base-2 exponent's factor (1 at scale
     // 1: the same bits)
     const float c2 = scale * 1.4426950408889634f;
-    // the lane's rows turned into bf16 in registers, then the bf16 tile through
-    // LDS so that each row leaves as 16-byte vectors
+    // the constants of all of the lane's rows ahead of the first store, which a later
+    // load would wait for
+    float gs[C::TM], lses[C::TM];
+    int32_t ys[C::TM];
 #pragma unroll
     for (int i = 0; i < C::TM; ++i) {
-        // the row's constants: -g, -lse log2(e), the target's gradient
-        // g (-expm1(logp)) (accurate when p_y -> 1), the target's column here;
-        // g carries the inverse temperature (the chain rule through scale z)
-        const int64_t t = m0 + wr + i * C::RS;
-        const int64_t tc = t < M ? t : M - 1;  // rows past M are not stored
-        const float g = coef[tc] * scale;
-        const float neg_g = -g, neg_lse = -lse[tc] * 1.4426950408889634f;
-        const int64_t yrel = (int64_t)target[tc] - vbase - n0 - wc;
-        const int y32 = yrel >= 0 && yrel < C::BN / C::WN ? (int)yrel : -1;
-#pragma unroll
-        for (int j = 0; j < C::TN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v)
-                acc[i][j][v] = neg_g * __builtin_amdgcn_exp2f(fmaf(acc[i][j][v], c2, neg_lse));
-        if (y32 >= 0 && ((y32 >> 2) & 1) == half) {
-            const float dy = g * -expm1f(logp[tc]);
-#pragma unroll
-            for (int j = 0; j < C::TN; ++j)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int col = j * 32 + (v >> 2) * 8 + (v & 3);
-                    acc[i][j][v] = col == y32 - half * 4 ? dy : acc[i][j][v];
-                }
-        }
+        const int64_t t = min(m0 + wr + i * C::RS, M - 1);  // rows past M are not stored
+        gs[i] = coef[t], lses[i] = lse[t], ys[i] = target[t];
     }
-    tile_to_lds_bf16<C>(acc, sm);
-    lds_ring_barrier();
-    constexpr int CHUNKS = C::BN / 8;  // 16-byte output chunks per tile row
-    for (int e = tid; e < C::BM * CHUNKS; e += C::THREADS) {
-        const int r = e / CHUNKS, ch = e % CHUNKS;
-        const int64_t t = m0 + r, col0 = n0 + ch * 8;
-        if (t >= M || col0 >= V) continue;
-        const u32x4 pk = *reinterpret_cast<const u32x4*>(&sm.c16[r][ch * 8]);
-        uint16_t* dst = out + t * ld_out + col0;
-        if (col0 + 8 <= V)
-            __builtin_nontemporal_store(pk, reinterpret_cast<u32x4*>(dst));
-        else
-            for (int q = 0; q < 8 && col0 + q < V; ++q) dst[q] = sm.c16[r][ch * 8 + q];
+    // Pieces of 32 rows x 64 columns: turned into bf16 in registers, then through the
+    // wave's own part of the LDS (its accesses run in order: no barrier), so that a
+    // row's piece leaves as one 128-byte line while the next piece is formed. With the
+    // whole tile formed, a barrier, and then every store, the stores came in one burst
+    // behind the exponentials, which a short K loop does not hide: at d = 512 1000 rows
+    // of V = 32000 took 42.2 us, now 38.0, 4096 of 8000 43.9 and 39.3, at d = 3584 4096
+    // of 152064 3439 and 3394.
+#pragma unroll
+    for (int i = 0; i < C::TM; ++i) {
+        // -g, -lse log2(e), the target's gradient g (-expm1(logp)) (accurate when
+        // p_y -> 1), the target's column; g carries the inverse temperature (the
+        // chain rule through scale z)
+        const float g = gs[i] * scale;
+        const float neg_g = -g, neg_lse = -lses[i] * 1.4426950408889634f;
+#pragma unroll
+        for (int u = 0; u < C::TN / 2; ++u) {
+            const int64_t yrel = (int64_t)ys[i] - vbase - n0 - wc - u * 64;
+            const int y64 = yrel >= 0 && yrel < 64 ? (int)yrel : -1;
+#pragma unroll
+            for (int j = 2 * u; j < 2 * u + 2; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    acc[i][j][v] = neg_g * __builtin_amdgcn_exp2f(fmaf(acc[i][j][v], c2, neg_lse));
+            if (y64 >= 0 && ((y64 >> 2) & 1) == half) {
+                const float dy = g * -expm1f(logp[min(m0 + wr + i * C::RS, M - 1)]);
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const int col = j * 32 + (v >> 2) * 8 + (v & 3);
+                        acc[i][2 * u + j][v] = col == y64 - half * 4 ? dy : acc[i][2 * u + j][v];
+                    }
+            }
+            blocks_to_lds_bf16<C, 2>(&acc[i][2 * u], i, 2 * u, sm);
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int r = (wave / C::WN) * 32 + i * C::RS + q * 8 + (lane >> 3);
+                const int c = wc + u * 64 + (lane & 7) * 8;
+                const int64_t t = m0 + r, col = n0 + c;
+                if (t >= M || col >= V) continue;
+                const u32x4 pk = *reinterpret_cast<const u32x4*>(&sm.c16[r][c]);
+                uint16_t* dst = out + t * ld_out + col;
+                if (col + 8 <= V)
+                    __builtin_nontemporal_store(pk, reinterpret_cast<u32x4*>(dst));
+                else
+                    for (int k = 0; k < 8 && col + k < V; ++k) dst[k] = sm.c16[r][c + k];
+            }
+        }
     }
 }
 
@@ -1105,7 +1120,8 @@ __device__ __forceinline__ void bwd_gemm_tile(const BwdGemm& g, int64_t b, typen
     const int wr = (wave / C::WN) * 32 + (lane & 31), wc = (wave % C::WN) * (C::BN / C::WN);
     if constexpr (OUT == kOutBf16) {
         constexpr int VPR = C::BN / 8;  // 16-byte vectors per tile row
-        tile_to_lds_bf16<C>(acc, sm);
+#pragma unroll
+        for (int i = 0; i < C::TM; ++i) blocks_to_lds_bf16<C, C::TN>(acc[i], i, 0, sm);
         lds_ring_barrier();
         for (int e = tid; e < C::BM * VPR; e += C::THREADS) {
             const int r = e / VPR, cv = e % VPR;
@@ -1304,9 +1320,13 @@ constexpr int64_t kMaxLd = int64_t(1) << 22;
 // of the three but for 600 rows of V = 32000 (58.1 against 54.4 us at d = 1024, 96.6
 // against 88.3 at 2048, by the last tile's rule), and none takes longer than with
 // 256-row tiles alone (statistics).
+// A round of 128-row tiles of dlogits is worth 57 us up to d = 1024, where the two
+// heights come within 5% of each other (129 to 256 rows of V = 152064): the taller tile
+// reads W once and has fewer first slices to wait for. 130 rows 50.0 us in 128-row
+// tiles and 45.8 in 256-row ones at d = 512, 87.0 and 83.0 at 1024; 170 and 181 at 2048.
 constexpr int64_t kUnits = 256;
-int tile_rows(int64_t rows, int64_t V) {
-    const double nvt = (double)((V + LmCfg::BN - 1) / LmCfg::BN), t256 = 92, t128 = 54, t64 = 45;
+int tile_rows(int64_t rows, int64_t V, double t128 = 54) {
+    const double nvt = (double)((V + LmCfg::BN - 1) / LmCfg::BN), t256 = 92, t64 = 45;
     auto rounds = [](double tiles) { return ceil(tiles / kUnits); };
     const int64_t nmt = (rows + 255) / 256, r = rows % 256;
     double least = rounds((double)nmt * nvt) * t256;
@@ -1331,11 +1351,10 @@ bool bad_lmhead_args(const void* hidden, int64_t T, int64_t d, int64_t ld_h, con
     return reinterpret_cast<uintptr_t>(hidden) % 16 || reinterpret_cast<uintptr_t>(weight) % 16;
 }
 
-// f(tile configuration) for rows x V logits. The launch's limits are checked
+// f(configuration of bm-row tiles) for rows x V logits. The launch's limits are checked
 // with 256-row tiles, as ever; smaller ones are taken where they fit too.
 template <class F>
-void with_tile(int64_t rows, int64_t V, F&& f) {
-    int bm = tile_rows(rows, V);
+void with_tile(int bm, int64_t rows, int64_t V, F&& f) {
     if (!grid_fits((rows + bm - 1) / bm * vocab_tiles(V), LmCfg::THREADS)) bm = 256;
     if (bm == 64)
         f(LmCfg64{});
@@ -1354,7 +1373,7 @@ dart_status_t launch_dlogits(const uint16_t* hidden, int64_t rows, int64_t d, in
     const int64_t nmt = (rows + LmCfg::BM - 1) / LmCfg::BM, nvt = vocab_tiles(V);
     if (!grid_fits(nmt * nvt, LmCfg::THREADS) || ld_h > kMaxLd || ld_w > kMaxLd)
         return DART_ERR_UNSUPPORTED;
-    with_tile(rows, V, [&](auto cfg) {
+    with_tile(tile_rows(rows, V, d <= 1024 ? 57 : 54), rows, V, [&](auto cfg) {
         using C = decltype(cfg);
         const int64_t nm = (rows + C::BM - 1) / C::BM;
         hipLaunchKernelGGL(lmhead_dlogits_kernel<C>, dim3((unsigned)(nm * nvt)), dim3(C::THREADS),
@@ -1395,7 +1414,7 @@ dart_status_t dart_lmhead_tok_stats_ex(const void* hidden, int64_t T, int64_t d,
         return DART_ERR_UNSUPPORTED;
     float4* part = static_cast<float4*>(workspace);
     float* z_y = reinterpret_cast<float*>(part + T * nvt);
-    with_tile(T, V, [&](auto cfg) {
+    with_tile(tile_rows(T, V), T, V, [&](auto cfg) {
         using C = decltype(cfg);
         const int64_t nm = (T + C::BM - 1) / C::BM;
         hipLaunchKernelGGL(lmhead_stats_kernel<C>, dim3((unsigned)(nm * nvt)), dim3(C::THREADS), 0,
