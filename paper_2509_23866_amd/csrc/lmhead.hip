@@ -86,6 +86,15 @@ __device__ __forceinline__ __attribute__((address_space(3))) void* lds_ptr(void*
     asm volatile("" ::: "memory");
 }
 
+// Orders a wave's LDS accesses before it against those after it, across its lanes
+// (which the convergent barrier brings together): the hardware runs them in the
+// program's order, so nothing is waited for.
+[[maybe_unused]] __device__ __forceinline__ void lds_wave_order() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
+}
+
 // Tile configuration: BM tokens x BN vocabulary entries per workgroup, K in
 // slices of 64 through an NS-buffer LDS ring filled by direct global->LDS
 // loads (no staging registers), WM x WN waves each owning a (BM/WM) x (BN/WN)
@@ -675,7 +684,7 @@ __device__ __forceinline__ void lmhead_dlogits_tile(
                     }
             }
             blocks_to_lds_bf16<C, 2>(&acc[i][2 * u], i, 2 * u, sm);
-            asm volatile("" ::: "memory");
+            lds_wave_order();
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int r = (wave / C::WN) * 32 + i * C::RS + q * 8 + (lane >> 3);
@@ -1079,9 +1088,7 @@ __device__ __forceinline__ void tile_of_block_nfast(int64_t b, int64_t nmt, int6
     mt = lg / nnt;
 }
 
-// Tile b of GEMM g: the MFMA tile, then the result through LDS (bf16 whole,
-// fp32 128 rows at a time), so that each row leaves as 16-byte vectors (vec),
-// else one element at a time.
+// Tile b of GEMM g: the MFMA tile, then the result through LDS.
 template <class C, bool A_KMAJ, int OUT>
 __device__ __forceinline__ void bwd_gemm_tile(const BwdGemm& g, int64_t b, typename C::Smem& sm) {
     using OutT = typename std::conditional<OUT == kOutBf16, uint16_t, float>::type;
@@ -1116,59 +1123,67 @@ __device__ __forceinline__ void bwd_gemm_tile(const BwdGemm& g, int64_t b, typen
     f32x16 acc[C::TM][C::TN];
     gemm_tile_bwd<C, A_KMAJ>(g.A, g.lda, g.B, g.ldb, M, N, kbeg, K, m0, n0, sm, acc);
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = (wave / C::WN) * 32 + (lane & 31), wc = (wave % C::WN) * (C::BN / C::WN);
-    if constexpr (OUT == kOutBf16) {
-        constexpr int VPR = C::BN / 8;  // 16-byte vectors per tile row
+    // Pieces of 32 rows x 64 columns through the wave's own part of the LDS, without
+    // barriers, as in lmhead_dlogits_tile: a row's piece leaves as 16-byte vectors (vec),
+    // else one element at a time.
+    constexpr int EPC = 16 / sizeof(OutT), CPR = 64 / EPC, RPI = 64 / CPR;  // a chunk, a row,
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;             // a store
+    const int wr = (wave / C::WN) * 32, wc = (wave % C::WN) * (C::BN / C::WN);
+    const int rr = lane / CPR, cc = lane % CPR * EPC;
 #pragma unroll
-        for (int i = 0; i < C::TM; ++i) blocks_to_lds_bf16<C, C::TN>(acc[i], i, 0, sm);
-        lds_ring_barrier();
-        for (int e = tid; e < C::BM * VPR; e += C::THREADS) {
-            const int r = e / VPR, cv = e % VPR;
-            const int64_t m = m0 + r, n = n0 + (int64_t)cv * 8;
-            if (m >= M || n >= N) continue;
-            uint16_t* dst = out + m * g.ldc + n;
-            if (g.vec && n + 8 <= N)
-                *reinterpret_cast<u32x4*>(dst) = *reinterpret_cast<const u32x4*>(&sm.c16[r][cv * 8]);
-            else
-                for (int q = 0; q < 8 && n + q < N; ++q) dst[q] = sm.c16[r][cv * 8 + q];
-        }
-        return;
-    } else {
-        constexpr int VPR = C::BN / 4;
-        static_assert(C::EPI == C::RS, "one row block of every wave per pass");
+    for (int i = 0; i < C::TM; ++i)
 #pragma unroll
-        for (int i = 0; i < C::TM; ++i) {
-            const int e0 = i * C::EPI;
-            // LDS-only barriers: a __syncthreads fence here would also wait for
-            // the previous pass's stores
-            if (i) lds_ring_barrier();
+        for (int u = 0; u < C::TN / 2; ++u) {
+            const OutT* src;  // the lane's chunk of the piece's first RPI rows
+            int ld;
+            lds_wave_order();  // fp32 pieces of every i share their rows of the LDS
+            if constexpr (OUT == kOutBf16) {
+                blocks_to_lds_bf16<C, 2>(&acc[i][2 * u], i, 2 * u, sm);
+                src = &sm.c16[wr + i * C::RS + rr][wc + u * 64 + cc];
+                ld = C::CROW16;
+            } else {
 #pragma unroll
-            for (int j = 0; j < C::TN; ++j)
+                for (int j = 0; j < 2; ++j)
 #pragma unroll
-                for (int v = 0; v < 16; v += 4) {
-                    const f32x4 x = {acc[i][j][v], acc[i][j][v + 1], acc[i][j][v + 2],
-                                     acc[i][j][v + 3]};
-                    *reinterpret_cast<f32x4*>(
-                        &sm.c[wr][wc + j * 32 + (v >> 2) * 8 + (lane >> 5) * 4]) = x;
+                    for (int v = 0; v < 16; v += 4) {
+                        const f32x16& t = acc[i][2 * u + j];
+                        const f32x4 x = {t[v], t[v + 1], t[v + 2], t[v + 3]};
+                        *reinterpret_cast<f32x4*>(
+                            &sm.c[wr + (lane & 31)]
+                                 [wc + u * 64 + j * 32 + (v >> 2) * 8 + (lane >> 5) * 4]) = x;
+                    }
+                src = &sm.c[wr + rr][wc + u * 64 + cc];
+                ld = C::CROW;
+            }
+            lds_wave_order();
+            const int64_t m = m0 + wr + i * C::RS + rr, n = n0 + wc + u * 64 + cc;
+            OutT* dst = out + m * g.ldc + n;
+            if (g.vec && n + EPC <= N) {
+                typedef typename std::conditional<ACC, f32x4, u32x4>::type Vec;
+                Vec x[32 / RPI];
+#pragma unroll
+                for (int q = 0; q < 32 / RPI; ++q)
+                    if constexpr (ACC)
+                        if (m + q * RPI < M) x[q] = *reinterpret_cast<const Vec*>(dst + q * RPI * g.ldc);
+#pragma unroll
+                for (int q = 0; q < 32 / RPI; ++q) {
+                    const Vec y = *reinterpret_cast<const Vec*>(src + q * RPI * ld);
+                    if (m + q * RPI >= M) continue;
+                    if constexpr (ACC)
+                        x[q] += y;
+                    else
+                        x[q] = y;
+                    *reinterpret_cast<Vec*>(dst + q * RPI * g.ldc) = x[q];
                 }
-            lds_ring_barrier();
-            for (int e = tid; e < C::EPI * VPR; e += C::THREADS) {
-                const int r = e / VPR, cv = e % VPR;
-                const int64_t m = m0 + e0 + r, n = n0 + (int64_t)cv * 4;
-                if (m >= M || n >= N) continue;
-                const float* src = &sm.c[r][cv * 4];
-                OutT* dst = out + m * g.ldc + n;
-                if (g.vec && n + 4 <= N) {
-                    f32x4 x = *reinterpret_cast<const f32x4*>(src);
-                    if constexpr (ACC) x += *reinterpret_cast<const f32x4*>(dst);
-                    *reinterpret_cast<f32x4*>(dst) = x;
-                } else {
-                    for (int q = 0; q < 4 && n + q < N; ++q) dst[q] = ACC ? dst[q] + src[q] : src[q];
-                }
+            } else {
+                for (int q = 0; q < 32 / RPI && m + q * RPI < M; ++q)
+                    for (int e = 0; e < EPC && n + e < N; ++e) {
+                        OutT* o = dst + q * RPI * g.ldc + e;
+                        const OutT y = src[q * RPI * ld + e];
+                        *o = ACC ? *o + y : y;
+                    }
             }
         }
-    }
 }
 
 // The two GEMMs of one backward block in one launch: dh = dz W (dz read
