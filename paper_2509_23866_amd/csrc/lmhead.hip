@@ -1066,6 +1066,8 @@ struct BwdGemm {
     const int32_t* dyn;
     int64_t dyn_base;
     bool dyn_m, dyn_k;
+    // optional: row m of the result belongs at row map[m] of out
+    const int32_t* map;
     // the sum over k in ksplit parts of kper (a multiple of BK), part i written
     // to out + i * part_stride elements
     int64_t ksplit, kper, part_stride;
@@ -1157,14 +1159,18 @@ __device__ __forceinline__ void bwd_gemm_tile(const BwdGemm& g, int64_t b, typen
             }
             lds_wave_order();
             const int64_t m = m0 + wr + i * C::RS + rr, n = n0 + wc + u * 64 + cc;
-            OutT* dst = out + m * g.ldc + n;
+            // the lane's q-th row of the piece, which is below M
+            auto dst = [&](int q) {
+                const int64_t r = m + q * RPI;
+                return out + (g.map ? (int64_t)g.map[r] : r) * g.ldc + n;
+            };
             if (g.vec && n + EPC <= N) {
                 typedef typename std::conditional<ACC, f32x4, u32x4>::type Vec;
                 Vec x[32 / RPI];
 #pragma unroll
                 for (int q = 0; q < 32 / RPI; ++q)
                     if constexpr (ACC)
-                        if (m + q * RPI < M) x[q] = *reinterpret_cast<const Vec*>(dst + q * RPI * g.ldc);
+                        if (m + q * RPI < M) x[q] = *reinterpret_cast<const Vec*>(dst(q));
 #pragma unroll
                 for (int q = 0; q < 32 / RPI; ++q) {
                     const Vec y = *reinterpret_cast<const Vec*>(src + q * RPI * ld);
@@ -1173,15 +1179,16 @@ __device__ __forceinline__ void bwd_gemm_tile(const BwdGemm& g, int64_t b, typen
                         x[q] += y;
                     else
                         x[q] = y;
-                    *reinterpret_cast<Vec*>(dst + q * RPI * g.ldc) = x[q];
+                    *reinterpret_cast<Vec*>(dst(q)) = x[q];
                 }
             } else {
-                for (int q = 0; q < 32 / RPI && m + q * RPI < M; ++q)
+                for (int q = 0; q < 32 / RPI && m + q * RPI < M; ++q) {
+                    OutT* o = dst(q);
                     for (int e = 0; e < EPC && n + e < N; ++e) {
-                        OutT* o = dst + q * RPI * g.ldc + e;
                         const OutT y = src[q * RPI * ld + e];
-                        *o = ACC ? *o + y : y;
+                        o[e] = ACC ? o[e] + y : y;
                     }
+                }
             }
         }
 }
@@ -1512,13 +1519,14 @@ struct BackwardPlan {
 
 // Whether a call that is not told to skip zero rows leaves them out all the
 // same, as the gradient pass on logits does: where that is worth the kernels
-// around it (7 - 10 us at d = 3584, against the share of zero rows of a backward
-// that takes at least 0.5 ms) and the compact rows fit 128 MiB. Few rows are
-// bound by W and dW, not by their number.
+// around it (finding the rows and copying them: 7 us at T = 1000, 20 at 2500, d = 3584,
+// against the share of zero rows of a backward that takes at least 0.5 ms) and the
+// compact rows fit 128 MiB. Few rows are bound by W and dW, not by their number.
 // Measured at d = 3584, V = 152064, bf16 gradients: with 20% zero rows 2738 -> 2568
 // us at T = 1000 and 10107 -> 8629 at 4096, with 50% 2668 -> 1658 and 9830 -> 5626;
-// with none 2801 -> 2808 and 10322 -> 10331 (1585 -> 1592 at 512). Below the line,
-// at T = 1500, V = 14000, d = 1776 (3.7e10), leaving none out costs 3%.
+// with none 2801 -> 2808 and 10475 -> 10490, at T = 2500 1425 -> 1442 (V = 32000) and
+// 979 -> 990 (V = 20000). Below the line, at T = 1500, V = 14000, d = 1776 (3.7e10),
+// leaving none out costs 3%.
 bool leaves_zero_rows_out(int64_t T, int64_t d, int64_t V) {
     return T >= 256 && (double)T * (double)V * (double)d >= 1e11 &&
            (double)T * (double)(6 * d + 20) <= double(128 << 20);
@@ -1606,7 +1614,7 @@ BwdGemm make_bwd_gemm(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t
     g.nmt = (M + LmCfg::BM - 1) / LmCfg::BM;
     g.nnt = (N + LmCfg::BN - 1) / LmCfg::BN;
     g.dyn = nullptr, g.dyn_base = 0, g.dyn_m = g.dyn_k = false;
-    g.ksplit = 1, g.kper = K, g.part_stride = 0;
+    g.map = nullptr, g.ksplit = 1, g.kper = K, g.part_stride = 0;
     return g;
 }
 
@@ -1633,13 +1641,14 @@ void launch_bwd_gemms_dw(int dw_mode, const BwdGemm& dh, const BwdGemm& dw, int6
 // dW[cols, d] (+)= dz[rows, cols]^T h[rows, d], in one launch. A bf16 output
 // is never added to (sums over blocks go through fp32). With ksplit > 1 dh_out is
 // ksplit fp32 matrices part_stride elements apart, which each get their part of
-// the sum. With dyn_rows, the block's rows are at most *dyn_rows - dyn_base
-// (read on the device).
+// the sum. With dh_map row i of dh goes to row dh_map[i] of dh_out. With dyn_rows,
+// the block's rows are at most *dyn_rows - dyn_base (read on the device).
 dart_status_t launch_bwd_gemms(const uint16_t* dz, int64_t ld_dz, int64_t rows, int64_t cols,
                                const uint16_t* w, int64_t ld_w, const uint16_t* h, int64_t ld_h,
                                int64_t d, const Grad& dh_out, bool dh_acc, int64_t ksplit,
                                int64_t part_stride, const Grad& dw_out, bool dw_acc,
-                               hipStream_t stream, const int32_t* dyn_rows, int64_t dyn_base) {
+                               hipStream_t stream, const int32_t* dh_map, const int32_t* dyn_rows,
+                               int64_t dyn_base) {
     if ((dh_out.bf16 && dh_acc) || (dw_out.bf16 && dw_acc)) return DART_ERR_INVALID_ARG;
     if (ld_dz > kMaxLd || ld_w > kMaxLd || ld_h > kMaxLd || dh_out.ld > kMaxLd ||
         dw_out.ld > kMaxLd)
@@ -1650,6 +1659,7 @@ dart_status_t launch_bwd_gemms(const uint16_t* dz, int64_t ld_dz, int64_t rows, 
     dh.dyn = dw.dyn = dyn_rows;
     dh.dyn_base = dw.dyn_base = dyn_base;
     dh.dyn_m = dw.dyn_k = dyn_rows != nullptr;
+    dh.map = dh_map;
     if (ksplit > 1) {
         const int64_t nk = (cols + LmCfg::BK - 1) / LmCfg::BK;
         dh.ksplit = ksplit, dh.kper = (nk + ksplit - 1) / ksplit * LmCfg::BK;
@@ -1684,8 +1694,11 @@ void launch_to_bf16(const float* src, int64_t rows, int64_t cols, const Grad& ds
 // first row block writes dW even when it holds no rows). With parts (ksplit > 1),
 // a row block's dh is summed there, [ksplit][R, d], and added up once its last
 // vocabulary block is in. With map (and dyn_rows), the rows are compact ones and
-// row i of dh belongs at row map[i]: dh's sums stay in acc_h ([T, d]) or the parts
-// and are put there at the end.
+// row i of dh belongs at row map[i]: the GEMM puts it there, unless its sum needs
+// acc_h ([T, d]) or the parts, from where it is put there at the end. (With every sum
+// in acc_h first, 2500 rows of V = 20000, d = 3584, none of them zero, took 1012 us
+// with bf16 gradients and 1052 with fp32 ones, now 990 and 1022; 999 and 1006 where
+// the rows are not looked at.)
 dart_status_t backward_core(const uint16_t* h, int64_t T, int64_t d,
                             int64_t ld_h, const uint16_t* w, int64_t V, int64_t ld_w,
                             const int32_t* target, const float* lse, const float* logp,
@@ -1697,7 +1710,8 @@ dart_status_t backward_core(const uint16_t* h, int64_t T, int64_t d,
     if (R > T) R = T;
     if (C > V) C = V;
     const int64_t ld_dz = ceil8(C);
-    const bool via_h = !parts && (map || (dh.bf16 && C < V)), via_w = dw.bf16 && R < T;
+    const bool via_h = !parts && dh.bf16 && C < V, via_w = dw.bf16 && R < T;
+    const bool put = map && !parts && !via_h;
     auto sum_parts = [&](const float* p, int64_t n, int64_t stride, int64_t r0, int64_t rows) {
         const int64_t blocks = (rows * d / 4 + 255) / 256;
         const dim3 grid((unsigned)(blocks < kRowBlocks ? blocks : kRowBlocks));
@@ -1724,8 +1738,10 @@ dart_status_t backward_core(const uint16_t* h, int64_t T, int64_t d,
             if (st != DART_OK) return st;
             const dart_status_t sg = launch_bwd_gemms(
                 dz, ld_dz, rows, cols, wc, ld_w, hr, ld_h, d,
-                parts ? Grad{parts, d, false} : Grad{sum_h.row(r0), sum_h.ld, sum_h.bf16}, c0 > 0,
-                parts ? ksplit : 1, R * d, Grad{sum_w.row(c0), sum_w.ld, sum_w.bf16}, r0 > 0, stream, dyn_rows, r0);
+                parts ? Grad{parts, d, false}
+                      : Grad{put ? sum_h.p : sum_h.row(r0), sum_h.ld, sum_h.bf16},
+                c0 > 0, parts ? ksplit : 1, R * d, Grad{sum_w.row(c0), sum_w.ld, sum_w.bf16},
+                r0 > 0, stream, put ? map + r0 : nullptr, dyn_rows, r0);
             if (sg != DART_OK) return sg;
         }
         if (parts) sum_parts(parts, ksplit, R * d, r0, rows);

@@ -472,11 +472,12 @@ def test_token_statistics_do_not_depend_on_the_number_of_rows(vecs, dtype):
         assert _same_bits(dart.dart_tok_stats(z[:n], y[:n]), [x[:n] for x in want]), n
 
 
-@pytest.mark.parametrize("flags", [SKIP, SKIP | BF16])
-def test_lmhead_backward_puts_back_more_rows_than_one_sweep(flags):
-    """Skipped rows: the kept rows' dhidden, more than the 65,536 workgroups of one
-    sweep put back, bit for bit those of the dense call (the sums over one short
-    vocabulary block run in the same order)."""
+@pytest.mark.parametrize("flags,cols", [(SKIP, 40), (SKIP, 24), (SKIP | BF16, 40),
+                                        (SKIP | BF16, 24)])
+def test_lmhead_backward_puts_back_more_rows_than_one_sweep(flags, cols):
+    """Skipped rows: the kept rows' dhidden, put back by the GEMM or from its fp32 sums
+    (more than the 65,536 workgroups of one sweep put back), bit for bit those of the
+    dense call (the sums over short vocabulary blocks run in the same order)."""
     import torch
 
     import paper_2509_23866_amd as dart
@@ -490,7 +491,7 @@ def test_lmhead_backward_puts_back_more_rows_than_one_sweep(flags):
     coef[torch.rand(T, generator=g, device="cuda") < 0.05] = 0.0
     logp, _, lse = dart.dart_lmhead_tok_stats(h, w, y)
     run = lambda f: dart.dart_lmhead_backward_ex(h, w, y, lse, logp, coef, chunk_rows=T,  # noqa: E731
-                                                 chunk_cols=V, flags=f)[0]
+                                                 chunk_cols=cols, flags=f)[0]
     got, dense = run(flags), run(flags & BF16)
     kept = coef != 0
     assert int(kept.sum()) * d > 65536 * 1024

@@ -41,12 +41,13 @@ extern "C" hipError_t hipLaunchKernel(const void*, dim3 grid, dim3 block, void**
 extern "C" hipError_t hipGetLastError() { return hipSuccess; }
 
 int main(int, char** v) {
-    const long long T = atoll(v[1]), d = atoll(v[2]), V = atoll(v[3]), rows = atoll(v[4]);
-    const unsigned flags = (unsigned)atoi(v[5]);
+    const long long T = atoll(v[1]), d = atoll(v[2]), V = atoll(v[3]), rows = atoll(v[4]),
+                    cols = atoll(v[5]);
+    const unsigned flags = (unsigned)atoi(v[6]);
     void* const p = (void*)4096;
     const dart_status_t st = dart_lmhead_backward_ex(
         p, T, d, d, p, V, d, (const int32_t*)p, (const float*)p, (const float*)p, (const float*)p,
-        1.f, p, d, p, d, rows, V, flags, p, (size_t)1 << 60, (hipStream_t)0);
+        1.f, p, d, p, d, rows, cols, flags, p, (size_t)1 << 60, (hipStream_t)0);
     printf("%d %lld %lld\n", (int)st, launches, largest);
     return 0;
 }
@@ -73,14 +74,15 @@ def backward(tmp_path_factory):
 
 
 @pytest.mark.parametrize("flags", [1, 1 | 4])
-@pytest.mark.parametrize("T,d,V", [
-    (4096, 3584, 32000),
-    (1 << 22, 4096, 16),       # T d = 2^34: rows skipped, their sums put back over all of dhidden
-    (4800000, 3584, 32000),
-    (0x7FFFFFFF, 8, 16),
+@pytest.mark.parametrize("T,d,V,cols", [
+    (4096, 3584, 32000, 32000),
+    (1 << 22, 4096, 16, 8),    # T d = 2^34: rows skipped, their sums put back over all of dhidden
+    (4800000, 3584, 32000, 16000),
+    (4800000, 3584, 32000, 32000),
+    (0x7FFFFFFF, 8, 16, 8),
 ])
-def test_backward_launches_fit_a_dispatch(backward, T, d, V, flags):
+def test_backward_launches_fit_a_dispatch(backward, T, d, V, cols, flags):
     """At any T d: what is scattered back over [T, d] is launched in a bounded grid."""
-    status, launches, largest = backward(T, d, V, 1 << 16, flags)
+    status, launches, largest = backward(T, d, V, 1 << 16, cols, flags)
     assert status == 0 and launches > 0
     assert largest <= 0xFFFFFFFF
