@@ -242,7 +242,7 @@ __device__ __forceinline__ Triple triple_wave_merge(const Triple a) {
 // j % THREADS in iteration j / (THREADS * kStatsUnroll), so every wave reads 1
 // KiB contiguous per load, and the last, partial iteration is one batch too.
 // THREADS follows the row's length, see stats_threads. The gradient pass runs
-// one-shot workgroups of 128 threads x 2 vectors over 4 KB chunks of a row (best
+// one-shot workgroups of 128 threads x 2 vectors over 4 KB chunks of a bf16 row (best
 // of 32..1024 threads x 1..8 vectors, ~15% faster than one 1024-thread workgroup
 // per row and faster than a plain elementwise copy). Non-temporal loads and
 // stores win in both (see kCachedLogits); register double-buffering does not. NTL
@@ -252,6 +252,14 @@ constexpr int kStatsUnroll = 4;
 constexpr int64_t kStatsMaxRows = int64_t(1) << 22;
 constexpr int kGradThreads = 128;
 constexpr int kGradUnroll = 2;
+// fp32 rows of at least this many vectors go in 8 KB chunks, by twice the threads
+// (half the elements a byte: less arithmetic between a chunk's loads and stores).
+// Measured against 4 KB (us; in brackets before a row's coefficient decided on its
+// loads): 1000 x 152064 204 -> 191 [204], 6000 x 32003 288 -> 259 [275], 2000 x 50257
+// 136 -> 129 [133], 2048 x 32000 84.9 -> 81.0 [83.1], 1000 x 70001 91.5 -> 89.9 [89.0],
+// 3000 x 120000 449 -> 454 [443], 4000 x 5000 27.6 -> 27.2 [26.9]; but 20000 x 1000,
+// where a row does not fill a chunk, 27.4 -> 28.3. bf16: 4096 x 152064 384 -> 423.
+constexpr int64_t kGradWideVectors = 1024;
 constexpr int64_t kGradMaxBlocks = 1ll << 24;
 constexpr bool kNtStore = true;
 // Logits up to this size are loaded as any other data, larger ones
@@ -1383,25 +1391,28 @@ tis_loss_finalize_kernel(const double* __restrict__ part, int64_t nblocks,
 // dlogits[t, v] = it * g_t * (onehot(y_t)[v] - exp(it * z_tv - lse_t)), it the
 // inverse temperature, written in the logits dtype (bf16 rounded to nearest
 // even). The body of each row is cut into chunks of THREADS * UNROLL 16-byte
-// vectors, and workgroup b takes chunk b % nchunk of row b / nchunk in one
-// shot (every load of the lane in flight before its first store); chunk 0 also
-// takes the row's unaligned head and tail elements. The vectors are those of the
-// output row (16-byte stores); where the logits row has another alignment (a
-// padded head's logits cut to an odd vocabulary, the gradient contiguous) they
-// are loaded as they lie, in the same instruction. (Such rows went element by
-// element through chunk 0's workgroup: at T = 2000, V = 50257 in rows of 50304,
-// 282 us; as vectors 69 us, the bytes alone at the rate of a copy 64 us.) Small one-shot workgroups
-// walking along the rows keep HBM busier than long per-row loops. The target
-// element uses 1 - p_y = -expm1(logp_y), accurate when p_y -> 1. dlogits may
-// be the logits buffer itself (in place): each element is read, then written,
-// by the same lane. A row whose coefficient is zero (a dropped step's, a clipped
-// token's) is written without reading its logits: with a finite lse, and logits that
-// are finite or -inf, every 2^x is finite, so the product is the zero of -g's sign
-// that is written (DART_GRAD_SKIP_ZERO_ROWS: +0, whatever lse). A NaN or +inf logit
-// is not seen: the statistics drop it from the row's sums, so that lse need not tell
-// of it, and where its product would be NaN a zero is written. At T = 16384, V = 151936 with a
-// quarter of the steps kept the pass takes 1.00 ms against 1.58 for reading every
-// row, at T = 4096, V = 152064 with four fifths kept 0.375 against 0.388.
+// vectors, and workgroup b takes chunk b % nchunk of row b / nchunk in one shot;
+// chunk 0 also takes the row's unaligned head and tail elements. Small one-shot
+// workgroups walking along the rows keep HBM busier than long per-row loops. (The
+// compiler waits for a lane's first load ahead of its second, which is under a
+// condition. With both out at once 6000 x 32003 bf16 takes 135 us in place of 143, but
+// 4096 x 152064 400 in place of 384, and fp32 rows 0 to 5% longer.)
+// The vectors are those of the output row (16-byte stores); where the logits row has
+// another alignment (a padded head's logits cut to an odd vocabulary, the gradient
+// contiguous) they are loaded as they lie, in the same instruction. (Such rows went
+// element by element through chunk 0's workgroup: at T = 2000, V = 50257 in rows of
+// 50304, 282 us; as vectors 69 us, the bytes alone at the rate of a copy 64 us.)
+// The target element uses 1 - p_y = -expm1(logp_y), accurate when p_y -> 1. dlogits
+// may be the logits buffer itself (in place): each element is read, then written, by
+// the same lane.
+// A row whose coefficient is zero (a dropped step's, a clipped token's) is written
+// without reading its logits: with a finite lse, and logits that are finite or -inf,
+// every 2^x is finite, so the product is the zero of -g's sign that is written
+// (DART_GRAD_SKIP_ZERO_ROWS: +0, whatever lse). A NaN or +inf logit is not seen: the
+// statistics drop it from the row's sums, so that lse need not tell of it, and where
+// its product would be NaN a zero is written. At T = 16384, V = 151936 with a quarter
+// of the steps kept the pass takes 1.00 ms against 1.58 for reading every row, at T =
+// 4096, V = 152064 with four fifths kept 0.375 against 0.388.
 template <dart_dtype_t D, int THREADS, int UNROLL, bool NTL, bool NTS>
 __global__ void __launch_bounds__(THREADS)
 tis_grad_kernel(const void* logits, int64_t V, int64_t ld,
@@ -1934,19 +1945,27 @@ dart_status_t dart_tis_grad_ex(const void* logits, dart_dtype_t dtype, int64_t T
     if (const dart_status_t ck = dart_check::run(
             stream, {{dart_check::Item::Ids, target, T, V}}); ck != DART_OK)
         return ck;
-    // chunks of kGradThreads * kGradUnroll vectors per row; a grid of at most
-    // kGradMaxBlocks workgroups strides over the T * nchunk chunks
-    const int64_t per = (int64_t)kGradThreads * kGradUnroll;
     const int64_t nvec = V / (int64_t)(16 / es);
-    const int64_t nchunk = nvec > 0 ? (nvec + per - 1) / per : 1;
-    const int64_t nblocks = T * nchunk < kGradMaxBlocks ? T * nchunk : kGradMaxBlocks;
-    const dim3 grid((unsigned)nblocks), block(kGradThreads);
-    with_logits(dtype, T, V, [&](auto dt, auto nt) {
-        hipLaunchKernelGGL((tis_grad_kernel<decltype(dt)::value, kGradThreads, kGradUnroll,
-                                            decltype(nt)::value, kNtStore>),
-                           grid, block, 0, stream, logits, V, ld, target, lse, logp, tok_coef,
-                           inv_temp, flags, dlogits, ld_out, T, nchunk);
-    });
+    auto launch = [&](auto threads) {
+        // chunks of threads * kGradUnroll vectors per row; a grid of at most
+        // kGradMaxBlocks workgroups strides over the T * nchunk chunks
+        constexpr int N = decltype(threads)::value;
+        const int64_t per = (int64_t)N * kGradUnroll;
+        const int64_t nchunk = nvec > 0 ? (nvec + per - 1) / per : 1;
+        const int64_t nblocks = T * nchunk < kGradMaxBlocks ? T * nchunk : kGradMaxBlocks;
+        with_logits(dtype, T, V, [&](auto dt, auto nt) {
+            constexpr dart_dtype_t D = decltype(dt)::value;
+            if constexpr (N == kGradThreads || D == DART_F32)
+                hipLaunchKernelGGL((tis_grad_kernel<D, N, kGradUnroll, decltype(nt)::value, kNtStore>),
+                                   dim3((unsigned)nblocks), dim3(N), 0, stream, logits, V, ld,
+                                   target, lse, logp, tok_coef, inv_temp, flags, dlogits, ld_out, T,
+                                   nchunk);
+        });
+    };
+    if (dtype == DART_F32 && nvec >= kGradWideVectors)
+        launch(std::integral_constant<int, 2 * kGradThreads>{});
+    else
+        launch(std::integral_constant<int, kGradThreads>{});
     return launch_status();
 }
 
