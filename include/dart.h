@@ -153,10 +153,9 @@ dart_status_t dart_tis_loss_fwd_bwd(const void* logits, dart_dtype_t dtype, int6
  * T < 1 or T > INT32_MAX). Host only. */
 size_t dart_tis_loss_workspace_bytes(int64_t T);
 
-/* Bytes of workspace with which every loss call is fastest: twice the value above
- * (0 for T < 1 or T > INT32_MAX). The second half takes the partial sums of the
- * two cases that leave a smaller workspace untouched and run on one workgroup
- * there: step-level ratios of more than 32 steps (dart_tis_loss_fwd_ex), and the
+/* Bytes of workspace with which every loss call is fastest: the value above and at
+ * most 10,300 more (0 for T < 1 or T > INT32_MAX). What is beyond takes the partial sums of the two cases that leave a smaller workspace
+ * untouched and run on one workgroup there: step-level ratios of more than 32 steps (dart_tis_loss_fwd_ex), and the
  * loss of dart_select_tis_loss_fwd with T <= 4096 and 80 < S <= 8192. Host only. */
 size_t dart_tis_loss_split_workspace_bytes(int64_t T);
 

@@ -1271,8 +1271,9 @@ select_coef_kernel(const float* __restrict__ H, int64_t T, const int32_t* __rest
 // A step costs a wave ~2 us of dependent loads and fp64 arithmetic, whatever
 // its length up to a few hundred tokens, so the steps have to run beside each
 // other: 1600 steps of 95 tokens took 200 us on one workgroup (100 steps a
-// wave). A lane's next kStepBatch tokens are loaded together.
+// wave). With BATCH a lane's next kStepBatch tokens are loaded together.
 constexpr int kStepBatch = 4;
+template <bool BATCH>
 __global__ void __launch_bounds__(kStepCoefThreads)
 tis_coef_step_kernel(int64_t T, const float* __restrict__ logp, const float* __restrict__ lp_old,
                      const float* __restrict__ lp_roll, const float* __restrict__ lp_ref,
@@ -1298,8 +1299,10 @@ tis_coef_step_kernel(int64_t T, const float* __restrict__ logp, const float* __r
     const bool with_kl = cfg.kl != DART_KL_NONE;
     const double beta = (double)cfg.beta;
     double acc[kParts] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int64_t s = (int64_t)blockIdx.x * kStepCoefWaves + wave; s < S;
-         s += (int64_t)gridDim.x * kStepCoefWaves) {
+    // in a register: the grid's size would be loaded again for every step
+    uint32_t stride = gridDim.x * kStepCoefWaves;
+    asm volatile("" : "+s"(stride));
+    for (int64_t s = (int64_t)blockIdx.x * kStepCoefWaves + wave; s < S; s += stride) {
         int64_t b, e;
         step_bounds(off, s, T, b, e);
         const int64_t len = e - b;
@@ -1312,25 +1315,33 @@ tis_coef_step_kernel(int64_t T, const float* __restrict__ logp, const float* __r
         if (cfg.agg == DART_AGG_TOKEN_MEAN_ALL) om = 1.0 / (double)T;
         if (cfg.agg == DART_AGG_STEP_MEAN) om = 1.0 / ((double)K * (double)len);
         double slr = 0.0, slw = 0.0, sa = 0.0, dlog = 1.0;
-        for (int64_t t0 = b + lane; t0 < e; t0 += 64 * kStepBatch) {
-            float lp[kStepBatch], lpo[kStepBatch], lpr[kStepBatch], A[kStepBatch];
-#pragma unroll
-            for (int j = 0; j < kStepBatch; ++j) {
-                const int64_t t = t0 + 64 * j;
-                // tokens past the step's end add exact zeros
-                lp[j] = lpo[j] = lpr[j] = A[j] = 0.f;
-                if (t < e) {
-                    lp[j] = logp[t];
-                    lpo[j] = lp_old[t];
-                    lpr[j] = lp_roll[t];
-                    A[j] = adv[t];
-                }
+        if constexpr (!BATCH) {
+            for (int64_t t = b + lane; t < e; t += 64) {
+                slr += (double)logp[t] - (double)lp_old[t];
+                slw += (double)lp_old[t] - (double)lp_roll[t];
+                sa += (double)adv[t];
             }
+        } else {
+            for (int64_t t0 = b + lane; t0 < e; t0 += 64 * kStepBatch) {
+                float lp[kStepBatch], lpo[kStepBatch], lpr[kStepBatch], A[kStepBatch];
 #pragma unroll
-            for (int j = 0; j < kStepBatch; ++j) {
-                slr += (double)lp[j] - (double)lpo[j];
-                slw += (double)lpo[j] - (double)lpr[j];
-                sa += (double)A[j];
+                for (int j = 0; j < kStepBatch; ++j) {
+                    const int64_t t = t0 + 64 * j;
+                    // tokens past the step's end add exact zeros
+                    lp[j] = lpo[j] = lpr[j] = A[j] = 0.f;
+                    if (t < e) {
+                        lp[j] = logp[t];
+                        lpo[j] = lp_old[t];
+                        lpr[j] = lp_roll[t];
+                        A[j] = adv[t];
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < kStepBatch; ++j) {
+                    slr += (double)lp[j] - (double)lpo[j];
+                    slw += (double)lpo[j] - (double)lpr[j];
+                    sa += (double)A[j];
+                }
             }
         }
         slr = wave_sum(slr);
@@ -1566,13 +1577,32 @@ void launch_tok_stats(const void* logits, dart_dtype_t dtype, int64_t T, int64_t
     }
 }
 
-// The second half of a loss workspace of the split size, null where it is smaller.
-// Step ratios and small fused selections leave their partial sums there: the first
-// half is untouched by them, so that a caller may share it with them unordered.
+// Workgroups of the step ratios, for which a workspace of the split size has room: one
+// for every 16 tokens, that is, for every step a wave, however short the steps, and
+// one a compute unit at most (each counts the kept steps for itself: 20,000 steps take
+// 32 us on 149 workgroups and 45 on 1024).
+constexpr int64_t kStepMaxBlocks = 256;
+constexpr int64_t spare_blocks(int64_t T) {
+    return T > int64_t(kStepCoefWaves) * kStepMaxBlocks ? kStepMaxBlocks
+                                                       : (T + kStepCoefWaves - 1) / kStepCoefWaves;
+}
+static_assert(spare_blocks(1) >= coef_blocks(1) &&
+                  spare_blocks(kSelCoefMaxT) >= coef_blocks(kSelCoefMaxT),
+              "the spare part serves the token ratios of small fused selections too");
+
+// Step ratios load a lane's tokens in batches from this many tokens a mean step on:
+// below, most places of a batch are empty, and adding up their zeros is work. On one
+// workgroup, batches and one token at a time: 5000 steps of 1 token 573 and 546 us,
+// 20,000 of 8 2290 and 2210; 1600 of 95 229 either way.
+constexpr int64_t kStepBatchTokens = 48;
+
+// What a loss workspace of the split size has beyond the plain size, null where it is
+// smaller. Step ratios and small fused selections leave their partial sums there: the
+// plain part is untouched by them, so that a caller may share it with them unordered.
 double* spare_part(void* workspace, size_t bytes, int64_t T) {
-    const size_t half = dart_tis_loss_workspace_bytes(T);
-    return workspace && bytes >= 2 * half
-               ? reinterpret_cast<double*>(static_cast<char*>(workspace) + half)
+    return workspace && bytes >= dart_tis_loss_split_workspace_bytes(T)
+               ? reinterpret_cast<double*>(static_cast<char*>(workspace) +
+                                           dart_tis_loss_workspace_bytes(T))
                : nullptr;
 }
 
@@ -1587,12 +1617,18 @@ dart_status_t launch_tis_coef(bool general, int64_t T, const float* logp, const 
                               int nstats, void* workspace, double* spare, hipStream_t stream) {
     if (general && cfg.ratio != DART_RATIO_TOKEN) {
         // never more workgroups than the spare part has room for
-        const int64_t want = (S + kStepCoefWaves - 1) / kStepCoefWaves, room = coef_blocks(T);
+        const int64_t want = (S + kStepCoefWaves - 1) / kStepCoefWaves, room = spare_blocks(T);
         const int64_t nb = !spare || S <= kStepCoefOneBlockMaxS ? 1 : want < room ? want : room;
         double* part = nb > 1 ? spare : nullptr;
-        hipLaunchKernelGGL(tis_coef_step_kernel, dim3((unsigned)nb), dim3(kStepCoefThreads), 0,
-                           stream, T, logp, lp_old, lp_roll, lp_ref, adv, off, S, mask, cfg, coef,
-                           part, loss, stats, nstats);
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)nb), dim3(kStepCoefThreads), 0, stream, T,
+                               logp, lp_old, lp_roll, lp_ref, adv, off, S, mask, cfg, coef, part,
+                               loss, stats, nstats);
+        };
+        if (T >= kStepBatchTokens * S)
+            launch(tis_coef_step_kernel<true>);
+        else
+            launch(tis_coef_step_kernel<false>);
         if (part)
             hipLaunchKernelGGL(tis_loss_finalize_kernel, dim3(1), dim3(kCoefThreads), 0, stream,
                                part, nb, loss, stats, nstats);
@@ -1725,7 +1761,8 @@ size_t dart_tis_loss_workspace_bytes(int64_t T) {
 }
 
 size_t dart_tis_loss_split_workspace_bytes(int64_t T) {
-    return 2 * dart_tis_loss_workspace_bytes(T);
+    const size_t plain = dart_tis_loss_workspace_bytes(T);
+    return plain ? plain + (size_t)coef_workspace_doubles(spare_blocks(T)) * sizeof(double) : 0;
 }
 
 dart_status_t dart_tok_stats_ex(const void* logits, dart_dtype_t dtype, int64_t T, int64_t V,

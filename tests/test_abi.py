@@ -493,9 +493,11 @@ def test_hip_builds_disable_packed_fp32():
 
 
 def test_split_workspace_bytes():
-    """Room for the partial sums behind the workspace of every size."""
-    for T in (1, 512, 4096, 152569, 0x7FFFFFFF):
+    """The plain workspace and, behind it, 5 doubles for every workgroup of 16 steps that
+    T tokens can hold (at most 256), N and K."""
+    for T in (1, 16, 17, 512, 4096, 16384, 152569, 0x7FFFFFFF):
+        room = (min(256, -(-T // 16)) * 5 + 2) * 8
         assert (dart.dart_tis_loss_split_workspace_bytes(T)
-                == 2 * dart.dart_tis_loss_workspace_bytes(T) > 0)
+                == dart.dart_tis_loss_workspace_bytes(T) + room <= 51300)
     for T in (0, -1, 0x80000000):
         assert dart.dart_tis_loss_split_workspace_bytes(T) == 0

@@ -36,7 +36,10 @@ def _loss_inputs(rng, lens):
     (32, 40),      # the last size on one workgroup
     (33, 40),      # the first on several, the second workgroup's waves mostly idle
     (48, 257),     # a lane's second batch of tokens holds one token
-    (3000, 1),     # fewer workgroups than the steps ask for (the workspace's room)
+    (20, 47), (20, 50),  # one workgroup: a lane's tokens one by one, in batches
+    (70, 47), (70, 50),  # several
+    (3000, 1),     # as many workgroups as 3000 tokens have room for
+    (20000, 1),    # fewer workgroups than the steps ask for (the workspace's room)
     (700, 256),
 ])
 def test_step_ratio_launch_shapes(S, length, kl, ratio):
@@ -501,7 +504,7 @@ def test_lmhead_backward_puts_back_more_rows_than_one_sweep(flags, cols):
 @pytest.mark.parametrize("call", ["step ratios", "selection"])
 def test_workspace_that_stays_untouched(call):
     """Step ratios, and the loss of a small fused selection, leave a workspace of
-    dart_tis_loss_workspace_bytes alone, and of one of the split size the first half;
+    dart_tis_loss_workspace_bytes alone, and of one of the split size as much;
     with either, the same coefficients bit for bit and the same loss."""
     import torch
 
