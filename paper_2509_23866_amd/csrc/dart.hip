@@ -455,9 +455,9 @@ constexpr int kSelWaves = kSelThreads / 64;
 constexpr int kSelLdsKeys = 8192;  // groups up to this many steps keep their keys in LDS
 constexpr int kSelLdsTokens = 16384;  // one group of up to this many tokens: means fused in,
 // up to this many steps: the one workgroup takes ~1 us for every 16 of them, as long
-// as a launch of step_mean_kernel at 48. Measured (fused against two launches, us):
-// 42 steps of 96 tokens 4.8 and 4.8, 62 of 96 6.5 and 5.9, 170 of 96 13.5 and 6.1,
-// 512 of 32 23.8 and 7.6
+// as a launch of step_mean_kernel at 48. Measured (fused against two launches, us, 3000
+// tokens): 33 steps 3.9 and 4.5, 40 4.3 and 4.5, 49 4.7 and 4.6, 64 5.3 and 4.6; 512
+// steps of 32 tokens 23.8 and 7.6
 constexpr int64_t kSelFusedMaxS = 48;
 constexpr int kSelRankMax = 256;   // groups up to this many steps are ranked directly
 
@@ -644,9 +644,10 @@ __device__ __forceinline__ void select_steps(const float* __restrict__ H, int64_
 
     if (FUSED || Sg <= kSelRankMax) {
         // small group: the rank of each step among the group (higher key
-        // first, equal keys lower index first) decides directly; beyond 64
+        // first, equal keys lower index first) decides directly; beyond 16
         // steps four work-items (of four waves) share a step's comparisons
-        // (one alone: 256 steps took 4 us longer than the radix select)
+        // (one alone: 256 steps took 4 us longer than the radix select, 64 steps 5.7 us
+        // in place of 4.6, 33 4.8 in place of 4.3; 16 steps alike)
         static_assert(kSelThreads == 4 * kSelRankMax, "four work-items a step");
         const int n = (int)Sg, i = tid % kSelRankMax, way = tid / kSelRankMax;
         auto rank_of = [&](auto ways) {
@@ -660,7 +661,7 @@ __device__ __forceinline__ void select_steps(const float* __restrict__ H, int64_
             return r;
         };
         uint32_t rank = 0;
-        if (n <= 64) {
+        if (n <= 16) {
             if (tid < n) rank = rank_of(std::integral_constant<int, 1>{});
         } else {
             if (i < n) rank = rank_of(std::integral_constant<int, 4>{});

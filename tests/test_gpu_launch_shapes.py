@@ -373,7 +373,7 @@ def test_lmhead_backward_leaves_zero_rows_out(rows, cols, kept, flags):
         assert bool(((dense.double() - ref).abs() <= tol + 1e-30).all())
 
 
-@pytest.mark.parametrize("S", [1, 48, 49, 64, 65, 80, 81, 128, 256, 257])
+@pytest.mark.parametrize("S", [1, 16, 17, 48, 49, 64, 65, 80, 81, 128, 256, 257])
 @pytest.mark.parametrize("rho", [0.3, 0.8])
 def test_selection_by_number_of_steps(S, rho):
     """Step means and mask exactly the oracle's, ties between whole steps
