@@ -650,13 +650,15 @@ __device__ __forceinline__ void lmhead_dlogits_tile(
         const int64_t t = min(m0 + wr + i * C::RS, M - 1);  // rows past M are not stored
         gs[i] = coef[t], lses[i] = lse[t], ys[i] = target[t];
     }
-    // Pieces of 32 rows x 64 columns: turned into bf16 in registers, then through the
-    // wave's own part of the LDS (its accesses run in order: no barrier), so that a
-    // row's piece leaves as one 128-byte line while the next piece is formed. With the
+    // Row blocks of 32 rows x the wave's columns: turned into bf16 in registers, then
+    // through the wave's own part of the LDS (its accesses run in order: no barrier), so
+    // that a row's 256 bytes leave together while the next block is formed. With the
     // whole tile formed, a barrier, and then every store, the stores came in one burst
     // behind the exponentials, which a short K loop does not hide: at d = 512 1000 rows
-    // of V = 32000 took 42.2 us, now 38.0, 4096 of 8000 43.9 and 39.3, at d = 3584 4096
-    // of 152064 3439 and 3394.
+    // of V = 32000 took 42.2 us, now 39.9, 4096 of 8000 43.9 and 42.7, at d = 3584 4096
+    // of 152064 3439 and 3394. (128 bytes at a time are 1 to 3% better where they are
+    // whole lines, but rows of 60328 elements took 343 us in place of 300.)
+    constexpr int CPR = C::TN * 4, RPI = 64 / CPR;  // 16-byte chunks a row, rows a store
 #pragma unroll
     for (int i = 0; i < C::TM; ++i) {
         // -g, -lse log2(e), the target's gradient g (-expm1(logp)) (accurate when
@@ -664,40 +666,37 @@ __device__ __forceinline__ void lmhead_dlogits_tile(
         // chain rule through scale z)
         const float g = gs[i] * scale;
         const float neg_g = -g, neg_lse = -lses[i] * 1.4426950408889634f;
+        const int64_t yrel = (int64_t)ys[i] - vbase - n0 - wc;
+        const int y32 = yrel >= 0 && yrel < C::BN / C::WN ? (int)yrel : -1;
 #pragma unroll
-        for (int u = 0; u < C::TN / 2; ++u) {
-            const int64_t yrel = (int64_t)ys[i] - vbase - n0 - wc - u * 64;
-            const int y64 = yrel >= 0 && yrel < 64 ? (int)yrel : -1;
+        for (int j = 0; j < C::TN; ++j)
 #pragma unroll
-            for (int j = 2 * u; j < 2 * u + 2; ++j)
+            for (int v = 0; v < 16; ++v)
+                acc[i][j][v] = neg_g * __builtin_amdgcn_exp2f(fmaf(acc[i][j][v], c2, neg_lse));
+        if (y32 >= 0 && ((y32 >> 2) & 1) == half) {
+            const float dy = g * -expm1f(logp[min(m0 + wr + i * C::RS, M - 1)]);
 #pragma unroll
-                for (int v = 0; v < 16; ++v)
-                    acc[i][j][v] = neg_g * __builtin_amdgcn_exp2f(fmaf(acc[i][j][v], c2, neg_lse));
-            if (y64 >= 0 && ((y64 >> 2) & 1) == half) {
-                const float dy = g * -expm1f(logp[min(m0 + wr + i * C::RS, M - 1)]);
+            for (int j = 0; j < C::TN; ++j)
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
+                for (int v = 0; v < 16; ++v) {
+                    const int col = j * 32 + (v >> 2) * 8 + (v & 3);
+                    acc[i][j][v] = col == y32 - half * 4 ? dy : acc[i][j][v];
+                }
+        }
+        blocks_to_lds_bf16<C, C::TN>(acc[i], i, 0, sm);
+        lds_wave_order();
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const int col = j * 32 + (v >> 2) * 8 + (v & 3);
-                        acc[i][2 * u + j][v] = col == y64 - half * 4 ? dy : acc[i][2 * u + j][v];
-                    }
-            }
-            blocks_to_lds_bf16<C, 2>(&acc[i][2 * u], i, 2 * u, sm);
-            lds_wave_order();
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int r = (wave / C::WN) * 32 + i * C::RS + q * 8 + (lane >> 3);
-                const int c = wc + u * 64 + (lane & 7) * 8;
-                const int64_t t = m0 + r, col = n0 + c;
-                if (t >= M || col >= V) continue;
-                const u32x4 pk = *reinterpret_cast<const u32x4*>(&sm.c16[r][c]);
-                uint16_t* dst = out + t * ld_out + col;
-                if (col + 8 <= V)
-                    __builtin_nontemporal_store(pk, reinterpret_cast<u32x4*>(dst));
-                else
-                    for (int k = 0; k < 8 && col + k < V; ++k) dst[k] = sm.c16[r][c + k];
-            }
+        for (int q = 0; q < 32 / RPI; ++q) {
+            const int r = (wave / C::WN) * 32 + i * C::RS + q * RPI + lane / CPR;
+            const int c = wc + lane % CPR * 8;
+            const int64_t t = m0 + r, col = n0 + c;
+            if (t >= M || col >= V) continue;
+            const u32x4 pk = *reinterpret_cast<const u32x4*>(&sm.c16[r][c]);
+            uint16_t* dst = out + t * ld_out + col;
+            if (col + 8 <= V)
+                __builtin_nontemporal_store(pk, reinterpret_cast<u32x4*>(dst));
+            else
+                for (int k = 0; k < 8 && col + k < V; ++k) dst[k] = sm.c16[r][c + k];
         }
     }
 }
