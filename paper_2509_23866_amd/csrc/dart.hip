@@ -252,13 +252,15 @@ constexpr int kStatsUnroll = 4;
 constexpr int64_t kStatsMaxRows = int64_t(1) << 22;
 constexpr int kGradThreads = 128;
 constexpr int kGradUnroll = 2;
-// fp32 rows of at least this many vectors go in 8 KB chunks, by twice the threads
-// (half the elements a byte: less arithmetic between a chunk's loads and stores).
-// Measured against 4 KB (us; in brackets before a row's coefficient decided on its
-// loads): 1000 x 152064 204 -> 191 [204], 6000 x 32003 288 -> 259 [275], 2000 x 50257
-// 136 -> 129 [133], 2048 x 32000 84.9 -> 81.0 [83.1], 1000 x 70001 91.5 -> 89.9 [89.0],
-// 3000 x 120000 449 -> 454 [443], 4000 x 5000 27.6 -> 27.2 [26.9]; but 20000 x 1000,
-// where a row does not fill a chunk, 27.4 -> 28.3. bf16: 4096 x 152064 384 -> 423.
+// fp32 rows of at least this many vectors that are no whole number of 128-byte lines
+// apart go in 8 KB chunks, by twice the threads: the workgroups on both sides of a
+// chunk's end share its line, and there are half as many ends. Measured against 4 KB (us;
+// in brackets before a row's coefficient decided on its loads): 12000 x 32003 618 ->
+// 545 [599], 3000 x 32003 143 -> 129 [139], 8000 x 50257 560 -> 534 [543], 2500 x 70001
+// 232 -> 228 [225], 6000 x 17000 135 -> 133 [131]; but 20000 x 1000, where a row does not
+// fill a chunk, 27.4 -> 28.3. Rows of whole lines go either way by V (152064 -6%, 32000
+// -2%, 120000 +1%, 107392 +3 to +5%) and keep 4 KB, as bf16 rows do (4096 x 152064 384 ->
+// 423).
 constexpr int64_t kGradWideVectors = 1024;
 constexpr int64_t kGradMaxBlocks = 1ll << 24;
 constexpr bool kNtStore = true;
@@ -2003,7 +2005,8 @@ dart_status_t dart_tis_grad_ex(const void* logits, dart_dtype_t dtype, int64_t T
                                    nchunk);
         });
     };
-    if (dtype == DART_F32 && nvec >= kGradWideVectors)
+    const bool lines = (ld_out * es) % 128 == 0 && reinterpret_cast<uintptr_t>(dlogits) % 128 == 0;
+    if (dtype == DART_F32 && nvec >= kGradWideVectors && !lines)
         launch(std::integral_constant<int, 2 * kGradThreads>{});
     else
         launch(std::integral_constant<int, kGradThreads>{});
